@@ -76,6 +76,9 @@ struct ScanArgs {
 
 // Launchers implemented next to their kernels.
 hipError_t launch_scan_valu(const ssm_plan *plan, const ScanArgs &args, hipStream_t stream);
+// the fp32 matrix-core scan behind it, which is also the roll-forward over more than a few tokens (state_ptrs not null)
+bool scan_f32_supports(const ssm_shape_t &s);
+hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, void *const *state_ptrs, hipStream_t stream);
 hipError_t launch_scan_mfma(const ssm_plan *plan, const ScanArgs &args, void *workspace, hipStream_t stream);
 // events to record after the first and after the second kernel of the matrix-core scan on the calling thread
 // (nullptr: none)

@@ -18,6 +18,9 @@ namespace {
 
 constexpr int kAdvThreads = 256;
 constexpr int kAdvMaxRows = 8;  // state rows per thread
+// A batch with a longer sequence is rolled forward by the 16-token tiles of scan_valu.hip (fp32 as here): the token loop
+// is one chain of dependent loads, 1.8 us a token.  Three sequences of 17 to 256 tokens at 128 heads: 466 -> 54 us.
+constexpr int kAdvMaxTokens = 4;
 constexpr float kAdvLog2e = 1.4426950408889634f;
 
 #define ADV_DPP(v, ctrl, row_mask)                                                                            \
@@ -232,6 +235,14 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
         return hipErrorInvalidValue;
     if (plan->batch == 0 || plan->tiles.empty())
         return hipSuccess;
+    int longest = 0;
+    for (const SsmSeq &q : plan->seqs)
+        if (q.tile_end > q.tile_begin) {
+            const SsmTile &first = plan->tiles[q.tile_begin], &last = plan->tiles[q.tile_end - 1];
+            longest = last.tok0 + last.len - first.tok0 > longest ? last.tok0 + last.len - first.tok0 : longest;
+        }
+    if (longest > kAdvMaxTokens && scan_f32_supports(plan->shape))
+        return launch_scan_f32(plan, args, d_state_ptrs, stream);
     AdvanceArgs a;
     a.x = args.x;
     a.dt = args.dt;

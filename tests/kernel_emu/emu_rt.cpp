@@ -13,6 +13,7 @@
 //   mfma_f32_32x32x16_bf16  A: lane l holds row l%32, k = 8(l/32)+e;  B: lane l holds column l%32, same k;
 //                           C/D: lane l, element r: column l%32, row 8(r/4) + 4(l/32) + r%4
 //   mfma_f32_16x16x32_bf16  A: row l%16, k = 8(l/16)+e;  C/D: column l%16, row 4(l/16)+r
+//   mfma_f32_16x16x4_f32    A: row l%16, k = l/16;  B: column l%16, same k;  C/D as above
 //   ds_read_tr16_b64        per 16 lanes: lane i receives as element e the 16-bit element i%4 of the 8 bytes that
 //                           lane 4e + i/4 of the group points at
 // Products are accumulated in double and rounded once; the matrix cores round differently in the last bits.
@@ -30,7 +31,7 @@
 namespace emu {
 namespace {
 enum St { RUN, W_WAVE, W_BARRIER, DONE };
-enum Op { OP_NONE, OP_SYNC, OP_MFMA32, OP_MFMA32H, OP_MFMA16, OP_TR, OP_DPP, OP_READLANE, OP_READFIRST, OP_SHFL, OP_YIELD };
+enum Op { OP_NONE, OP_SYNC, OP_MFMA32, OP_MFMA32H, OP_MFMA16, OP_MFMA4F, OP_TR, OP_DPP, OP_READLANE, OP_READFIRST, OP_SHFL, OP_YIELD };
 
 struct Coll {
     int op = OP_NONE, line = 0;
@@ -160,6 +161,26 @@ void run_collective(Lane *L)
             f32x4 d;
             for (int r = 0; r < 4; ++r)
                 d[r] = (float)(acc[4 * (l / 16) + r][l % 16] + (double)c[r]);
+            *static_cast<f32x4 *>(L[l].k.res) = d;
+        }
+        break;
+    }
+    case OP_MFMA4F: {
+        // A: lane l holds row l%16, k = l/16.  B: column l%16, same k.  C/D: lane l, element r: column l%16, row 4(l/16) + r.
+        float A[16][4], B[4][16];
+        for (int l = 0; l < 64; ++l) {
+            A[l % 16][l / 16] = *static_cast<const float *>(L[l].k.a);
+            B[l / 16][l % 16] = *static_cast<const float *>(L[l].k.b);
+        }
+        for (int l = 0; l < 64; ++l) {
+            const f32x4 c = *static_cast<const f32x4 *>(L[l].k.c);
+            f32x4 d;
+            for (int r = 0; r < 4; ++r) {
+                double acc = (double)c[r];
+                for (int kk = 0; kk < 4; ++kk)
+                    acc += (double)A[4 * (l / 16) + r][kk] * (double)B[kk][l % 16];
+                d[r] = (float)acc;
+            }
             *static_cast<f32x4 *>(L[l].k.res) = d;
         }
         break;
@@ -448,6 +469,14 @@ f32x4 mfma_16x16x32_bf16(bf16x8 a, bf16x8 b, f32x4 c, int line)
     f32x4 res;
     cur->k.a = &a, cur->k.b = &b, cur->k.c = &c, cur->k.res = &res;
     collective(OP_MFMA16, line);
+    return res;
+}
+
+f32x4 mfma_16x16x4_f32(float a, float b, f32x4 c, int line)
+{
+    f32x4 res;
+    cur->k.a = &a, cur->k.b = &b, cur->k.c = &c, cur->k.res = &res;
+    collective(OP_MFMA4F, line);
     return res;
 }
 

@@ -60,6 +60,7 @@ void wave_yield(int line);  // inside a spin-wait: the other waves of the workgr
 f32x16 mfma_32x32x16_bf16(bf16x8 a, bf16x8 b, f32x16 c, int line);
 f32x16 mfma_32x32x16_f16(f16x8 a, f16x8 b, f32x16 c, int line);
 f32x4 mfma_16x16x32_bf16(bf16x8 a, bf16x8 b, f32x4 c, int line);
+f32x4 mfma_16x16x4_f32(float a, float b, f32x4 c, int line);
 s16x4 ds_read_tr16_b64(const void *p, int line);
 int update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool bound_ctrl, int line);
 int readlane(int v, int lane, int line);
@@ -115,6 +116,7 @@ template <typename F> void launch(dim3 grid, dim3 block, size_t lds_bytes, F &&b
 #define __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, x, y, z) emu::mfma_32x32x16_bf16((a), (b), (c), __LINE__)
 #define __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, x, y, z) emu::mfma_32x32x16_f16((a), (b), (c), __LINE__)
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) emu::mfma_16x16x32_bf16((a), (b), (c), __LINE__)
+#define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) emu::mfma_16x16x4_f32((a), (b), (c), __LINE__)
 #define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) emu::ds_read_tr16_b64((const void *)(p), __LINE__)
 #define __builtin_amdgcn_update_dpp(old, src, ctrl, rm, bm, bc) emu::update_dpp((old), (src), (ctrl), (rm), (bm), (bc), __LINE__)
 #define __builtin_amdgcn_readlane(v, l) emu::readlane((v), (l), __LINE__)
