@@ -173,12 +173,12 @@ static void fill_args(const ssm_plan *plan, ScanArgs &args, const void *tiles, c
     args.state_dtype = plan->shape.state_dtype;
 }
 
-// Launch the scan with the plan's tables at the given device addresses; `d_init_ptrs` is null when no sequence
-// starts from a cached state.
+// Launch the scan with the plan's tables at the given device addresses.  The initial states' pointers come as a device
+// array or, for a batch small enough, as the host array itself; both are null when no sequence starts from one.
 static int launch_scan(const ssm_plan *plan, const void *x, const void *dt, const float *A, const void *B,
                        const void *C, const float *D, void *y_out, void *state_out, void *workspace,
                        const void *d_tiles, const void *d_seqs, const void *d_scan_seqs, const void *d_init_ptrs,
-                       hipStream_t stream)
+                       const void *const *host_ptrs, hipStream_t stream)
 {
     ScanArgs args;
     args.x = x;
@@ -190,6 +190,8 @@ static int launch_scan(const ssm_plan *plan, const void *x, const void *dt, cons
     args.y = y_out;
     args.state_out = state_out;
     args.init_ptrs = static_cast<const void *const *>(d_init_ptrs);
+    args.host_ptrs = host_ptrs;
+    args.n_host_ptrs = host_ptrs ? plan->batch : 0;
     fill_args(plan, args, d_tiles, d_seqs, d_scan_seqs);
     const hipError_t e = plan->path == SSM_PATH_MFMA_BF16 ? launch_scan_mfma(plan, args, workspace, stream)
                                                           : launch_scan_valu(plan, args, stream);
@@ -220,13 +222,14 @@ extern "C" int ssm_prefill(const ssm_plan_t *plan,
     rc = device_tables(plan, stream, &t);
     if (rc != SSM_OK)
         return rc;
-    if (any_init) {
+    const bool in_args = any_init && plan->batch <= kStatePtrsInArgs, in_table = any_init && !in_args;
+    if (in_table) {
         const hipError_t e = upload_table(t.ptrs, init_state_ptrs, (size_t)plan->batch * sizeof(void *), stream);
         if (e != hipSuccess)
             return hip_fail("upload of the initial-state pointers", e);
     }
     return launch_scan(plan, x, dt, A, B, C, D, y_out, state_out, workspace, t.tiles, t.seqs, t.scan_seqs,
-                       any_init ? t.ptrs : nullptr, stream);
+                       in_table ? t.ptrs : nullptr, in_args ? init_state_ptrs : nullptr, stream);
 }
 
 // ---------------------------------------------------------------- the scan for callers that cannot allocate
@@ -301,12 +304,14 @@ extern "C" int ssm_prefill_noalloc(const ssm_plan_t *plan,
     if (e == hipSuccess)
         e = upload_table(base + kScratchScanSeqsOff, plan->scan_seqs.data(), plan->scan_seqs.size() * sizeof(SsmScanSeq),
                          stream);
-    if (e == hipSuccess && any_init)
+    const bool in_args = any_init && plan->batch <= kStatePtrsInArgs, in_table = any_init && !in_args;
+    if (e == hipSuccess && in_table)
         e = upload_table(base + kScratchPtrsOff, init_state_ptrs, (size_t)plan->batch * sizeof(void *), stream);
     if (e != hipSuccess)
         return hip_fail("upload of the plan's tables into the fixed device array", e);
     return launch_scan(plan, x, dt, A, B, C, D, y_out, state_out, workspace, base, base + kScratchSeqsOff,
-                       base + kScratchScanSeqsOff, any_init ? base + kScratchPtrsOff : nullptr, stream);
+                       base + kScratchScanSeqsOff, in_table ? base + kScratchPtrsOff : nullptr,
+                       in_args ? init_state_ptrs : nullptr, stream);
 }
 
 // ---------------------------------------------------------------- roll-forward / decode step
@@ -338,10 +343,15 @@ extern "C" int ssm_state_advance(const ssm_plan_t *plan,
     rc = device_tables(plan, stream, &t);
     if (rc != SSM_OK)
         return rc;
-    hipError_t e = upload_table(t.ptrs, state_ptrs, (size_t)plan->batch * sizeof(void *), stream);
+    hipError_t e = hipSuccess;
+    const bool in_args = plan->batch <= kStatePtrsInArgs;
+    if (!in_args)
+        e = upload_table(t.ptrs, state_ptrs, (size_t)plan->batch * sizeof(void *), stream);
     if (e != hipSuccess)
         return hip_fail("upload of the state pointers", e);
     ScanArgs args;
+    args.host_ptrs = in_args ? state_ptrs : nullptr;
+    args.n_host_ptrs = in_args ? plan->batch : 0;
     args.x = x;
     args.dt = dt;
     args.A = A;
@@ -389,15 +399,16 @@ extern "C" int ssm_conv1d_prefill(const ssm_plan_t *plan, int32_t channels, int3
     rc = device_tables(plan, stream, &t);
     if (rc != SSM_OK)
         return rc;
-    if (any_init) {
+    const bool in_args = any_init && plan->batch <= kStatePtrsInArgs, in_table = any_init && !in_args;
+    if (in_table) {
         const hipError_t e = upload_table(t.ptrs, init_state_ptrs, (size_t)plan->batch * sizeof(void *), stream);
         if (e != hipSuccess)
             return hip_fail("upload of the initial-state pointers", e);
     }
     const hipError_t e = launch_conv1d_prefill(
         plan, static_cast<const SsmTile *>(t.tiles), static_cast<const SsmSeq *>(t.seqs), channels, kernel_width, in,
-        weight, bias, any_init ? static_cast<const void *const *>(t.ptrs) : nullptr, out, state_out, activation,
-        stream);
+        weight, bias, in_table ? static_cast<const void *const *>(t.ptrs) : nullptr, out, state_out, activation,
+        stream, in_args ? init_state_ptrs : nullptr, in_args ? plan->batch : 0);
     if (e != hipSuccess)
         return hip_fail("kernel launch", e);
     return SSM_OK;

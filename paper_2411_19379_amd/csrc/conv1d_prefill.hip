@@ -60,7 +60,7 @@ struct ConvArgs {
     const float *w;                 // [Cch,K]
     const float *bias;              // [Cch] or null
     void *out;                      // [T,Cch] storage type
-    const void *const *init_ptrs;   // null, or [batch] device pointers (null entry = zeros) to [Cch,K] storage type
+    StatePtrs init;                 // [batch] device pointers (null = zeros) to [Cch,K] storage type
     void *state_out;                // [n_ckpt,Cch,K] storage type
     const SsmTile *tiles;
     const SsmSeq *seqs;
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kConvThreads) void ssm_conv1d_kernel(ConvArgs a)
 
     const IO *__restrict__ in = static_cast<const IO *>(a.in);  // the caller keeps in and out apart
     IO *__restrict__ out = static_cast<IO *>(a.out);
-    const IO *init = a.init_ptrs ? static_cast<const IO *>(a.init_ptrs[t.seq]) : nullptr;
+    const IO *init = static_cast<const IO *>(a.init.of(__builtin_amdgcn_readfirstlane(t.seq)));
 
     float wk[K][V], bias[V];
 #pragma unroll
@@ -185,7 +185,7 @@ bool conv1d_supports(int channels, int K, int io_dtype)
 hipError_t launch_conv1d_prefill(const ssm_plan *plan, const SsmTile *d_tiles, const SsmSeq *d_seqs, int channels,
                                  int K, const void *in, const float *w, const float *bias,
                                  const void *const *d_init_ptrs, void *out, void *state_out, int act,
-                                 hipStream_t stream)
+                                 hipStream_t stream, const void *const *host_ptrs, int n_host_ptrs)
 {
     if (!conv1d_supports(channels, K, plan->shape.io_dtype))
         return hipErrorInvalidValue;
@@ -198,7 +198,7 @@ hipError_t launch_conv1d_prefill(const ssm_plan *plan, const SsmTile *d_tiles, c
     a.w = w;
     a.bias = bias;
     a.out = out;
-    a.init_ptrs = d_init_ptrs;
+    a.init = state_ptrs_of(d_init_ptrs, host_ptrs, n_host_ptrs);
     a.state_out = state_out;
     a.tiles = d_tiles;
     a.seqs = d_seqs;

@@ -55,6 +55,20 @@ __device__ __forceinline__ void state_store(void *base, size_t idx, float v, int
         static_cast<float *>(base)[idx] = v;
 }
 
+// The per-call state pointers of a batch.  Up to kStatePtrsInArgs of them travel in the kernel's own arguments; a larger
+// batch reads them from a device array that another launch has filled.  (A launch of its own for a few pointers costs 1
+// to 5 us in front of every call; 64 pointers are half a KiB of arguments, which costs nothing measurable.)
+constexpr int kStatePtrsInArgs = 64;
+struct StatePtrs {
+    const void *const *table;  // device array, or null
+    int32_t n;                 // entries in p; 0: use the table
+    const void *p[kStatePtrsInArgs];
+    __device__ __forceinline__ const void *of(int seq) const
+    {
+        return n > 0 ? p[seq] : table ? table[seq] : nullptr;
+    }
+};
+
 // Arguments common to the scan kernels.  Pointers are device pointers.
 struct ScanArgs {
     const void *x;
@@ -72,13 +86,25 @@ struct ScanArgs {
     int32_t H, P, N, G;
     int32_t p_split;
     int32_t state_dtype;            // ssm_state_dtype_t
+    const void *const *host_ptrs = nullptr;  // the same pointers as a host array of n_host_ptrs <= kStatePtrsInArgs
+    int32_t n_host_ptrs = 0;                 // entries (then the device array is not needed)
 };
+
+inline StatePtrs state_ptrs_of(const void *const *device_table, const void *const *host, int n)
+{
+    StatePtrs s = {};
+    s.table = device_table;
+    s.n = host ? n : 0;
+    for (int i = 0; i < s.n; ++i)
+        s.p[i] = host[i];
+    return s;
+}
 
 // Launchers implemented next to their kernels.
 hipError_t launch_scan_valu(const ssm_plan *plan, const ScanArgs &args, hipStream_t stream);
-// the fp32 matrix-core scan behind it, which is also the roll-forward over more than a few tokens (state_ptrs not null)
+// the fp32 matrix-core scan behind it, which is also the roll-forward over more than a few tokens
 bool scan_f32_supports(const ssm_shape_t &s);
-hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, void *const *state_ptrs, hipStream_t stream);
+hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll, hipStream_t stream);
 hipError_t launch_scan_mfma(const ssm_plan *plan, const ScanArgs &args, void *workspace, hipStream_t stream);
 // events to record after the first and after the second kernel of the matrix-core scan on the calling thread
 // (nullptr: none)
@@ -90,4 +116,4 @@ bool conv1d_supports(int channels, int K, int io_dtype);
 hipError_t launch_conv1d_prefill(const ssm_plan *plan, const SsmTile *d_tiles, const SsmSeq *d_seqs, int channels,
                                  int K, const void *in, const float *w, const float *bias,
                                  const void *const *d_init_ptrs, void *out, void *state_out, int act,
-                                 hipStream_t stream);
+                                 hipStream_t stream, const void *const *host_ptrs = nullptr, int n_host_ptrs = 0);

@@ -428,7 +428,7 @@ struct LdsT {
 template <int ST, int NC, int NW>
 __global__ __launch_bounds__(64 * NW) void ssm_scan_mfma_kernel(
     const bf16_t *__restrict__ x, const float *__restrict__ A_, const float *__restrict__ D_, bf16_t *__restrict__ y,
-    void *__restrict__ state_out, const void *const *__restrict__ init_ptrs, const uint4 *__restrict__ frags,
+    void *__restrict__ state_out, StatePtrs init_ptrs, const uint4 *__restrict__ frags,
     const bf16_t *__restrict__ dt_t, const SsmTile *__restrict__ tiles, const SsmScanSeq *__restrict__ scan_seqs,
     float *__restrict__ tile_decay, float *__restrict__ carry, int H, int P, int G, int p_split, int n_items,
     int n_tiles_all)
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_mfma_kernel(
     const int pbase = ps * kCh;
     const float Ah = A_[h], Dh = D_[h];
     const SsmScanSeq sq = scan_seqs[stretch];
-    const void *init = init_ptrs && sq.init_seq >= 0 ? init_ptrs[sq.init_seq] : nullptr;
+    const void *init = sq.init_seq >= 0 ? init_ptrs.of(sq.init_seq) : nullptr;
     const int tile_begin = sq.tile_begin;
     const int n_tiles = sq.tile_end - sq.tile_begin;
     if (n_tiles <= 0)
@@ -1060,7 +1060,7 @@ hipError_t launch_scan_st(const ssm_plan *plan, const ScanArgs &args, const uint
         return hipSuccess;  // every sequence is empty
     hipLaunchKernelGGL((ssm_scan_mfma_kernel<ST, NC, NW>), dim3((unsigned)ssm_launch_blocks(plan->n_items)), dim3(64 * NW), lds,
                        stream, static_cast<const bf16_t *>(args.x), args.A, args.D, static_cast<bf16_t *>(args.y),
-                       args.state_out, args.init_ptrs, frags, dt_t, args.tiles, args.scan_seqs, tile_decay, carry, args.H,
+                       args.state_out, state_ptrs_of(args.init_ptrs, args.host_ptrs, args.n_host_ptrs), frags, dt_t, args.tiles, args.scan_seqs, tile_decay, carry, args.H,
                        args.P, args.G, args.p_split, plan->n_items, (int)plan->tiles.size());
     return hipGetLastError();
 }

@@ -71,8 +71,8 @@ struct F32Args {
     const float *A, *D;
     void *y;                        // may be null (roll-forward without outputs)
     void *state_out;                // [n_ckpt,H,P,N] in the state type (scan)
-    const void *const *init_ptrs;   // [batch] or null (scan)
-    void *const *state_ptrs;        // [batch]: roll-forward in place; null in the scan
+    StatePtrs init;                 // [batch]: the states the scan starts from, or those the roll-forward advances
+    bool roll;                      // roll-forward in place
     const SsmTile *tiles;
     const SsmSeq *seqs;
     int H, P, G, slices, state_dtype;
@@ -187,9 +187,9 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
     const int g = h / (H / G);
     const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool roll = a.state_ptrs != nullptr;
+    const bool roll = a.roll;
     const SsmSeq sq = a.seqs[seq];
-    const void *from = roll ? a.state_ptrs[seq] : a.init_ptrs ? a.init_ptrs[seq] : nullptr;
+    const void *from = a.init.of(seq);
     if (sq.tile_end <= sq.tile_begin || (roll && !from))
         return;  // nothing to scan; the whole workgroup leaves
     // The scan takes the plan's tiles, which end at checkpoints; the roll-forward knows no checkpoints and cuts the
@@ -396,7 +396,7 @@ constexpr int kThreads = 256;
 constexpr int kQ = kValuTileTokens;
 
 template <typename IO, int EPT>
-__global__ __launch_bounds__(kThreads) void ssm_scan_valu_kernel(ScanArgs a)
+__global__ __launch_bounds__(kThreads) void ssm_scan_valu_kernel(ScanArgs a, StatePtrs from)
 {
     const int tid = threadIdx.x;
     const int H = a.H, P = a.P, N = a.N, G = a.G;
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kThreads) void ssm_scan_valu_kernel(ScanArgs a)
 
     // running state: element e = tid + k*256 of this head's [P,N] block
     float acc[EPT];
-    const void *init = a.init_ptrs ? a.init_ptrs[seq] : nullptr;
+    const void *init = from.of(seq);
     const int st = a.state_dtype;
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
@@ -525,7 +525,8 @@ template <typename IO>
 hipError_t launch_ept(int ept, dim3 grid, size_t lds, hipStream_t stream, const ScanArgs &args)
 {
 #define SSM_LAUNCH(E)                                                                     \
-    hipLaunchKernelGGL((ssm_scan_valu_kernel<IO, E>), grid, dim3(kThreads), lds, stream, args); \
+    hipLaunchKernelGGL((ssm_scan_valu_kernel<IO, E>), grid, dim3(kThreads), lds, stream, args, \
+                       state_ptrs_of(args.init_ptrs, args.host_ptrs, args.n_host_ptrs));        \
     break;
     switch (ept) {
     case 1: SSM_LAUNCH(1)
@@ -547,16 +548,17 @@ bool scan_f32_supports(const ssm_shape_t &s)
     return s.headdim % 16 == 0 && (n == 16 || n == 32 || n == 64 || n == 128);
 }
 
-// With state_ptrs: the roll-forward, states advanced in place.  Without: the scan over the plan's tiles.
-hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, void *const *state_ptrs, hipStream_t stream)
+// roll: the states behind init_ptrs / host_ptrs are advanced in place over the sequences' tokens.  Else the scan over the
+// plan's tiles.
+hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll, hipStream_t stream)
 {
     F32Args a;
     a.x = args.x, a.dt = args.dt, a.B = args.B, a.C = args.C;
     a.A = args.A, a.D = args.D;
     a.y = args.y;
     a.state_out = args.state_out;
-    a.init_ptrs = args.init_ptrs;
-    a.state_ptrs = state_ptrs;
+    a.init = state_ptrs_of(args.init_ptrs, args.host_ptrs, args.n_host_ptrs);
+    a.roll = roll;
     a.tiles = args.tiles;
     a.seqs = args.seqs;
     a.H = args.H, a.P = args.P, a.G = args.G;
@@ -587,7 +589,7 @@ size_t ssm_valu_lds_bytes(int P, int N);
 hipError_t launch_scan_valu(const ssm_plan *plan, const ScanArgs &args, hipStream_t stream)
 {
     if (scan_f32_supports(plan->shape))
-        return launch_scan_f32(plan, args, nullptr, stream);
+        return launch_scan_f32(plan, args, false, stream);
     const int PN = args.P * args.N;
     int ept = 1;
     while (ept * kThreads < PN)

@@ -99,7 +99,7 @@ struct AdvanceArgs {
     const void *x, *dt, *B, *C;
     const float *A, *D;
     void *y;                   // may be null
-    void *const *state_ptrs;   // [batch] device pointers, each [H,P,N] in the state type; null = leave the sequence alone
+    StatePtrs states;          // [batch] device pointers, each [H,P,N] in the state type; null = leave the sequence alone
     const SsmTile *tiles;
     const SsmSeq *seqs;
     int H, P, N, G;
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
     const int p_first = slice * kRowsPerPass * R + rs;  // rows p_first + kRowsPerPass * r
 
     const SsmSeq sq = a.seqs[seq];
-    state_t *state = static_cast<state_t *>(a.state_ptrs[seq]);
+    state_t *state = static_cast<state_t *>(const_cast<void *>(a.states.of(seq)));
     if (sq.tile_end <= sq.tile_begin || state == nullptr)
         return;  // nothing to advance; the whole workgroup leaves
 
@@ -225,7 +225,7 @@ bool state_advance_supports(const ssm_shape_t &s)
 }
 
 // Advance the state of every sequence of the plan in place by the sequence's tokens; `d_state_ptrs` is a device array
-// of plan->batch device pointers to states in the plan's state type.  y may be null.
+// of plan->batch device pointers to states in the plan's state type (not needed if args.host_ptrs is set).  y may be null.
 // Checkpoints of the plan are ignored (the result is the in-place state after the last token).
 hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void *const *d_state_ptrs,
                                 hipStream_t stream)
@@ -242,7 +242,11 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
             longest = last.tok0 + last.len - first.tok0 > longest ? last.tok0 + last.len - first.tok0 : longest;
         }
     if (longest > kAdvMaxTokens && scan_f32_supports(plan->shape))
-        return launch_scan_f32(plan, args, d_state_ptrs, stream);
+    {
+        ScanArgs roll = args;
+        roll.init_ptrs = d_state_ptrs;
+        return launch_scan_f32(plan, roll, true, stream);
+    }
     AdvanceArgs a;
     a.x = args.x;
     a.dt = args.dt;
@@ -251,7 +255,7 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
     a.A = args.A;
     a.D = args.D;
     a.y = args.y;
-    a.state_ptrs = d_state_ptrs;
+    a.states = state_ptrs_of(d_state_ptrs, args.host_ptrs, args.n_host_ptrs);
     a.tiles = args.tiles;
     a.seqs = args.seqs;
     a.H = args.H;
