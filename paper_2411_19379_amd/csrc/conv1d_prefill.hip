@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kConvThreads) void ssm_conv1d_kernel(ConvArgs a)
 
     const IO *__restrict__ in = static_cast<const IO *>(a.in);  // the caller keeps in and out apart
     IO *__restrict__ out = static_cast<IO *>(a.out);
-    const IO *init = static_cast<const IO *>(a.init.of(__builtin_amdgcn_readfirstlane(t.seq)));
+    const IO *init = static_cast<const IO *>(a.init.of(t.seq));
 
     float wk[K][V], bias[V];
 #pragma unroll
