@@ -49,7 +49,10 @@ static int choose_path(const ssm_shape_t &s, ssm_plan *plan)
         return fail(SSM_ERR_UNSUPPORTED_SHAPE, "shape needs more than 64 KiB of LDS in the fp32 kernel");
     plan->path = SSM_PATH_VALU_F32;
     plan->p_split = 1;
-    plan->tile_tokens = kValuTileTokens;
+    // bf16 storage on the fp32 matrix-core path works in units of 32 tokens (split operands)
+    const bool split = s.io_dtype == SSM_DT_BF16 && P % 16 == 0 && (N == 16 || N == 32 || N == 64 || N == 128);
+    const int tile = split ? kSplitTileTokens : kValuTileTokens;
+    plan->tile_tokens = s.chunk < tile ? s.chunk : tile;
     return SSM_OK;
 }
 

@@ -128,6 +128,7 @@ SsmMfmaWorkspace ssm_mfma_workspace(const ssm_plan *plan);
 
 // Tile lengths the two kernel families work with.
 constexpr int kValuTileTokens = 16;
+constexpr int kSplitTileTokens = 32;
 constexpr int kMfmaTileTokens = 64;
 
 // Workspace of the matrix-core scan: per (tile, group) the operands the heads of a group share (C and B^T as fp16

@@ -9,8 +9,9 @@
 //   S_e  = e^{l_q} S_s + sum_j e^{l_q-l_j} dt_j x_j B_j^T
 //
 // which is the token recurrence of ssm_prefill.h unrolled over the tile.  Where d_state is 16, 32, 64 or 128 and headdim
-// a multiple of 16 the contractions run on the matrix cores in fp32 (ssm_scan_f32_kernel); any other shape takes the
-// vector ALUs (ssm_scan_valu_kernel).
+// a multiple of 16 the contractions run on the matrix cores: with fp32 instructions for f32 storage (ssm_scan_f32_kernel),
+// with bf16 ones on split operands for bf16 storage (ssm_scan_split_kernel, units of 32 tokens).  Any other shape takes
+// the vector ALUs (ssm_scan_valu_kernel).
 #include "device_utils.h"
 
 namespace {
@@ -34,8 +35,8 @@ namespace {
 // What bounds it: the matrix cores, whose fp32 rate is a sixteenth of their bf16 one (NC (8 NB + 4) + 4 NB products of
 // 32 cycles per tile; the 4 NB of the scores are the same for every slice, hence NC > 1), and the chain of hand-offs.
 // Against the vector-ALU kernel below (one workgroup per head, five barriers per 16 tokens, dot products from LDS), per
-// call: 80 heads x 64 channels, d_state 128, 2048 tokens in fp32 8180 -> 141 us; 32 heads x 64 channels, d_state 16, eight
-// requests of 18 K tokens in all, bf16 storage, 2130 -> 109 us; 4 heads x 16 channels, d_state 16, 256 tokens 64 -> 12 us.
+// call: 80 heads x 64 channels, d_state 128, 2048 tokens 8180 -> 146 us; 4 heads x 16 channels, d_state 16, 256 tokens
+// 64 -> 12 us.
 constexpr int kF32SpinLimit = 1 << 16;  // polls of the hand-off counter before a wave gives up waiting (milliseconds)
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((address_space(3))) int lds_int_t;
@@ -76,6 +77,7 @@ struct F32Args {
     const SsmTile *tiles;
     const SsmSeq *seqs;
     int H, P, G, slices, state_dtype;
+    int units_per_tile = 1;         // split-operand kernel: units of 32 tokens per tile of the plan
 };
 
 // n values (a multiple of 4, or 1 or 2) of the storage type as floats; p is aligned to the run's size, at most 16 bytes
@@ -119,24 +121,33 @@ template <int NV> __device__ __forceinline__ void load_run(const bf16_t *p, floa
     }
 }
 
-// Four neighbouring elements of a cached state.
+// Four neighbouring elements of a cached state (index a multiple of four).
+typedef __attribute__((ext_vector_type(4))) _Float16 st_f16x4;
 __device__ __forceinline__ float4 state_load4(const void *base, size_t idx, int st)
 {
-    if (st == SSM_ST_F32)
-        return *reinterpret_cast<const float4 *>(static_cast<const float *>(base) + idx);
-    return make_float4(state_load(base, idx, st), state_load(base, idx + 1, st), state_load(base, idx + 2, st),
-                       state_load(base, idx + 3, st));
+    if (st == SSM_ST_F16) {
+        const st_f16x4 v = *reinterpret_cast<const st_f16x4 *>(static_cast<const _Float16 *>(base) + idx);
+        return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+    }
+    if (st == SSM_ST_BF16) {
+        const uint2 u = *reinterpret_cast<const uint2 *>(static_cast<const bf16_t *>(base) + idx);
+        return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                           __uint_as_float(u.y & 0xffff0000u));
+    }
+    return *reinterpret_cast<const float4 *>(static_cast<const float *>(base) + idx);
 }
 __device__ __forceinline__ void state_store4(void *base, size_t idx, float4 v, int st)
 {
-    if (st == SSM_ST_F32) {
+    if (st == SSM_ST_F16) {
+        const st_f16x4 h = {(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
+        *reinterpret_cast<st_f16x4 *>(static_cast<_Float16 *>(base) + idx) = h;
+    } else if (st == SSM_ST_BF16) {
+        *reinterpret_cast<uint2 *>(static_cast<bf16_t *>(base) + idx) =
+            make_uint2((uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16),
+                       (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16));
+    } else {
         *reinterpret_cast<float4 *>(static_cast<float *>(base) + idx) = v;
-        return;
     }
-    state_store(base, idx, v.x, st);
-    state_store(base, idx + 1, v.y, st);
-    state_store(base, idx + 2, v.z, st);
-    state_store(base, idx + 3, v.w, st);
 }
 
 #define F32_DPP64(v, ctrl)                                                                                         \
@@ -174,9 +185,10 @@ template <int NB, int NC, int NW> struct F32Lds {
     F32Wave wv[NW];
 };
 
-template <typename IO, int NB, int NC, int NW>
+template <int NB, int NC, int NW>
 __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
 {
+    typedef float IO;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     F32Lds<NB, NC, NW> &L = *reinterpret_cast<F32Lds<NB, NC, NW> *>(lds_raw);
     constexpr int N = 16 * NB;
@@ -359,35 +371,572 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
     }
 }
 
-template <typename IO, int NB, int NC>
+// ================================================================ matrix cores, bf16 storage: split operands
+// The same scan for bf16 x, dt, B, C and y.  B, C and x are bf16 already, so of every product only one factor is a
+// 32-bit value (the decay-weighted x, the masked scores, the state), and a 32-bit value is exactly the sum of three
+// bf16 ones (8 + 8 + 8 bits of its significand).  Three v_mfma_f32_16x16x32_bf16 therefore give the same products
+// added up in fp32 as the fp32 instruction does, in 3/16 of its time, and the scores C.B take a single one.  Against
+// 64 bits it is no further off than the fp32 instruction was.
+//
+// One workgroup per (sequence, head, NC slices of 16 channels); its waves take units of 32 tokens round-robin and each
+// computes all of its unit, the state handed from wave to wave through LDS as in the fp32 kernel above.  A unit is a
+// whole tile of the plan, or half of a 64-token one; the roll-forward cuts the sequence's tokens itself.
+//
+// Layouts (kq = lane / 16, li = lane % 16; an operand holds row or column li, k = 8 kq + e; a result element r is row
+// 4 kq + r, column li).  Any order of the k index will do as long as both operands use the same one, so every operand is
+// read from device memory in runs of neighbouring elements and what one product leaves in its result registers is what
+// the next takes as an operand; nothing passes through LDS but the state and the tables of decay factors:
+//   tokens     slot (kq, e) is token 16 (e / 4) + 4 kq + e % 4: the tokens whose results the lane holds
+//   state      slot (kq, f) is state index 4 NB kq + f; row i of result block nb is state index NB i + nb
+//   channels   column i of slice c is channel NC i + c of the workgroup's 16 NC
+// With d_state 16 a lane holds four state indices per product and the other four slots take the second part of the
+// split; the first 16 queries of a unit have only 16 keys and do the same.
+//
+// What bounds it: the vector ALUs that split and mask (three to four times the cycles of the products).  Per call, this
+// kernel against the fp32 instruction on the same storage: 32 heads x 64 channels, d_state 16, eight requests of 18 K
+// tokens in all, 107 -> 67 us; roll-forward of three sequences of 17 to 256 tokens, 128 heads x 64 channels, d_state 128,
+// 52 -> 37 us.
+constexpr int kUnit = 32;
+typedef __attribute__((ext_vector_type(8))) __bf16 split_bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 split_bf16x2;
+typedef __attribute__((ext_vector_type(2))) float split_f32x2;
+typedef __attribute__((ext_vector_type(2))) uint32_t split_u32x2;
+typedef __attribute__((ext_vector_type(4))) uint32_t split_u32x4;
+
+__device__ __forceinline__ f32x4 mfma_b16(uint4 a, uint4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, a), __builtin_bit_cast(split_bf16x8, b),
+                                                   c, 0, 0, 0);
+}
+__device__ __forceinline__ uint32_t split_pack(float lo, float hi)  // two floats rounded to bf16
+{
+    const split_f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, split_bf16x2));
+}
+// the upper 16 bits of two words, the lower 16 bits of two words
+__device__ __forceinline__ uint32_t upper2(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
+__device__ __forceinline__ uint32_t lower2(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x05040100u); }
+
+// Two fp32 values as three pairs of bf16 whose sums they are: cut off after 8 bits of the significand, twice.
+__device__ __forceinline__ void split3(float a, float b, uint32_t (&part)[3])
+{
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+        part[s] = upper2(ua, ub);
+        a -= __uint_as_float(ua & 0xffff0000u);
+        b -= __uint_as_float(ub & 0xffff0000u);
+    }
+}
+__device__ __forceinline__ void split3x8(const float (&v)[8], uint4 (&part)[3])
+{
+    uint32_t p[4][3];
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        split3(v[2 * d], v[2 * d + 1], p[d]);
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+        part[s] = make_uint4(p[0][s], p[1][s], p[2][s], p[3][s]);
+}
+
+// Loads go through buffer descriptors: a uniform base and size, one 32-bit offset per lane and a uniform offset, so that
+// no 64-bit address arithmetic runs on the vector ALUs.  Every access stays inside its descriptor.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t split_rsrc(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+// BYTES (2, 4, 8, or a multiple of 16) neighbouring bytes as words
+template <int BYTES>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t uniform_off, uint32_t *v)
+{
+    if (BYTES == 2) {
+        v[0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)lane_off, (int)uniform_off, 0);
+    } else if (BYTES == 4) {
+        v[0] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)lane_off, (int)uniform_off, 0);
+    } else if (BYTES == 8) {
+        const auto u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane_off, (int)uniform_off, 0);
+        v[0] = u[0], v[1] = u[1];
+    } else {
+#pragma unroll
+        for (int e = 0; e < BYTES / 16; ++e) {
+            const auto u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(lane_off + 16 * e), (int)uniform_off, 0);
+            v[4 * e] = u[0], v[4 * e + 1] = u[1], v[4 * e + 2] = u[2], v[4 * e + 3] = u[3];
+        }
+    }
+}
+
+// Four neighbouring elements of a cached state behind a descriptor (lane offset in elements), ST its storage type.
+template <int ST> __device__ __forceinline__ float4 split_state_load4(__amdgpu_buffer_rsrc_t r, uint32_t elem)
+{
+    uint32_t u[4];
+    if constexpr (ST == SSM_ST_F32) {
+        load_words<16>(r, 4 * elem, 0, u);
+        return make_float4(__uint_as_float(u[0]), __uint_as_float(u[1]), __uint_as_float(u[2]), __uint_as_float(u[3]));
+    }
+    load_words<8>(r, 2 * elem, 0, u);
+    if constexpr (ST == SSM_ST_F16) {
+        const st_f16x4 v = __builtin_bit_cast(st_f16x4, make_uint2(u[0], u[1]));
+        return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+    }
+    return make_float4(__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u), __uint_as_float(u[1] << 16),
+                       __uint_as_float(u[1] & 0xffff0000u));
+}
+template <int ST> __device__ __forceinline__ void split_state_store4(__amdgpu_buffer_rsrc_t r, uint32_t elem, float4 v)
+{
+    if constexpr (ST == SSM_ST_F32) {
+        const split_u32x4 u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+        __builtin_amdgcn_raw_buffer_store_b128(u, r, (int)(4 * elem), 0, 0);
+    } else if constexpr (ST == SSM_ST_F16) {
+        const st_f16x4 h = {(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(split_u32x2, h), r, (int)(2 * elem), 0, 0);
+    } else {
+        const split_u32x2 u = {split_pack(v.x, v.y), split_pack(v.z, v.w)};
+        __builtin_amdgcn_raw_buffer_store_b64(u, r, (int)(2 * elem), 0, 0);
+    }
+}
+
+struct SplitWave {        // private to one wave
+    double ell[kUnit];    // l_i log2(e)
+    float ei[kUnit];      // e^{l_i}
+    float wt[kUnit];      // e^{l_q - l_j} dt_j
+    float dt[kUnit];
+    int first_bad[64];
+};
+__device__ __forceinline__ const void *uniform_ptr(const void *p)
+{
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<const void *>(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u));
+}
+template <int T> struct StateType {
+    static constexpr int value = T;
+};
+template <int NB, int NC, int NW> struct SplitLds {
+    float4 S[NC][NB][64];  // [slice][four of a lane's 4 NB state elements][lane]
+    int done;
+    int pad[3];
+    SplitWave wv[NW];
+};
+
+// Waves per SIMD that the registers are budgeted for: workgroups of four waves share a compute unit in twos.
+template <int NB, int NC, int NW>
+__global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kernel(F32Args a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    SplitLds<NB, NC, NW> &L = *reinterpret_cast<SplitLds<NB, NC, NW> *>(lds_raw);
+    constexpr int N = 16 * NB, kRun = 4 * NB;          // d_state; state indices per lane
+    constexpr int kSteps = NB == 1 ? 1 : NB / 2;       // products over the state indices, 32 at a time
+    constexpr int kRowWords = kRun / 2;                // words of a lane's run of a row of B or C
+    constexpr int kBtWords = NB == 1 ? 1 : NB / 2, kXWords = NC == 4 ? 2 : 1;
+    const int H = a.H, P = a.P, G = a.G, st = a.state_dtype;
+    const int slice = blockIdx.x % a.slices;
+    const int h = (blockIdx.x / a.slices) % H;
+    const int seq = blockIdx.x / (a.slices * H);
+    const int g = h / (H / G);
+    const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool roll = a.roll;
+    const int per_tile = roll ? 1 : a.units_per_tile;
+    const SsmSeq sq = a.seqs[seq];
+    const void *from = uniform_ptr(a.init.of(seq));
+    if (sq.tile_end <= sq.tile_begin || (roll && !from))
+        return;  // nothing to scan; the whole workgroup leaves
+    int tok_begin = 0, n_tok = 0, n_units = (sq.tile_end - sq.tile_begin) * per_tile;
+    if (roll) {
+        const SsmTile last = a.tiles[sq.tile_end - 1];
+        tok_begin = a.tiles[sq.tile_begin].tok0;
+        n_tok = last.tok0 + last.len - tok_begin;
+        n_units = (n_tok + kUnit - 1) / kUnit;
+    }
+    const unsigned char *x = static_cast<const unsigned char *>(a.x) + ((size_t)h * P + 16 * NC * slice) * 2;
+    const unsigned char *Bg = static_cast<const unsigned char *>(a.B) + (size_t)g * N * 2;
+    const unsigned char *Cg = static_cast<const unsigned char *>(a.C) + (size_t)g * N * 2;
+    const bf16_t *dt = static_cast<const bf16_t *>(a.dt) + h;
+    unsigned char *y = a.y ? static_cast<unsigned char *>(a.y) + ((size_t)h * P + 16 * NC * slice) * 2 : nullptr;
+    const float Ah = a.A[h], Dh = a.D[h];
+    const uint32_t gn_b = (uint32_t)G * N * 2, hp_b = (uint32_t)H * P * 2;  // bytes per token row
+    // the workgroup's part of a cached state; the lane's: channel NC li + c, state indices 4 NB kq .. 4 NB kq + 4 NB - 1
+    const size_t part_elem = ((size_t)h * P + 16 * NC * slice) * N;
+    const int st_bytes = st == SSM_ST_F32 ? 4 : 2;
+    const uint32_t lane_elem = NC * li * N + kRun * kq;
+    auto state_part = [&](const void *base, size_t elem) {
+        return split_rsrc(static_cast<const unsigned char *>(base) + (elem + part_elem) * st_bytes,
+                          16u * NC * N * (uint32_t)st_bytes);
+    };
+
+    // operand of product s from a lane's run of a row; with d_state 16 the run fills four slots and `rest` the others
+    auto row_operand = [&](const uint32_t (&r)[kRowWords], int s, bool twice) {
+        if constexpr (NB == 1)
+            return make_uint4(r[0], r[1], twice ? r[0] : 0u, twice ? r[1] : 0u);
+        else
+            return make_uint4(r[4 * s], r[4 * s + 1], r[4 * s + 2], r[4 * s + 3]);
+    };
+
+    auto start_from = [&](auto type) {
+        const __amdgpu_buffer_rsrc_t part = state_part(from, 0);
+        for (int b = w; b < NC * NB; b += NW)
+            L.S[b / NB][b % NB][lane] = split_state_load4<decltype(type)::value>(part, lane_elem + b / NB * N + 4 * (b % NB));
+    };
+    if (!from) {
+        for (int b = w; b < NC * NB; b += NW)
+            L.S[b / NB][b % NB][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else if (st == SSM_ST_F32) {
+        start_from(StateType<SSM_ST_F32>());
+    } else if (st == SSM_ST_F16) {
+        start_from(StateType<SSM_ST_F16>());
+    } else {
+        start_from(StateType<SSM_ST_BF16>());
+    }
+    if (threadIdx.x == 0)
+        L.done = 0;
+    __syncthreads();  // the only one: the starting state and the counter are in place
+
+    SplitWave &W = L.wv[w];
+    for (int k = w; k < n_units; k += NW) {
+        int tok0, len, ckpt = -1;
+        if (roll) {
+            tok0 = tok_begin + kUnit * k;
+            len = n_tok - kUnit * k < kUnit ? n_tok - kUnit * k : kUnit;
+        } else {
+            const SsmTile t = a.tiles[sq.tile_begin + (per_tile == 2 ? k >> 1 : k)];
+            const int off = per_tile == 2 ? kUnit * (k & 1) : 0, left = t.len - off;
+            tok0 = t.tok0 + off;
+            len = left < kUnit ? left : kUnit;
+            ckpt = left <= kUnit ? t.ckpt_slot : -1;
+        }
+        tok0 = __builtin_amdgcn_readfirstlane(tok0);
+        len = __builtin_amdgcn_readfirstlane(len);
+        ckpt = __builtin_amdgcn_readfirstlane(ckpt);
+        if (len <= 0) {  // the second half of a tile that has none: the state passes through
+            f32_wait_counter(&L.done, k);
+            f32_publish_counter(&L.done, k + 1, lane);
+            continue;
+        }
+        // ---- the unit's operands as they come from device memory.  Rows past the end of a partial unit re-read its last
+        // row: their weights are zero, and an x there that is not finite is treated like the last token's own.
+        float dtl;
+        uint32_t Cr[2][kRowWords], Br[2][kRowWords], Bt[8][kBtWords], xr[8][kXWords];
+        {
+            const uint32_t rows = (uint32_t)(len - 1);
+            const __amdgpu_buffer_rsrc_t xs = split_rsrc(x + (size_t)tok0 * hp_b, rows * hp_b + 32 * NC);
+            const __amdgpu_buffer_rsrc_t bs = split_rsrc(Bg + (size_t)tok0 * gn_b, rows * gn_b + 2 * N);
+            const __amdgpu_buffer_rsrc_t cs = split_rsrc(Cg + (size_t)tok0 * gn_b, rows * gn_b + 2 * N);
+            const __amdgpu_buffer_rsrc_t ds = split_rsrc(dt + (size_t)tok0 * H, (rows * H + 1) * 2);
+            // row (own row of the lane) + up, at most the last one: a uniform part and a part per lane
+            auto up_at = [&](uint32_t up, uint32_t stride) { return up < rows ? up * stride : rows * stride; };
+            auto own_at = [&](uint32_t own, uint32_t up, uint32_t stride) {
+                const uint32_t most = rows * stride - up_at(up, stride);
+                return own < most ? own : most;
+            };
+            const int dt_tok = lane & (kUnit - 1);
+            const uint32_t dt_raw = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
+                ds, (int)own_at(dt_tok * 2u * H, 0, 2u * H), 0, 0);
+            dtl = dt_tok < len ? __uint_as_float(dt_raw << 16) : 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t up = 16 * (e >> 2) + (e & 3);
+                load_words<2 * NC>(xs, own_at(4 * kq * hp_b, up, hp_b) + 2 * NC * li, up_at(up, hp_b), xr[e]);
+                load_words<2 * NB>(bs, own_at(4 * kq * gn_b, up, gn_b) + 2 * NB * li, up_at(up, gn_b), Bt[e]);
+            }
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                const uint32_t own = own_at(li * gn_b, 16 * hf, gn_b) + 2 * kRun * kq;
+                load_words<2 * kRun>(bs, own, up_at(16 * hf, gn_b), Br[hf]);
+                load_words<2 * kRun>(cs, own, up_at(16 * hf, gn_b), Cr[hf]);
+            }
+        }
+        // ---- decay factors.  Lanes 32..63 repeat lanes 0..31.
+        float dl;
+        {
+            const double half = row_inclusive_sum((double)dtl * (double)Ah);  // tokens past the end add nothing
+            const uint64_t u = __builtin_bit_cast(uint64_t, half);
+            const uint64_t u15 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(u >> 32), 15) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 15);
+            const double ell = 1.4426950408889634074 * (half + ((lane & 16) ? __builtin_bit_cast(double, u15) : 0.0));
+            const uint64_t v = __builtin_bit_cast(uint64_t, ell);
+            const uint64_t v31 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 31) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 31);
+            const double last = __builtin_bit_cast(double, v31);
+            dl = __builtin_amdgcn_exp2f((float)last);
+            if (lane < kUnit) {
+                W.ell[lane] = ell;
+                W.dt[lane] = dtl;
+                W.ei[lane] = __builtin_amdgcn_exp2f((float)ell);
+                W.wt[lane] = __builtin_amdgcn_exp2f((float)(last - ell)) * dtl;
+            }
+        }
+        lds_wait();
+        // channel c of the lane's token e, and the operand of the products with x
+        auto xval = [&](int c, int e) {
+            const uint32_t u = xr[e][c >> 1];
+            return __uint_as_float((c & 1) ? u & 0xffff0000u : u << 16);
+        };
+        auto xpair = [&](int c, int d) {
+            return (c & 1) ? upper2(xr[2 * d][c >> 1], xr[2 * d + 1][c >> 1])
+                           : lower2(xr[2 * d][c >> 1], xr[2 * d + 1][c >> 1]);
+        };
+
+        __builtin_amdgcn_sched_barrier(0);
+        // ---- the unit's own state
+        f32x4 Sl[NC * NB];  // [slice][block]
+#pragma unroll
+        for (int c = 0; c < NC * NB; ++c)
+            Sl[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        {
+            uint4 bo[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                uint32_t b[4];
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    b[d] = (nb & 1) ? upper2(Bt[2 * d][nb >> 1], Bt[2 * d + 1][nb >> 1])
+                                    : lower2(Bt[2 * d][nb >> 1], Bt[2 * d + 1][nb >> 1]);
+                bo[nb] = make_uint4(b[0], b[1], b[2], b[3]);
+            }
+            const float4 w0 = *reinterpret_cast<const float4 *>(&W.wt[4 * kq]);
+            const float4 w1 = *reinterpret_cast<const float4 *>(&W.wt[16 + 4 * kq]);
+            const float wt[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                __builtin_amdgcn_sched_barrier(0);
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    v[e] = wt[e] * xval(c, e);
+                uint4 wx[3];
+                split3x8(v, wx);
+#pragma unroll
+                for (int s = 2; s >= 0; --s)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        Sl[c * NB + nb] = mfma_b16(bo[nb], wx[s], Sl[c * NB + nb]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // ---- masked, decayed scores as split operands: queries 0..15 have keys 0..15 (two parts share a product),
+        // queries 16..31 all of them
+        uint4 g_hm, g_l, g_hi[3];
+        {
+            f32x4 sc[3];  // queries / keys: first / first, second / first, second / second half
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                sc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s)
+                    sc[b] = mfma_b16(row_operand(Br[b == 2], s, false), row_operand(Cr[b > 0], s, false), sc[b]);
+            }
+            const double e0 = W.ell[li], e1 = W.ell[16 + li];
+            float v0[4], v1[8];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (r == 2)
+                    __builtin_amdgcn_sched_barrier(0);
+                const double k0 = W.ell[4 * kq + r], k1 = W.ell[16 + 4 * kq + r];
+                const float d0 = W.dt[4 * kq + r], d1 = W.dt[16 + 4 * kq + r];
+                const bool in = 4 * kq + r <= li;
+                v0[r] = in ? sc[0][r] * (__builtin_amdgcn_exp2f((float)(e0 - k0)) * d0) : 0.f;
+                v1[r] = sc[1][r] * (__builtin_amdgcn_exp2f((float)(e1 - k0)) * d0);
+                v1[4 + r] = in ? sc[2][r] * (__builtin_amdgcn_exp2f((float)(e1 - k1)) * d1) : 0.f;
+            }
+            uint32_t p[2][3];
+            split3(v0[0], v0[1], p[0]);
+            split3(v0[2], v0[3], p[1]);
+            g_hm = make_uint4(p[0][0], p[1][0], p[0][1], p[1][1]);
+            g_l = make_uint4(p[0][2], p[1][2], 0u, 0u);
+            split3x8(v1, g_hi);
+        }
+#pragma unroll
+        for (int c = 0; c < NC * NB; ++c)  // done before the wait starts
+            asm volatile("" : "+v"(Sl[c]));
+        __builtin_amdgcn_sched_barrier(0);
+        f32_wait_counter(&L.done, k);
+        // ---- read the state, multiply-add, write it back, publish
+        float4 sp[NC][NB];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int f4 = 0; f4 < NB; ++f4)
+                sp[c][f4] = L.S[c][f4][lane];
+        // element f = NB rr + nb of a lane's run is element rr of block nb
+        auto next = [&](int c, int f) {
+            const float4 &q = sp[c][f / 4];
+            const float s = f % 4 == 0 ? q.x : f % 4 == 1 ? q.y : f % 4 == 2 ? q.z : q.w;
+            return __builtin_fmaf(dl, s, Sl[c * NB + f % NB][f / NB]);
+        };
+        auto next4 = [&](int c, int f4) {
+            return make_float4(next(c, 4 * f4), next(c, 4 * f4 + 1), next(c, 4 * f4 + 2), next(c, 4 * f4 + 3));
+        };
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int f4 = 0; f4 < NB; ++f4)
+                L.S[c][f4][lane] = next4(c, f4);
+        __builtin_amdgcn_sched_barrier(0);
+        f32_publish_counter(&L.done, k + 1, lane);
+        if (ckpt >= 0 || (roll && k == n_units - 1)) {
+            const __amdgpu_buffer_rsrc_t part =
+                state_part(roll ? from : a.state_out, roll ? 0 : (size_t)ckpt * H * P * N);
+            auto keep = [&](auto type) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int f4 = 0; f4 < NB; ++f4)
+                        split_state_store4<decltype(type)::value>(part, lane_elem + c * N + 4 * f4, next4(c, f4));
+            };
+            if (st == SSM_ST_F32)
+                keep(StateType<SSM_ST_F32>());
+            else if (st == SSM_ST_F16)
+                keep(StateType<SSM_ST_F16>());
+            else
+                keep(StateType<SSM_ST_BF16>());
+        }
+        if (!y)
+            continue;
+        // ---- outputs, one channel of the lane after the other: element r of Y[ih] is token 16 ih + 4 kq + r
+        auto intra = [&](const uint4 &xo, f32x4 &y0, f32x4 &y1) {
+            const uint4 x2 = make_uint4(xo.x, xo.y, xo.x, xo.y);
+            y0 = mfma_b16(g_l, x2, y0);
+            y1 = mfma_b16(g_hi[2], xo, y1);
+            y1 = mfma_b16(g_hi[1], xo, y1);
+            y0 = mfma_b16(g_hm, x2, y0);
+            y1 = mfma_b16(g_hi[0], xo, y1);
+        };
+        const float4 ei0 = *reinterpret_cast<const float4 *>(&W.ei[4 * kq]);
+        const float4 ei1 = *reinterpret_cast<const float4 *>(&W.ei[16 + 4 * kq]);
+        const f32x4 ei[2] = {{ei0.x, ei0.y, ei0.z, ei0.w}, {ei1.x, ei1.y, ei1.z, ei1.w}};
+        float Yf[2][8];                     // the present channel and the one before it
+        uint32_t out[(NC + 1) / 2][8];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4 Y[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            if constexpr (NB == 1) {
+                uint32_t p[2][3];
+                split3(sp[c][0].x, sp[c][0].y, p[0]);
+                split3(sp[c][0].z, sp[c][0].w, p[1]);
+                const uint4 s_hm = make_uint4(p[0][0], p[1][0], p[0][1], p[1][1]), s_l = make_uint4(p[0][2], p[1][2], 0u, 0u);
+#pragma unroll
+                for (int ih = 0; ih < 2; ++ih) {
+                    const uint4 co = row_operand(Cr[ih], 0, true);
+                    Y[ih] = mfma_b16(co, s_l, Y[ih]);
+                    Y[ih] = mfma_b16(co, s_hm, Y[ih]);
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) {
+                    const float4 s0 = sp[c][2 * s], s1 = sp[c][2 * s + 1];
+                    const float v[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+                    uint4 so[3];
+                    split3x8(v, so);
+#pragma unroll
+                    for (int part = 2; part >= 0; --part)
+#pragma unroll
+                        for (int ih = 0; ih < 2; ++ih)
+                            Y[ih] = mfma_b16(row_operand(Cr[ih], s, false), so[part], Y[ih]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                Y[e >> 2][e & 3] *= ei[e >> 2][e & 3];
+            const f32x4 in0 = Y[0], in1 = Y[1];
+            intra(make_uint4(xpair(c, 0), xpair(c, 1), xpair(c, 2), xpair(c, 3)), Y[0], Y[1]);
+            // a token whose x is not finite has reached every query of its channel, the earlier ones as 0 * inf
+            const bool bad = !(__builtin_fabsf(Y[0][0]) < __builtin_inff()) || !(__builtin_fabsf(Y[1][0]) < __builtin_inff());
+            if (__any(bad)) {
+                int first = kUnit;  // the channel's first such token
+                uint32_t u[8];
+#pragma unroll
+                for (int e = 7; e >= 0; --e) {
+                    const uint32_t raw = __float_as_uint(xval(c, e));
+                    const bool nf = (raw & 0x7f800000u) == 0x7f800000u;
+                    u[e] = nf ? 0u : raw;
+                    first = nf ? 16 * (e >> 2) + (e & 3) : first;
+                }
+                first += 4 * kq;
+                W.first_bad[lane] = first;
+                lds_wait();
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    first = W.first_bad[16 * q + li] < first ? W.first_bad[16 * q + li] : first;
+                lds_wait();
+                first -= 4 * kq;
+                f32x4 c0 = in0, c1 = in1;
+                intra(make_uint4(upper2(u[0], u[1]), upper2(u[2], u[3]), upper2(u[4], u[5]), upper2(u[6], u[7])), c0, c1);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    Y[0][r] = r < first ? c0[r] : Y[0][r];
+                    Y[1][r] = 16 + r < first ? c1[r] : Y[1][r];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                Yf[c & 1][e] = __builtin_fmaf(Dh, xval(c, e), Y[e >> 2][e & 3]);
+                if ((c & 1) || NC == 1)
+                    out[c / 2][e] = split_pack(Yf[0][e], Yf[NC == 1 ? 0 : 1][e]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const __amdgpu_buffer_rsrc_t ys = split_rsrc(y + (size_t)tok0 * hp_b, (uint32_t)(len - 1) * hp_b + 32 * NC);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int up = 16 * (e >> 2) + (e & 3);
+            if (4 * kq >= len - up)
+                continue;
+            const int own = (int)(4 * kq * hp_b + 2 * NC * li), row = (int)(up * hp_b);
+            if constexpr (NC == 1) {
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)out[0][e], ys, own, row, 0);
+            } else if constexpr (NC == 2) {
+                __builtin_amdgcn_raw_buffer_store_b32(out[0][e], ys, own, row, 0);
+            } else {
+                const split_u32x2 both = {out[0][e], out[1][e]};
+                __builtin_amdgcn_raw_buffer_store_b64(both, ys, own, row, 0);
+            }
+        }
+    }
+}
+
+template <int NB, int NC>
 hipError_t launch_f32(const F32Args &a, int batch, hipStream_t stream)
 {
     constexpr int NW = NB == 1 ? 16 : 8;
-    hipLaunchKernelGGL((ssm_scan_f32_kernel<IO, NB, NC, NW>), dim3((unsigned)batch * (unsigned)a.H * (unsigned)a.slices),
+    hipLaunchKernelGGL((ssm_scan_f32_kernel<NB, NC, NW>), dim3((unsigned)batch * (unsigned)a.H * (unsigned)a.slices),
                        dim3(64 * NW), sizeof(F32Lds<NB, NC, NW>), stream, a);
     return hipGetLastError();
 }
 
-template <typename IO, int NB>
-hipError_t launch_f32_nc(F32Args &a, int nc, int batch, hipStream_t stream)
+template <int NB, int NC, int NW>
+hipError_t launch_split_nw(const F32Args &a, int batch, hipStream_t stream)
 {
-    a.slices = a.P / (16 * nc);
-    if (nc == 4)
-        return launch_f32<IO, NB, NB <= 2 ? 4 : 2>(a, batch, stream);  // 4 slices only with small states
-    if (nc == 2)
-        return launch_f32<IO, NB, 2>(a, batch, stream);
-    return launch_f32<IO, NB, 1>(a, batch, stream);
+    hipLaunchKernelGGL((ssm_scan_split_kernel<NB, NC, NW>), dim3((unsigned)batch * (unsigned)a.H * (unsigned)a.slices),
+                       dim3(64 * NW), sizeof(SplitLds<NB, NC, NW>), stream, a);
+    return hipGetLastError();
 }
 
-template <typename IO>
-hipError_t launch_f32_nb(F32Args &a, int nb, int nc, int batch, hipStream_t stream)
+// Waves per workgroup: 8, or with larger states 4 where a sequence has no more units or where the launch has enough
+// workgroups for two on each of the 256 compute units (the roll-forward above with 8 waves: 46 us; d_state 16 with 16
+// waves, whose registers then spill: 94 us).
+template <int NB, int NC>
+hipError_t launch_split(const F32Args &a, int batch, int units, hipStream_t stream)
 {
-    switch (nb) {
-    case 1: return launch_f32_nc<IO, 1>(a, nc, batch, stream);
-    case 2: return launch_f32_nc<IO, 2>(a, nc, batch, stream);
-    case 4: return launch_f32_nc<IO, 4>(a, nc, batch, stream);
-    default: return launch_f32_nc<IO, 8>(a, nc, batch, stream);
-    }
+    if (NB == 1 || (units > 4 && (long long)batch * a.H * a.slices <= 256))
+        return launch_split_nw<NB, NC, 8>(a, batch, stream);
+    if constexpr (NB > 1)
+        return launch_split_nw<NB, NC, 4>(a, batch, stream);
+    return hipErrorInvalidValue;
+}
+
+template <int NB>
+hipError_t launch_f32_nc(F32Args &a, bool split, int nc, int batch, int units, hipStream_t stream)
+{
+    a.slices = a.P / (16 * nc);
+    constexpr int kMost = NB <= 2 ? 4 : 2;  // four slices only with small states
+    if (nc == 4)
+        return split ? launch_split<NB, NB == 8 ? 1 : kMost>(a, batch, units, stream) : launch_f32<NB, kMost>(a, batch, stream);
+    constexpr int kMostSplit = NB == 8 ? 1 : kMost;
+    if (nc == 2)
+        return split ? launch_split<NB, kMostSplit < 2 ? 1 : 2>(a, batch, units, stream)
+                     : launch_f32<NB, 2>(a, batch, stream);
+    return split ? launch_split<NB, 1>(a, batch, units, stream) : launch_f32<NB, 1>(a, batch, stream);
 }
 
 // ================================================================ vector ALUs, any shape
@@ -563,25 +1112,39 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     a.seqs = args.seqs;
     a.H = args.H, a.P = args.P, a.G = args.G;
     a.state_dtype = args.state_dtype;
-    // Slices of 16 channels per workgroup: more of them share the scores (4 nb of a tile's products), fewer leave more
-    // workgroups.  Products per tile times rounds of 256 workgroups, the smaller the better.
+    // Slices of 16 channels per workgroup: more of them share the scores (4 nb of a tile's products in fp32), fewer leave
+    // more workgroups.  Products per tile times rounds of 256 workgroups, the smaller the better.
+    const bool split = plan->shape.io_dtype == SSM_DT_BF16;
     const int nb = args.N / 16, all = args.P / 16;
     long long streams = 0;
+    int longest = 0;
     for (const SsmSeq &q : plan->seqs)
-        streams += q.tile_end > q.tile_begin;
+        if (q.tile_end > q.tile_begin) {
+            const SsmTile &first = plan->tiles[q.tile_begin], &last = plan->tiles[q.tile_end - 1];
+            longest = last.tok0 + last.len - first.tok0 > longest ? last.tok0 + last.len - first.tok0 : longest;
+            ++streams;
+        }
     streams *= args.H;
+    a.units_per_tile = (plan->tile_tokens + kUnit - 1) / kUnit;
     int nc = 1;
     long long best = 0;
-    for (int c = 1; c <= (nb <= 2 ? 4 : 2); c *= 2) {
+    // What the registers hold: with d_state 128 two split slices spill (the roll-forward 47 us instead of 37).
+    const int most = nb <= 2 ? 4 : split && nb == 8 ? 1 : 2;
+    for (int c = 1; c <= most; c *= 2) {
         if (all % c != 0)
             break;
-        const long long rounds = (streams * (all / c) + 255) / 256, cost = rounds * (c * (8 * nb + 4) + 4 * nb);
+        const long long rounds = (streams * (all / c) + 255) / 256;
+        const long long cost = rounds * (split ? c * (6 * nb + 8) + 2 * nb + 8 : c * (8 * nb + 4) + 4 * nb);
         if (c == 1 || cost <= best)
             nc = c, best = cost;
     }
-    if (plan->shape.io_dtype == SSM_DT_F32)
-        return launch_f32_nb<float>(a, nb, nc, plan->batch, stream);
-    return launch_f32_nb<bf16_t>(a, nb, nc, plan->batch, stream);
+    const int units = (longest + kUnit - 1) / kUnit;
+    switch (nb) {
+    case 1: return launch_f32_nc<1>(a, split, nc, plan->batch, units, stream);
+    case 2: return launch_f32_nc<2>(a, split, nc, plan->batch, units, stream);
+    case 4: return launch_f32_nc<4>(a, split, nc, plan->batch, units, stream);
+    default: return launch_f32_nc<8>(a, split, nc, plan->batch, units, stream);
+    }
 }
 
 size_t ssm_valu_lds_bytes(int P, int N);

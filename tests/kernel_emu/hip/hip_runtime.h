@@ -74,6 +74,7 @@ struct BufRsrc {
     unsigned char *base;
     uint32_t bytes;
 };
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 void buffer_range_fault(uint32_t off, uint32_t n, uint32_t bytes, int line);
 static inline BufRsrc make_buffer_rsrc(void *base, int stride, int bytes, int flags)
@@ -122,10 +123,35 @@ template <typename F> void launch(dim3 grid, dim3 block, size_t lds_bytes, F &&b
 #define __builtin_amdgcn_readlane(v, l) emu::readlane((v), (l), __LINE__)
 #define __builtin_amdgcn_readfirstlane(v) emu::readfirstlane((v), __LINE__)
 #define __shfl(v, l, w) __uint_as_float((uint32_t)emu::shfl((int)__float_as_uint(v), (l), __LINE__))
+namespace emu {
+inline bool any_lane(bool v, int line)
+{
+    bool any = false;
+    for (int l = 0; l < 64; ++l)
+        any = shfl(v ? 1 : 0, l, line) != 0 || any;
+    return any;
+}
+}  // namespace emu
+// v_perm_b32 with selectors 0..7: bytes of {hi, lo}
+static inline uint32_t emu_perm(uint32_t hi, uint32_t lo, uint32_t sel)
+{
+    const uint64_t both = ((uint64_t)hi << 32) | lo;
+    uint32_t r = 0;
+    for (int b = 0; b < 4; ++b)
+        r |= (uint32_t)((both >> (8 * ((sel >> (8 * b)) & 7))) & 0xff) << (8 * b);
+    return r;
+}
+#define __builtin_amdgcn_perm(hi, lo, sel) emu_perm((hi), (lo), (sel))
+#define __any(v) emu::any_lane((v), __LINE__)
 #define __amdgpu_buffer_rsrc_t emu::BufRsrc
 #define __builtin_amdgcn_make_buffer_rsrc(p, stride, n, flags) emu::make_buffer_rsrc((p), (stride), (n), (flags))
 #define __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, aux) emu::buffer_load<emu::u32x4>((r), (voff), (soff), __LINE__)
 #define __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, aux) emu::buffer_load<unsigned short>((r), (voff), (soff), __LINE__)
+#define __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, aux) emu::buffer_load<uint32_t>((r), (voff), (soff), __LINE__)
+#define __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, aux) emu::buffer_load<emu::u32x2>((r), (voff), (soff), __LINE__)
+#define __builtin_amdgcn_raw_buffer_store_b16(v, r, voff, soff, aux) emu::buffer_store((uint16_t)(v), (r), (voff), (soff), __LINE__)
+#define __builtin_amdgcn_raw_buffer_store_b32(v, r, voff, soff, aux) emu::buffer_store((uint32_t)(v), (r), (voff), (soff), __LINE__)
+#define __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, aux) emu::buffer_store((emu::u32x2)(v), (r), (voff), (soff), __LINE__)
 #define __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, aux) emu::buffer_store((v), (r), (voff), (soff), __LINE__)
 #define __builtin_amdgcn_exp2f(x) exp2f(x)
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
