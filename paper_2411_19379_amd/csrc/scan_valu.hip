@@ -177,6 +177,7 @@ struct F32Wave {          // private to one wave
     float ei[16];         // e^{l_i}
     float wt[16];         // e^{l_q - l_j} dt_j
     float dt[16];
+    int first_bad[64];
 };
 template <int NB, int NC, int NW> struct F32Lds {
     float4 S[NC][NB][64];  // [slice][four of a lane's 4 NB state elements][lane]
@@ -359,9 +360,31 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 Y0[r] = ei[r] * (Y0[r] + Y1[r]);
+            const f32x4 before = Y0;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 Y0 = mfma_f32(gm[r], xv[c][r], Y0);
+            // a token whose x is not finite has reached every query of its channel, the earlier ones as 0 * inf: these
+            // take the products without such tokens
+            if (__any(!(__builtin_fabsf(Y0[0]) < __builtin_inff()))) {
+                int first = 16;
+                f32x4 Y2 = before;
+#pragma unroll
+                for (int r = 3; r >= 0; --r)
+                    first = !(__builtin_fabsf(xv[c][r]) < __builtin_inff()) ? 4 * kq + r : first;
+                W.first_bad[lane] = first;
+                lds_wait();
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    first = W.first_bad[16 * q + li] < first ? W.first_bad[16 * q + li] : first;
+                lds_wait();
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    Y2 = mfma_f32(gm[r], __builtin_fabsf(xv[c][r]) < __builtin_inff() ? xv[c][r] : 0.f, Y2);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    Y0[r] = 4 * kq + r < first ? Y2[r] : Y0[r];
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (4 * kq + r < len)

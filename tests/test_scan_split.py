@@ -82,7 +82,7 @@ def _check_reach(y, y0, st, st0, ckpts, tok, h, p):
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
-@pytest.mark.parametrize("io", ["bf16"])
+@pytest.mark.parametrize("io", ["bf16", "f32"])
 @pytest.mark.parametrize("tok", [0, 13, 21, 40])
 def test_emulated_value_that_is_not_finite(emu_binary, tmp_path, tok, io, value):  # noqa: F811
     dims, lens = ((1, 32, 16, 1, 64), [41])
@@ -149,7 +149,7 @@ def test_gpu_roll_forward(H, lens, state_dtype, tdt, tol):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("io", ["bf16"])
+@pytest.mark.parametrize("io", ["bf16", "f32"])
 @pytest.mark.parametrize("tok", [0, 18, 63, 69])
 def test_gpu_value_that_is_not_finite(tok, io):
     print(f"x not finite at token {tok}, {io}", flush=True)
