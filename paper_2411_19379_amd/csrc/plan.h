@@ -149,5 +149,5 @@ constexpr int kMfmaWorkgroupsPerRound = 256;
 constexpr int kMfmaMinStretchTiles = 64;
 constexpr int kMfmaMinCutTiles = 160;
 
-// The kernel in front of the scan works per (tile, group); below this many pairs each pair gets four workgroups.
+// The kernel in front of the scan works per (tile, group); below this many pairs each pair gets eight workgroups.
 constexpr int kMfmaPrepSplitBelow = 256;

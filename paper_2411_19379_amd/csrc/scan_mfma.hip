@@ -271,9 +271,11 @@ __global__ __launch_bounds__(kPrepThreads) void ssm_prep_kernel(
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     PrepLds &L = *reinterpret_cast<PrepLds *>(lds_raw);
-    // parts = 1: one workgroup per (tile, group), its wave w writes quarter w of the operand images.  parts = 4 (small
-    // grids, which would leave most of the GPU idle): four workgroups per (tile, group), workgroup `part` writes
-    // quarter `part`, a sixteenth per wave, and transposes a quarter of the heads' dt.
+    // parts = 1: one workgroup per (tile, group), its wave w writes quarter w of the operand images.  parts = 8 (small
+    // grids, which would leave most of the GPU idle): eight workgroups per (tile, group); workgroup `part` < 4 writes
+    // quarter `part` of the images, a sixteenth per wave, workgroup 4 + k transposes the dt of the k-th quarter of the
+    // heads.  Such a launch takes as long as its slowest workgroup, so the two jobs run side by side instead of one after
+    // the other (2048 tokens, 80 heads in one group: 7.6 -> 5.6 us; three tiles, 8 groups of 16 heads: 4.6 -> 3.6 us).
     const int tg = blockIdx.x / parts, part = blockIdx.x % parts;
     const int tile = tg / G, g = tg % G;
     if (tile >= n_tiles)
@@ -282,12 +284,13 @@ __global__ __launch_bounds__(kPrepThreads) void ssm_prep_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hg = H / G;  // heads of this group: g * hg .. g * hg + hg - 1
-    const int quarter = parts == 1 ? w : part;                 // which quarter of the images this wave works on
-    const int sub0 = parts == 1 ? 0 : w, sub1 = parts == 1 ? 4 : w + 1;  // and which sixteenths of it
-    const int h_lo = hg * part / parts, h_hi = hg * (part + 1) / parts;   // heads whose dt this workgroup transposes
+    const bool whole = parts == 1, images = whole || part < 4, dt_rows = whole || part >= 4;
+    const int quarter = whole ? w : part;                    // which quarter of the images this wave works on
+    const int sub0 = whole ? 0 : w, sub1 = whole ? 4 : w + 1;  // and which sixteenths of it
+    const int h_lo = whole ? 0 : hg * (part - 4) / 4, h_hi = whole ? hg : hg * (part - 3) / 4;  // heads whose dt
 
     // B and C rows, 16 lanes per 256-byte row; rows past the end of a partial tile are zero
-    {
+    if (images) {
         const int row_l = tid >> 4, col = 8 * (tid & 15);
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
@@ -302,25 +305,29 @@ __global__ __launch_bounds__(kPrepThreads) void ssm_prep_kernel(
             *reinterpret_cast<uint4 *>(&L.Cs[row][col]) = bf16x8_to_f16x8(vc);
         }
     }
-    // dt of the tile, transposed to head-major rows of 64 tokens, kDtHeads heads at a time.  The barrier after the
-    // first pass's loads also publishes the B and C tiles.
-    for (int h0 = h_lo; h0 < h_hi || h0 == h_lo; h0 += kDtHeads) {  // at least one pass: its barrier is needed
-        const int nh = h_hi - h0 < kDtHeads ? (h_hi - h0 > 0 ? h_hi - h0 : 0) : kDtHeads;
-        if (h0 > h_lo)
-            __syncthreads();  // the previous pass has been written out
-        for (int idx = tid; idx < kQ * nh; idx += kPrepThreads) {
-            const int tok = idx / nh, hh = idx % nh;
-            bf16_t v = 0;
-            if (tok < t.len)
-                v = dt[((size_t)t.tok0 + tok) * H + g * hg + h0 + hh];
-            L.dts[hh][tok] = v;
+    // dt of the tile, transposed to head-major rows of 64 tokens, kDtHeads heads at a time: threads in rows of a power of
+    // two of at least as many as there are heads, a row per token
+    if (dt_rows)
+        for (int h0 = h_lo; h0 < h_hi; h0 += kDtHeads) {
+            const int nh = h_hi - h0 < kDtHeads ? h_hi - h0 : kDtHeads;
+            const int sh = nh > 1 ? 32 - __builtin_clz(nh - 1) : 0;
+            const int hh = tid & ((1 << sh) - 1), rows = kPrepThreads >> sh;
+            if (h0 > h_lo)
+                __syncthreads();  // the previous pass has been written out
+            if (hh < nh)
+                for (int tok = tid >> sh; tok < kQ; tok += rows) {
+                    bf16_t v = 0;
+                    if (tok < t.len)
+                        v = dt[((size_t)t.tok0 + tok) * H + g * hg + h0 + hh];
+                    L.dts[hh][tok] = v;
+                }
+            __syncthreads();
+            for (int idx = tid; idx < kQ * nh; idx += kPrepThreads)
+                dt_t[((size_t)tile * H + g * hg + h0 + idx / kQ) * kQ + idx % kQ] = L.dts[idx / kQ][idx % kQ];
         }
-        __syncthreads();
-        for (int idx = tid; idx < kQ * nh; idx += kPrepThreads) {
-            const int hh = idx / kQ, tok = idx % kQ;
-            dt_t[((size_t)tile * H + g * hg + h0 + hh) * kQ + tok] = L.dts[hh][tok];
-        }
-    }
+    if (!images)
+        return;
+    __syncthreads();  // the B and C tiles are in place
 
     uint4 *out = frags + (size_t)tg * (kCfWords + kBfWords + kCbWords);
     const int i = lane & 31, q = lane >> 5;
@@ -343,7 +350,7 @@ __global__ __launch_bounds__(kPrepThreads) void ssm_prep_kernel(
     }
     // raw score blocks Gm^T[j, i] = B_j . C_i: block 0 keys and queries 0..31, block 1 keys and queries 32..63,
     // block 2 keys 0..31 and queries 32..63; kept as the 16 accumulator elements of every lane, in fp16
-    if (quarter < 3 && (parts == 1 || w == 0)) {
+    if (quarter < 3 && (whole || w == 0)) {
         const _Float16 *pb = &L.Bs[(quarter == 1 ? 32 : 0) + i][8 * q];
         const _Float16 *pc = &L.Cs[(quarter == 0 ? 0 : 32) + i][8 * q];
         f32x16 acc = zero16();
@@ -1099,8 +1106,8 @@ hipError_t launch_scan_mfma(const ssm_plan *plan, const ScanArgs &args, void *wo
     bf16_t *dt_t = reinterpret_cast<bf16_t *>(base + ws.dt_rows);
     float *tile_decay = plan->n_carry > 0 ? reinterpret_cast<float *>(base + ws.tile_decay) : nullptr;
     float *carry = plan->n_carry > 0 ? reinterpret_cast<float *>(base + ws.carry) : nullptr;
-    // few (tile, group) pairs: four workgroups each, so that the preparation does not run on a corner of the GPU
-    const int parts = (long long)n_tiles * args.G < kMfmaPrepSplitBelow ? 4 : 1;
+    // few (tile, group) pairs: eight workgroups each, so that the preparation does not run on a corner of the GPU
+    const int parts = (long long)n_tiles * args.G < kMfmaPrepSplitBelow ? 8 : 1;
     hipLaunchKernelGGL(ssm_prep_kernel, dim3((unsigned)n_tiles * (unsigned)args.G * (unsigned)parts), dim3(kPrepThreads),
                        sizeof(PrepLds), stream, static_cast<const bf16_t *>(args.B), static_cast<const bf16_t *>(args.C),
                        static_cast<const bf16_t *>(args.dt), args.tiles, frags, dt_t, args.H, args.G, n_tiles, parts);
