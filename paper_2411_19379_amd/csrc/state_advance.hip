@@ -21,6 +21,13 @@ constexpr int kAdvMaxRows = 8;  // state rows per thread
 // A batch with a longer sequence is rolled forward by the matrix-core kernels of scan_valu.hip (fp32 as here): the token
 // loop is one chain of dependent loads, 1.8 us a token.  Three sequences of 17 to 256 tokens at 128 heads: 466 -> 37 us.
 constexpr int kAdvMaxTokens = 4;
+// States of more than this per call pass by the caches (non-temporal loads and stores): in a serving program every layer's
+// states come by between two steps, and two layers of this size do not fit the 256 MiB memory-side cache, so what a call
+// leaves there is gone before it is read again and only displaces.  64 sequences x 128 heads x 64 x 128 in fp32 (256 MiB),
+// other states in every call: 106 -> 93 us (5.0 -> 5.8 TB/s); 128 of them 212 -> 188 us.  Smaller calls gain as much on
+// cold states (64 MiB 33 -> 27 us) but lose on states that are still cached (160 MiB in fp16 69 -> 92 us), and below the
+// limit a model of few layers may find them there.
+constexpr long long kAdvStreamBytes = 128ll << 20;
 constexpr float kAdvLog2e = 1.4426950408889634f;
 
 #define ADV_DPP(v, ctrl, row_mask)                                                                            \
@@ -65,33 +72,63 @@ template <> struct Vec4<bf16_t> {
 // Appendix A.1: 2 bytes per state element), which halves the bytes this kernel moves.  Arithmetic stays fp32; a
 // reduced-precision state is rounded once, to nearest even, when it is written back.
 enum { ADV_STATE_F32 = SSM_ST_F32, ADV_STATE_F16 = SSM_ST_F16, ADV_STATE_BF16 = SSM_ST_BF16 };
+// NT: loads and stores that keep nothing in the caches (see kAdvStreamBytes).
+typedef float adv_f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t adv_u32x2 __attribute__((ext_vector_type(2)));
+template <bool NT, typename V> __device__ __forceinline__ V adv_load(const void *p)
+{
+    if constexpr (NT)
+        return __builtin_nontemporal_load(static_cast<const V *>(p));
+    return *static_cast<const V *>(p);
+}
+template <bool NT, typename V> __device__ __forceinline__ void adv_store(void *p, V v)
+{
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, static_cast<V *>(p));
+    else
+        *static_cast<V *>(p) = v;
+}
 template <int ST> struct StateVec;
 template <> struct StateVec<ADV_STATE_F32> {
     typedef float elem;
-    static __device__ __forceinline__ float4 load(const elem *p) { return *reinterpret_cast<const float4 *>(p); }
-    static __device__ __forceinline__ void store(elem *p, float4 v) { *reinterpret_cast<float4 *>(p) = v; }
+    template <bool NT> static __device__ __forceinline__ float4 load(const elem *p)
+    {
+        const adv_f32x4 v = adv_load<NT, adv_f32x4>(p);
+        return make_float4(v[0], v[1], v[2], v[3]);
+    }
+    template <bool NT> static __device__ __forceinline__ void store(elem *p, float4 v)
+    {
+        const adv_f32x4 u = {v.x, v.y, v.z, v.w};
+        adv_store<NT>(p, u);
+    }
 };
 template <> struct StateVec<ADV_STATE_F16> {
     typedef _Float16 elem;
     typedef __attribute__((ext_vector_type(4))) _Float16 h4;
-    static __device__ __forceinline__ float4 load(const elem *p)
+    template <bool NT> static __device__ __forceinline__ float4 load(const elem *p)
     {
-        const h4 h = *reinterpret_cast<const h4 *>(p);
+        const h4 h = __builtin_bit_cast(h4, adv_load<NT, adv_u32x2>(p));
         return make_float4((float)h[0], (float)h[1], (float)h[2], (float)h[3]);
     }
-    static __device__ __forceinline__ void store(elem *p, float4 v)
+    template <bool NT> static __device__ __forceinline__ void store(elem *p, float4 v)
     {
         const h4 h = {(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
-        *reinterpret_cast<h4 *>(p) = h;
+        adv_store<NT>(p, __builtin_bit_cast(adv_u32x2, h));
     }
 };
 template <> struct StateVec<ADV_STATE_BF16> {
     typedef bf16_t elem;
-    static __device__ __forceinline__ float4 load(const elem *p) { return Vec4<bf16_t>::load(p); }
-    static __device__ __forceinline__ void store(elem *p, float4 v)
+    template <bool NT> static __device__ __forceinline__ float4 load(const elem *p)
     {
-        *reinterpret_cast<uint2 *>(p) = make_uint2((uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16),
-                                                   (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16));
+        const adv_u32x2 u = adv_load<NT, adv_u32x2>(p);
+        return make_float4(__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u), __uint_as_float(u[1] << 16),
+                           __uint_as_float(u[1] & 0xffff0000u));
+    }
+    template <bool NT> static __device__ __forceinline__ void store(elem *p, float4 v)
+    {
+        const adv_u32x2 u = {(uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16),
+                             (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16)};
+        adv_store<NT>(p, u);
     }
 };
 
@@ -105,9 +142,10 @@ struct AdvanceArgs {
     int H, P, N, G;
     int rows_per_thread;       // 1..kAdvMaxRows
     int slices;                // workgroups per (sequence, head)
+    bool stream;               // the states pass by the caches
 };
 
-template <typename IO, int LPR, int ST>
+template <typename IO, int LPR, int ST, bool NT>
 __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
 {
     typedef typename StateVec<ST>::elem state_t;
@@ -141,7 +179,7 @@ __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
         const int p = p_first + kRowsPerPass * r;
         S[r] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (r < R && p < P)
-            S[r] = StateVec<ST>::load(state + ((size_t)h * P + p) * N + 4 * c);
+            S[r] = StateVec<ST>::template load<NT>(state + ((size_t)h * P + p) * N + 4 * c);
     }
 
     for (int ti = sq.tile_begin; ti < sq.tile_end; ++ti) {
@@ -177,18 +215,27 @@ __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
     for (int r = 0; r < kAdvMaxRows; ++r) {
         const int p = p_first + kRowsPerPass * r;
         if (r < R && p < P)
-            StateVec<ST>::store(state + ((size_t)h * P + p) * N + 4 * c, S[r]);
+            StateVec<ST>::template store<NT>(state + ((size_t)h * P + p) * N + 4 * c, S[r]);
     }
+}
+
+template <typename IO, int LPR, int ST>
+void launch_st(const AdvanceArgs &a, dim3 grid, hipStream_t stream)
+{
+    if (a.stream)
+        hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ST, true>), grid, dim3(kAdvThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ST, false>), grid, dim3(kAdvThreads), 0, stream, a);
 }
 
 template <typename IO, int LPR>
 void launch_lpr(const AdvanceArgs &a, int batch, int state_type, hipStream_t stream)
 {
-    const dim3 grid((unsigned)(batch * a.H * a.slices)), block(kAdvThreads);
+    const dim3 grid((unsigned)(batch * a.H * a.slices));
     switch (state_type) {
-    case ADV_STATE_F16: hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ADV_STATE_F16>), grid, block, 0, stream, a); break;
-    case ADV_STATE_BF16: hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ADV_STATE_BF16>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ADV_STATE_F32>), grid, block, 0, stream, a); break;
+    case ADV_STATE_F16: launch_st<IO, LPR, ADV_STATE_F16>(a, grid, stream); break;
+    case ADV_STATE_BF16: launch_st<IO, LPR, ADV_STATE_BF16>(a, grid, stream); break;
+    default: launch_st<IO, LPR, ADV_STATE_F32>(a, grid, stream); break;
     }
 }
 
@@ -262,6 +309,7 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
     a.P = args.P;
     a.N = args.N;
     a.G = args.G;
+    a.stream = (long long)plan->batch * a.H * a.P * a.N * (state_type == ADV_STATE_F32 ? 4 : 2) > kAdvStreamBytes;
     return plan->shape.io_dtype == SSM_DT_F32 ? launch_io<float>(a, plan->batch, state_type, stream)
                                               : launch_io<bf16_t>(a, plan->batch, state_type, stream);
 }
