@@ -149,5 +149,7 @@ constexpr int kMfmaWorkgroupsPerRound = 256;
 constexpr int kMfmaMinStretchTiles = 64;
 constexpr int kMfmaMinCutTiles = 160;
 
-// The kernel in front of the scan works per (tile, group); below this many pairs each pair gets eight workgroups.
+// The kernel in front of the scan works per (tile, group); below kMfmaPrepSplitBelow pairs
+// each pair gets four workgroups, below kMfmaPrepApartBelow, where eight of them still run at once, eight.
 constexpr int kMfmaPrepSplitBelow = 256;
+constexpr int kMfmaPrepApartBelow = 64;

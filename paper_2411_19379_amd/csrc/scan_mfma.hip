@@ -271,10 +271,10 @@ __global__ __launch_bounds__(kPrepThreads) void ssm_prep_kernel(
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     PrepLds &L = *reinterpret_cast<PrepLds *>(lds_raw);
-    // parts = 1: one workgroup per (tile, group), its wave w writes quarter w of the operand images.  parts = 8 (small
-    // grids, which would leave most of the GPU idle): eight workgroups per (tile, group); workgroup `part` < 4 writes
-    // quarter `part` of the images, a sixteenth per wave, workgroup 4 + k transposes the dt of the k-th quarter of the
-    // heads.  Such a launch takes as long as its slowest workgroup, so the two jobs run side by side instead of one after
+    // parts = 1: one workgroup per (tile, group), its wave w writes quarter w of the operand images.  parts = 4 (small
+    // grids, which would leave most of the GPU idle): workgroup `part` writes quarter `part` of the images, a sixteenth
+    // per wave, and transposes the dt of a quarter of the heads.  parts = 8 (smaller still): workgroups 0..3 write the
+    // images and 4..7 transpose.  Such a launch takes as long as its slowest workgroup, so the two jobs run side by side instead of one after
     // the other (2048 tokens, 80 heads in one group: 7.6 -> 5.6 us; three tiles, 8 groups of 16 heads: 4.6 -> 3.6 us).
     const int tg = blockIdx.x / parts, part = blockIdx.x % parts;
     const int tile = tg / G, g = tg % G;
@@ -284,10 +284,10 @@ __global__ __launch_bounds__(kPrepThreads) void ssm_prep_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hg = H / G;  // heads of this group: g * hg .. g * hg + hg - 1
-    const bool whole = parts == 1, images = whole || part < 4, dt_rows = whole || part >= 4;
+    const bool whole = parts == 1, images = part < 4, dt_rows = parts < 8 || part >= 4;
     const int quarter = whole ? w : part;                    // which quarter of the images this wave works on
     const int sub0 = whole ? 0 : w, sub1 = whole ? 4 : w + 1;  // and which sixteenths of it
-    const int h_lo = whole ? 0 : hg * (part - 4) / 4, h_hi = whole ? hg : hg * (part - 3) / 4;  // heads whose dt
+    const int h_lo = whole ? 0 : hg * (part & 3) / 4, h_hi = whole ? hg : hg * ((part & 3) + 1) / 4;  // heads whose dt
 
     // B and C rows, 16 lanes per 256-byte row; rows past the end of a partial tile are zero
     if (images) {
@@ -1106,8 +1106,9 @@ hipError_t launch_scan_mfma(const ssm_plan *plan, const ScanArgs &args, void *wo
     bf16_t *dt_t = reinterpret_cast<bf16_t *>(base + ws.dt_rows);
     float *tile_decay = plan->n_carry > 0 ? reinterpret_cast<float *>(base + ws.tile_decay) : nullptr;
     float *carry = plan->n_carry > 0 ? reinterpret_cast<float *>(base + ws.carry) : nullptr;
-    // few (tile, group) pairs: eight workgroups each, so that the preparation does not run on a corner of the GPU
-    const int parts = (long long)n_tiles * args.G < kMfmaPrepSplitBelow ? 8 : 1;
+    // few (tile, group) pairs: four or eight workgroups each, so that the preparation does not run on a corner of the GPU
+    const long long pairs = (long long)n_tiles * args.G;
+    const int parts = pairs < kMfmaPrepApartBelow ? 8 : pairs < kMfmaPrepSplitBelow ? 4 : 1;
     hipLaunchKernelGGL(ssm_prep_kernel, dim3((unsigned)n_tiles * (unsigned)args.G * (unsigned)parts), dim3(kPrepThreads),
                        sizeof(PrepLds), stream, static_cast<const bf16_t *>(args.B), static_cast<const bf16_t *>(args.C),
                        static_cast<const bf16_t *>(args.dt), args.tiles, frags, dt_t, args.H, args.G, n_tiles, parts);
