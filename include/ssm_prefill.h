@@ -228,8 +228,10 @@ int ssm_prefill_noalloc(const ssm_plan_t *plan,
  * prefill": a kernel that rolls a checkpointed state forward by a few tokens
  * to reach an exact position); with one token per sequence it is the decode
  * step.  Every sequence of the plan brings its own [H,P,N] state in the
- * plan's state_dtype, which is advanced IN PLACE by the sequence's tokens with
- * the token recurrence in fp32 and rounded once on the way back.
+ * plan's state_dtype, which is advanced IN PLACE by the sequence's tokens in
+ * fp32 (token by token, or unrolled over tiles of them where the sequence has
+ * more than a few) and rounded once on the way back.  What comes out for a
+ * sequence does not depend on the other sequences of the batch.
  *
  *   state_ptrs [batch]  HOST array of DEVICE pointers; a NULL entry leaves
  *                       that sequence alone (its y rows are not written)

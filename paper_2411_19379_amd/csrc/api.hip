@@ -79,6 +79,7 @@ static int device_tables(const ssm_plan *plan, hipStream_t stream, ssm_plan::Dev
         }
     const size_t tile_bytes = round16(plan->tiles.size() * sizeof(SsmTile));
     const size_t seq_bytes = round16(plan->seqs.size() * sizeof(SsmSeq));
+    const size_t order_bytes = round16(plan->order.size() * sizeof(int32_t));
     const size_t ptr_bytes = round16((size_t)plan->batch * sizeof(void *));
     const size_t scan_seq_bytes = round16(plan->scan_seqs.size() * sizeof(SsmScanSeq));
     ssm_plan::DeviceTables t;
@@ -91,10 +92,11 @@ static int device_tables(const ssm_plan *plan, hipStream_t stream, ssm_plan::Dev
     };
     if ((e = hipMalloc(&t.tiles, tile_bytes ? tile_bytes : 16)) != hipSuccess)
         return hip_fail("hipMalloc(tile table)", e);
-    if ((e = hipMalloc(&t.seqs, seq_bytes ? seq_bytes : 16)) != hipSuccess) {
+    if ((e = hipMalloc(&t.seqs, seq_bytes ? seq_bytes + order_bytes : 16)) != hipSuccess) {
         release();
         return hip_fail("hipMalloc(sequence table)", e);
     }
+    t.order = static_cast<unsigned char *>(t.seqs) + seq_bytes;
     if ((e = hipMalloc(&t.ptrs, ptr_bytes ? ptr_bytes : 16)) != hipSuccess) {
         release();
         return hip_fail("hipMalloc(state pointers)", e);
@@ -106,6 +108,8 @@ static int device_tables(const ssm_plan *plan, hipStream_t stream, ssm_plan::Dev
     e = upload_table(t.tiles, plan->tiles.data(), plan->tiles.size() * sizeof(SsmTile), stream);
     if (e == hipSuccess)
         e = upload_table(t.seqs, plan->seqs.data(), plan->seqs.size() * sizeof(SsmSeq), stream);
+    if (e == hipSuccess)
+        e = upload_table(t.order, plan->order.data(), plan->order.size() * sizeof(int32_t), stream);
     if (e == hipSuccess)
         e = upload_table(t.scan_seqs, plan->scan_seqs.data(), plan->scan_seqs.size() * sizeof(SsmScanSeq), stream);
     if (e == hipSuccess)
@@ -362,6 +366,7 @@ extern "C" int ssm_state_advance(const ssm_plan_t *plan,
     args.state_out = nullptr;
     args.init_ptrs = nullptr;
     fill_args(plan, args, t.tiles, t.seqs);
+    args.order = static_cast<const int32_t *>(t.order);
     e = launch_state_advance(plan, args, static_cast<void *const *>(t.ptrs), stream);
     if (e != hipSuccess)
         return hip_fail("kernel launch", e);

@@ -88,6 +88,7 @@ struct ScanArgs {
     int32_t state_dtype;            // ssm_state_dtype_t
     const void *const *host_ptrs = nullptr;  // the same pointers as a host array of n_host_ptrs <= kStatePtrsInArgs
     int32_t n_host_ptrs = 0;                 // entries (then the device array is not needed)
+    const int32_t *order = nullptr;          // [batch] the plan's sequences by decreasing number of tokens
 };
 
 inline StatePtrs state_ptrs_of(const void *const *device_table, const void *const *host, int n)
@@ -102,9 +103,10 @@ inline StatePtrs state_ptrs_of(const void *const *device_table, const void *cons
 
 // Launchers implemented next to their kernels.
 hipError_t launch_scan_valu(const ssm_plan *plan, const ScanArgs &args, hipStream_t stream);
-// the fp32 matrix-core scan behind it, which is also the roll-forward over more than a few tokens
+// the fp32 matrix-core scan behind it, which is also the roll-forward over more than a few tokens: of all sequences, or
+// of the `n_seqs` longest ones
 bool scan_f32_supports(const ssm_shape_t &s);
-hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll, hipStream_t stream);
+hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll, int n_seqs, hipStream_t stream);
 hipError_t launch_scan_mfma(const ssm_plan *plan, const ScanArgs &args, void *workspace, hipStream_t stream);
 // events to record after the first and after the second kernel of the matrix-core scan on the calling thread
 // (nullptr: none)

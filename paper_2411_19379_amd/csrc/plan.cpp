@@ -165,6 +165,11 @@ extern "C" int ssm_plan_create(const ssm_shape_t *shape, int32_t batch,
         }
         plan->seqs[i].tile_end = (int32_t)plan->tiles.size();
     }
+    plan->order.resize(batch);
+    std::iota(plan->order.begin(), plan->order.end(), 0);
+    std::stable_sort(plan->order.begin(), plan->order.end(), [&](int32_t a, int32_t b) {
+        return cu_seqlens_host[a + 1] - cu_seqlens_host[a] > cu_seqlens_host[b + 1] - cu_seqlens_host[b];
+    });
     const int64_t wgs = (int64_t)batch * s.nheads * plan->p_split;
     if (wgs > 0x7fffffffLL / 4) {
         delete plan;
@@ -175,6 +180,13 @@ extern "C" int ssm_plan_create(const ssm_shape_t *shape, int32_t batch,
         ssm_plan_build_stretches(plan, kMfmaWorkgroupsPerRound, kMfmaMinStretchTiles);
     *out = plan;
     return SSM_OK;
+}
+
+int32_t ssm_plan_longer_than(const ssm_plan *plan, int32_t tokens)
+{
+    return (int32_t)(std::partition_point(plan->order.begin(), plan->order.end(),
+                                          [&](int32_t i) { return ssm_plan_tokens(plan, i) > tokens; }) -
+                     plan->order.begin());
 }
 
 static void ssm_plan_order_sequences(ssm_plan *plan);

@@ -93,6 +93,7 @@ struct ssm_plan {
     bool carry_chains = false;    // some sequence is cut into three or more stretches
     std::vector<SsmTile> tiles;
     std::vector<SsmSeq> seqs;
+    std::vector<int32_t> order;  // the sequences by decreasing number of tokens (ties: lower index first)
     std::vector<SsmScanSeq> scan_seqs;  // matrix-core scan only
     // Device copies of the two tables and a buffer for the per-call state
     // pointers, one set per GPU the plan has been used on.  A cache behind a
@@ -101,6 +102,7 @@ struct ssm_plan {
         int device = -1;
         void *tiles = nullptr;  // SsmTile[n_tiles]
         void *seqs = nullptr;   // SsmSeq[batch]
+        void *order = nullptr;  // int32_t[batch], in the same allocation
         void *scan_seqs = nullptr;  // SsmScanSeq[stretches]
         void *ptrs = nullptr;   // void*[batch], rewritten by every call that passes states
     };
@@ -115,6 +117,18 @@ void ssm_set_error(const std::string &msg);
 // sequences are cut into floor(per_round / s) stretches of at least `min_tiles` tiles each; the 64-channel variant is
 // chosen if the 32-channel one would not fit one round.
 void ssm_plan_build_stretches(ssm_plan *plan, int64_t per_round, int32_t min_tiles);
+
+// Tokens of sequence i.
+inline int32_t ssm_plan_tokens(const ssm_plan *plan, int32_t i)
+{
+    const SsmSeq &q = plan->seqs[i];
+    if (q.tile_end <= q.tile_begin)
+        return 0;
+    const SsmTile &first = plan->tiles[q.tile_begin], &last = plan->tiles[q.tile_end - 1];
+    return last.tok0 + last.len - first.tok0;
+}
+// How many sequences have more than `tokens` tokens: they are the first ones of plan->order.
+int32_t ssm_plan_longer_than(const ssm_plan *plan, int32_t tokens);
 
 // Where the parts of the matrix-core scan's workspace start (bytes from its base), and its size.
 struct SsmMfmaWorkspace {

@@ -76,6 +76,7 @@ struct F32Args {
     bool roll;                      // roll-forward in place
     const SsmTile *tiles;
     const SsmSeq *seqs;
+    const int32_t *order;           // the launch's k-th sequence is order[k]; null: k
     int H, P, G, slices, state_dtype;
     int units_per_tile = 1;         // split-operand kernel: units of 32 tokens per tile of the plan
 };
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
     const int H = a.H, P = a.P, G = a.G, st = a.state_dtype;
     const int slice = blockIdx.x % a.slices;
     const int h = (blockIdx.x / a.slices) % H;
-    const int seq = blockIdx.x / (a.slices * H);
+    const int rank = blockIdx.x / (a.slices * H), seq = a.order ? a.order[rank] : rank;
     const int g = h / (H / G);
     const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -554,7 +555,7 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
     const int H = a.H, P = a.P, G = a.G, st = a.state_dtype;
     const int slice = blockIdx.x % a.slices;
     const int h = (blockIdx.x / a.slices) % H;
-    const int seq = blockIdx.x / (a.slices * H);
+    const int rank = blockIdx.x / (a.slices * H), seq = a.order ? a.order[rank] : rank;
     const int g = h / (H / G);
     const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1121,8 +1122,8 @@ bool scan_f32_supports(const ssm_shape_t &s)
 }
 
 // roll: the states behind init_ptrs / host_ptrs are advanced in place over the sequences' tokens.  Else the scan over the
-// plan's tiles.
-hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll, hipStream_t stream)
+// plan's tiles.  n_seqs: only so many of the plan's sequences, the longest ones (needs args.order unless it is all).
+hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll, int n_seqs, hipStream_t stream)
 {
     F32Args a;
     a.x = args.x, a.dt = args.dt, a.B = args.B, a.C = args.C;
@@ -1133,21 +1134,15 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     a.roll = roll;
     a.tiles = args.tiles;
     a.seqs = args.seqs;
+    a.order = n_seqs < plan->batch ? args.order : nullptr;
     a.H = args.H, a.P = args.P, a.G = args.G;
     a.state_dtype = args.state_dtype;
     // Slices of 16 channels per workgroup: more of them share the scores (4 nb of a tile's products in fp32), fewer leave
     // more workgroups.  Products per tile times rounds of 256 workgroups, the smaller the better.
     const bool split = plan->shape.io_dtype == SSM_DT_BF16;
     const int nb = args.N / 16, all = args.P / 16;
-    long long streams = 0;
-    int longest = 0;
-    for (const SsmSeq &q : plan->seqs)
-        if (q.tile_end > q.tile_begin) {
-            const SsmTile &first = plan->tiles[q.tile_begin], &last = plan->tiles[q.tile_end - 1];
-            longest = last.tok0 + last.len - first.tok0 > longest ? last.tok0 + last.len - first.tok0 : longest;
-            ++streams;
-        }
-    streams *= args.H;
+    const int busy = ssm_plan_longer_than(plan, 0), longest = ssm_plan_tokens(plan, plan->order[0]);
+    const long long streams = (long long)(busy < n_seqs ? busy : n_seqs) * args.H;
     a.units_per_tile = (plan->tile_tokens + kUnit - 1) / kUnit;
     int nc = 1;
     long long best = 0;
@@ -1163,10 +1158,10 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     }
     const int units = (longest + kUnit - 1) / kUnit;
     switch (nb) {
-    case 1: return launch_f32_nc<1>(a, split, nc, plan->batch, units, stream);
-    case 2: return launch_f32_nc<2>(a, split, nc, plan->batch, units, stream);
-    case 4: return launch_f32_nc<4>(a, split, nc, plan->batch, units, stream);
-    default: return launch_f32_nc<8>(a, split, nc, plan->batch, units, stream);
+    case 1: return launch_f32_nc<1>(a, split, nc, n_seqs, units, stream);
+    case 2: return launch_f32_nc<2>(a, split, nc, n_seqs, units, stream);
+    case 4: return launch_f32_nc<4>(a, split, nc, n_seqs, units, stream);
+    default: return launch_f32_nc<8>(a, split, nc, n_seqs, units, stream);
     }
 }
 
@@ -1175,7 +1170,7 @@ size_t ssm_valu_lds_bytes(int P, int N);
 hipError_t launch_scan_valu(const ssm_plan *plan, const ScanArgs &args, hipStream_t stream)
 {
     if (scan_f32_supports(plan->shape))
-        return launch_scan_f32(plan, args, false, stream);
+        return launch_scan_f32(plan, args, false, plan->batch, stream);
     const int PN = args.P * args.N;
     int ept = 1;
     while (ept * kThreads < PN)

@@ -18,8 +18,10 @@ namespace {
 
 constexpr int kAdvThreads = 256;
 constexpr int kAdvMaxRows = 8;  // state rows per thread
-// A batch with a longer sequence is rolled forward by the matrix-core kernels of scan_valu.hip (fp32 as here): the token
-// loop is one chain of dependent loads, 1.8 us a token.  Three sequences of 17 to 256 tokens at 128 heads: 466 -> 37 us.
+// A longer sequence is rolled forward by the matrix-core kernels of scan_valu.hip (fp32 as here): the token loop is one
+// chain of dependent loads, 1.8 us a token.  Three sequences of 17 to 256 tokens at 128 heads: 466 -> 37 us.  The
+// sequence's own length decides and nothing else of the batch, so that its bits do not depend on its neighbours; a batch
+// with both kinds takes two launches, each over its own sequences.
 constexpr int kAdvMaxTokens = 4;
 // States of more than this per call pass by the caches (non-temporal loads and stores): in a serving program every layer's
 // states come by between two steps, and two layers of this size do not fit the 256 MiB memory-side cache, so what a call
@@ -139,6 +141,7 @@ struct AdvanceArgs {
     StatePtrs states;          // [batch] device pointers, each [H,P,N] in the state type; null = leave the sequence alone
     const SsmTile *tiles;
     const SsmSeq *seqs;
+    const int32_t *order;      // the launch's k-th sequence is order[k]; null: k
     int H, P, N, G;
     int rows_per_thread;       // 1..kAdvMaxRows
     int slices;                // workgroups per (sequence, head)
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
     const int H = a.H, P = a.P, N = a.N, G = a.G;
     const int slice = blockIdx.x % a.slices;
     const int h = (blockIdx.x / a.slices) % H;
-    const int seq = blockIdx.x / (a.slices * H);
+    const int rank = blockIdx.x / (a.slices * H), seq = a.order ? a.order[rank] : rank;
     const int g = h / (H / G);
     const int c = threadIdx.x % LPR;   // this thread holds state columns 4c .. 4c+3
     const int rs = threadIdx.x / LPR;  // row slot inside a pass
@@ -273,6 +276,7 @@ bool state_advance_supports(const ssm_shape_t &s)
 
 // Advance the state of every sequence of the plan in place by the sequence's tokens; `d_state_ptrs` is a device array
 // of plan->batch device pointers to states in the plan's state type (not needed if args.host_ptrs is set).  y may be null.
+// args.order is needed.
 // Checkpoints of the plan are ignored (the result is the in-place state after the last token).
 hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void *const *d_state_ptrs,
                                 hipStream_t stream)
@@ -282,17 +286,14 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
         return hipErrorInvalidValue;
     if (plan->batch == 0 || plan->tiles.empty())
         return hipSuccess;
-    int longest = 0;
-    for (const SsmSeq &q : plan->seqs)
-        if (q.tile_end > q.tile_begin) {
-            const SsmTile &first = plan->tiles[q.tile_begin], &last = plan->tiles[q.tile_end - 1];
-            longest = last.tok0 + last.len - first.tok0 > longest ? last.tok0 + last.len - first.tok0 : longest;
-        }
-    if (longest > kAdvMaxTokens && scan_f32_supports(plan->shape))
-    {
+    const int busy = ssm_plan_longer_than(plan, 0);
+    const int n_long = scan_f32_supports(plan->shape) ? ssm_plan_longer_than(plan, kAdvMaxTokens) : 0;
+    if (n_long > 0) {
         ScanArgs roll = args;
         roll.init_ptrs = d_state_ptrs;
-        return launch_scan_f32(plan, roll, true, stream);
+        const hipError_t e = launch_scan_f32(plan, roll, true, n_long == busy ? plan->batch : n_long, stream);
+        if (e != hipSuccess || n_long == busy)
+            return e;
     }
     AdvanceArgs a;
     a.x = args.x;
@@ -305,11 +306,13 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
     a.states = state_ptrs_of(d_state_ptrs, args.host_ptrs, args.n_host_ptrs);
     a.tiles = args.tiles;
     a.seqs = args.seqs;
+    a.order = n_long > 0 ? args.order + n_long : nullptr;
     a.H = args.H;
     a.P = args.P;
     a.N = args.N;
     a.G = args.G;
     a.stream = (long long)plan->batch * a.H * a.P * a.N * (state_type == ADV_STATE_F32 ? 4 : 2) > kAdvStreamBytes;
-    return plan->shape.io_dtype == SSM_DT_F32 ? launch_io<float>(a, plan->batch, state_type, stream)
-                                              : launch_io<bf16_t>(a, plan->batch, state_type, stream);
+    const int n_seqs = n_long > 0 ? busy - n_long : plan->batch;
+    return plan->shape.io_dtype == SSM_DT_F32 ? launch_io<float>(a, n_seqs, state_type, stream)
+                                              : launch_io<bf16_t>(a, n_seqs, state_type, stream);
 }

@@ -135,7 +135,9 @@ int main(int argc, char **argv)
     ScanArgs args;
     args.x = x, args.dt = dt, args.A = A, args.B = B, args.C = C, args.D = D, args.y = y, args.state_out = st;
     args.init_ptrs = any_init ? reinterpret_cast<const void *const *>(init) : nullptr;
-    args.tiles = tiles, args.seqs = seqs, args.scan_seqs = scan_seqs;
+    int32_t *order = static_cast<int32_t *>(guarded(sizeof(int32_t) * (batch ? batch : 1), end_aligned));
+    memcpy(order, plan->order.data(), sizeof(int32_t) * batch);
+    args.tiles = tiles, args.seqs = seqs, args.scan_seqs = scan_seqs, args.order = order;
     args.H = H, args.P = P, args.N = N, args.G = G, args.p_split = plan->p_split;
     args.state_dtype = st_type;
     if (advance) {
