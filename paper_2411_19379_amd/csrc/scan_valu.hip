@@ -188,7 +188,7 @@ template <int NB, int NC, int NW> struct F32Lds {
 };
 
 template <int NB, int NC, int NW>
-__global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
+__global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_f32_kernel(F32Args a)
 {
     typedef float IO;
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -226,16 +226,24 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
     const size_t GN = (size_t)G * N, HP = (size_t)H * P;
     const size_t xcol = (size_t)h * P + 16 * NC * slice + li;
 
-    for (int b = w; b < NC * NB; b += NW) {
-        const int c = b / NB, f4 = b % NB;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (from)
-            v = state_load4(from, state_row + (size_t)16 * c * N + 4 * f4, st);
-        L.S[c][f4][lane] = v;
+    // One wave alone keeps the state in its registers: what it starts from arrives while the first tile is computed.
+    float4 sp[NC][NB];
+    auto start_at = [&](int c, int f4) {
+        return from ? state_load4(from, state_row + (size_t)16 * c * N + 4 * f4, st) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    if constexpr (NW == 1) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int f4 = 0; f4 < NB; ++f4)
+                sp[c][f4] = start_at(c, f4);
+    } else {
+        for (int b = w; b < NC * NB; b += NW)
+            L.S[b / NB][b % NB][lane] = start_at(b / NB, b % NB);
+        if (threadIdx.x == 0)
+            L.done = 0;
+        __syncthreads();  // the only one: the starting state and the counter are in place
     }
-    if (threadIdx.x == 0)
-        L.done = 0;
-    __syncthreads();  // the only one: the starting state and the counter are in place
 
     F32Wave &W = L.wv[w];
     for (int k = w; k < n_tiles; k += NW) {
@@ -312,14 +320,15 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
 #pragma unroll
         for (int c = 0; c < NC * NB; ++c)  // done before the wait starts
             asm volatile("" : "+v"(Sl[c]));
-        f32_wait_counter(&L.done, k);
         // read the state, multiply-add, write it back, publish
-        float4 sp[NC][NB];
+        if constexpr (NW > 1) {
+            f32_wait_counter(&L.done, k);
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
+            for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int f4 = 0; f4 < NB; ++f4)
-                sp[c][f4] = L.S[c][f4][lane];
+                for (int f4 = 0; f4 < NB; ++f4)
+                    sp[c][f4] = L.S[c][f4][lane];
+        }
         // element f = NB rr + nb of a lane's run is element rr of block nb
         auto next = [&](int c, int f) {
             const float4 &q = sp[c][f / 4];
@@ -332,9 +341,19 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
 #pragma unroll
             for (int f4 = 0; f4 < NB; ++f4) {
                 sn[c][f4] = make_float4(next(c, 4 * f4), next(c, 4 * f4 + 1), next(c, 4 * f4 + 2), next(c, 4 * f4 + 3));
-                L.S[c][f4][lane] = sn[c][f4];
+                if constexpr (NW > 1)
+                    L.S[c][f4][lane] = sn[c][f4];
             }
-        f32_publish_counter(&L.done, k + 1, lane);
+        if constexpr (NW > 1)
+            f32_publish_counter(&L.done, k + 1, lane);
+        auto keep_state = [&]() {
+            if constexpr (NW == 1)
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int f4 = 0; f4 < NB; ++f4)
+                        sp[c][f4] = sn[c][f4];
+        };
         if (ckpt >= 0 || (roll && k == n_tiles - 1)) {
             void *to = roll ? const_cast<void *>(from) : a.state_out;
             const size_t at = (roll ? 0 : (size_t)ckpt * HP * N) + state_row;
@@ -344,8 +363,10 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
                 for (int f4 = 0; f4 < NB; ++f4)
                     state_store4(to, at + (size_t)16 * c * N + 4 * f4, sn[c][f4], st);
         }
-        if (!y)
+        if (!y) {
+            keep_state();
             continue;
+        }
         const float4 ei4 = *reinterpret_cast<const float4 *>(&W.ei[4 * kq]);
         const float ei[4] = {ei4.x, ei4.y, ei4.z, ei4.w};
 #pragma unroll
@@ -392,6 +413,7 @@ __global__ __launch_bounds__(64 * NW) void ssm_scan_f32_kernel(F32Args a)
                     IoTraits<IO>::store(y + ((size_t)tok0 + 4 * kq + r) * HP + xcol + 16 * c,
                                         __builtin_fmaf(Dh, xv[c][r], Y0[r]));
         }
+        keep_state();
     }
 }
 
@@ -542,7 +564,7 @@ template <int NB, int NC, int NW> struct SplitLds {
     SplitWave wv[NW];
 };
 
-// Waves per SIMD that the registers are budgeted for: workgroups of four waves share a compute unit in twos.
+// Waves per SIMD that the registers are budgeted for: two, so that the workgroups of a launch share a compute unit.
 template <int NB, int NC, int NW>
 __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kernel(F32Args a)
 {
@@ -596,13 +618,28 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
             return make_uint4(r[4 * s], r[4 * s + 1], r[4 * s + 2], r[4 * s + 3]);
     };
 
+    // One wave alone keeps the state in its registers: what it starts from arrives while the first unit is computed.
+    float4 sp[NC][NB];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int f4 = 0; f4 < NB; ++f4)
+            sp[c][f4] = make_float4(0.f, 0.f, 0.f, 0.f);
     auto start_from = [&](auto type) {
         const __amdgpu_buffer_rsrc_t part = state_part(from, 0);
+        if constexpr (NW == 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int f4 = 0; f4 < NB; ++f4)
+                    sp[c][f4] = split_state_load4<decltype(type)::value>(part, lane_elem + c * N + 4 * f4);
+            return;
+        }
         for (int b = w; b < NC * NB; b += NW)
             L.S[b / NB][b % NB][lane] = split_state_load4<decltype(type)::value>(part, lane_elem + b / NB * N + 4 * (b % NB));
     };
     if (!from) {
-        for (int b = w; b < NC * NB; b += NW)
+        for (int b = w; NW > 1 && b < NC * NB; b += NW)
             L.S[b / NB][b % NB][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
     } else if (st == SSM_ST_F32) {
         start_from(StateType<SSM_ST_F32>());
@@ -611,9 +648,11 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
     } else {
         start_from(StateType<SSM_ST_BF16>());
     }
-    if (threadIdx.x == 0)
-        L.done = 0;
-    __syncthreads();  // the only one: the starting state and the counter are in place
+    if constexpr (NW > 1) {
+        if (threadIdx.x == 0)
+            L.done = 0;
+        __syncthreads();  // the only one: the starting state and the counter are in place
+    }
 
     SplitWave &W = L.wv[w];
     for (int k = w; k < n_units; k += NW) {
@@ -632,8 +671,10 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
         len = __builtin_amdgcn_readfirstlane(len);
         ckpt = __builtin_amdgcn_readfirstlane(ckpt);
         if (len <= 0) {  // the second half of a tile that has none: the state passes through
-            f32_wait_counter(&L.done, k);
-            f32_publish_counter(&L.done, k + 1, lane);
+            if constexpr (NW > 1) {
+                f32_wait_counter(&L.done, k);
+                f32_publish_counter(&L.done, k + 1, lane);
+            }
             continue;
         }
         // ---- the unit's operands as they come from device memory.  Rows past the end of a partial unit re-read its last
@@ -773,14 +814,15 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
         for (int c = 0; c < NC * NB; ++c)  // done before the wait starts
             asm volatile("" : "+v"(Sl[c]));
         __builtin_amdgcn_sched_barrier(0);
-        f32_wait_counter(&L.done, k);
         // ---- read the state, multiply-add, write it back, publish
-        float4 sp[NC][NB];
+        if constexpr (NW > 1) {
+            f32_wait_counter(&L.done, k);
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
+            for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int f4 = 0; f4 < NB; ++f4)
-                sp[c][f4] = L.S[c][f4][lane];
+                for (int f4 = 0; f4 < NB; ++f4)
+                    sp[c][f4] = L.S[c][f4][lane];
+        }
         // element f = NB rr + nb of a lane's run is element rr of block nb
         auto next = [&](int c, int f) {
             const float4 &q = sp[c][f / 4];
@@ -790,13 +832,23 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
         auto next4 = [&](int c, int f4) {
             return make_float4(next(c, 4 * f4), next(c, 4 * f4 + 1), next(c, 4 * f4 + 2), next(c, 4 * f4 + 3));
         };
+        if constexpr (NW > 1) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
+            for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int f4 = 0; f4 < NB; ++f4)
-                L.S[c][f4][lane] = next4(c, f4);
-        __builtin_amdgcn_sched_barrier(0);
-        f32_publish_counter(&L.done, k + 1, lane);
+                for (int f4 = 0; f4 < NB; ++f4)
+                    L.S[c][f4][lane] = next4(c, f4);
+            __builtin_amdgcn_sched_barrier(0);
+            f32_publish_counter(&L.done, k + 1, lane);
+        }
+        auto keep_state = [&]() {
+            if constexpr (NW == 1)
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int f4 = 0; f4 < NB; ++f4)
+                        sp[c][f4] = next4(c, f4);
+        };
         if (ckpt >= 0 || (roll && k == n_units - 1)) {
             const __amdgpu_buffer_rsrc_t part =
                 state_part(roll ? from : a.state_out, roll ? 0 : (size_t)ckpt * H * P * N);
@@ -814,8 +866,10 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
             else
                 keep(StateType<SSM_ST_BF16>());
         }
-        if (!y)
+        if (!y) {
+            keep_state();
             continue;
+        }
         // ---- outputs, one channel of the lane after the other: element r of Y[ih] is token 16 ih + 4 kq + r
         auto intra = [&](const uint4 &xo, f32x4 &y0, f32x4 &y1) {
             const uint4 x2 = make_uint4(xo.x, xo.y, xo.x, xo.y);
@@ -916,51 +970,88 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
                 __builtin_amdgcn_raw_buffer_store_b64(both, ys, own, row, 0);
             }
         }
+        keep_state();
     }
 }
 
-template <int NB, int NC>
-hipError_t launch_f32(const F32Args &a, int batch, hipStream_t stream)
+// What a launch covers: `seqs` sequences of `units` units (tiles of 16 tokens, units of 32) in all, `longest` in one.
+struct F32Batch {
+    int seqs, longest;
+    long long units;
+};
+
+// Waves per workgroup.  A workgroup's waves work on one sequence, so a long sequence wants many of them.  But waves a
+// sequence has no units for only keep others off the compute unit, and in a launch that fills the GPU anyway waves come
+// cheaper as workgroups of their own, with no hand-off between them.  So: as few as keep the longest sequence from
+// outlasting the average of the `resident` waves that the GPU holds (by 4 : 3, or more than four waves, if not all of the
+// workgroups then run at once, by 2 : 3), and at least four where up to three workgroups share a compute unit, which then read
+// the states faster.  Against eight waves for every launch (sixteen with d_state 16 in fp32), per call: 600 sequences of one
+// token, 32 heads x 64 channels, d_state 16, 328 -> 56 us in bf16 storage, 327 -> 45 us in fp32 (the vector-ALU kernel: 99
+// and 98); 64 sequences of 100 tokens 43 -> 21 us and 57 -> 32 us; roll-forward of 64 sequences by 8 tokens, 80 heads x 64
+// channels, d_state 128, 140 -> 74 us with fp16 states, 288 -> 107 us in fp32.
+inline int scan_waves(const F32Batch &b, long long streams_per_seq, int resident, int least, int most)
 {
-    constexpr int NW = NB == 1 ? 16 : 8;
-    hipLaunchKernelGGL((ssm_scan_f32_kernel<NB, NC, NW>), dim3((unsigned)batch * (unsigned)a.H * (unsigned)a.slices),
+    const long long wgs = b.seqs * streams_per_seq, per_wave = (b.units * streams_per_seq + resident - 1) / resident;
+    int nw = wgs <= 768 ? 4 : least;
+    while (nw < most && nw < b.longest) {
+        const bool in_turn = nw >= 4 && 2ll * nw * wgs > resident;  // workgroups of twice the waves would have to queue
+        if ((in_turn ? 6 : 3) * nw * per_wave >= 4ll * b.longest)
+            break;
+        nw *= 2;
+    }
+#ifdef SSM_F32_WAVES  // the emulator's: a number of waves for every launch, 0: this rule
+    if (SSM_F32_WAVES)
+        nw = SSM_F32_WAVES < least ? least : SSM_F32_WAVES;
+#endif
+    return nw;
+}
+
+template <int NB, int NC, int NW> hipError_t launch_f32_nw(const F32Args &a, const F32Batch &b, hipStream_t stream)
+{
+    hipLaunchKernelGGL((ssm_scan_f32_kernel<NB, NC, NW>), dim3((unsigned)b.seqs * (unsigned)a.H * (unsigned)a.slices),
                        dim3(64 * NW), sizeof(F32Lds<NB, NC, NW>), stream, a);
     return hipGetLastError();
 }
-
-template <int NB, int NC, int NW>
-hipError_t launch_split_nw(const F32Args &a, int batch, hipStream_t stream)
+template <int NB, int NC> hipError_t launch_f32(const F32Args &a, const F32Batch &b, hipStream_t stream)
 {
-    hipLaunchKernelGGL((ssm_scan_split_kernel<NB, NC, NW>), dim3((unsigned)batch * (unsigned)a.H * (unsigned)a.slices),
+    // registers for about three waves on each of the 1024 SIMDs; with d_state 128 one wave alone is slow to read the state
+    switch (scan_waves(b, (long long)a.H * a.slices, 3 * 1024, NB == 8 ? 2 : 1, NB == 1 ? 16 : 8)) {
+    case 1: return launch_f32_nw<NB, NC, NB == 8 ? 2 : 1>(a, b, stream);
+    case 2: return launch_f32_nw<NB, NC, 2>(a, b, stream);
+    case 4: return launch_f32_nw<NB, NC, 4>(a, b, stream);
+    case 8: return launch_f32_nw<NB, NC, 8>(a, b, stream);
+    default: return launch_f32_nw<NB, NC, NB == 1 ? 16 : 8>(a, b, stream);
+    }
+}
+
+template <int NB, int NC, int NW> hipError_t launch_split_nw(const F32Args &a, const F32Batch &b, hipStream_t stream)
+{
+    hipLaunchKernelGGL((ssm_scan_split_kernel<NB, NC, NW>), dim3((unsigned)b.seqs * (unsigned)a.H * (unsigned)a.slices),
                        dim3(64 * NW), sizeof(SplitLds<NB, NC, NW>), stream, a);
     return hipGetLastError();
 }
-
-// Waves per workgroup: 8, or with larger states 4 where a sequence has no more units or where the launch has enough
-// workgroups for two on each of the 256 compute units (the roll-forward above with 8 waves: 46 us; d_state 16 with 16
-// waves, whose registers then spill: 94 us).
-template <int NB, int NC>
-hipError_t launch_split(const F32Args &a, int batch, int units, hipStream_t stream)
+template <int NB, int NC> hipError_t launch_split(const F32Args &a, const F32Batch &b, hipStream_t stream)
 {
-    if (NB == 1 || (units > 4 && (long long)batch * a.H * a.slices <= 256))
-        return launch_split_nw<NB, NC, 8>(a, batch, stream);
-    if constexpr (NB > 1)
-        return launch_split_nw<NB, NC, 4>(a, batch, stream);
-    return hipErrorInvalidValue;
+    // registers for two waves per SIMD where the state is large; sixteen waves would spill (94 instead of 67 us for the
+    // packed batch above)
+    switch (scan_waves(b, (long long)a.H * a.slices, 2 * 1024, 1, 8)) {
+    case 1: return launch_split_nw<NB, NC, 1>(a, b, stream);
+    case 2: return launch_split_nw<NB, NC, 2>(a, b, stream);
+    case 4: return launch_split_nw<NB, NC, 4>(a, b, stream);
+    default: return launch_split_nw<NB, NC, 8>(a, b, stream);
+    }
 }
 
-template <int NB>
-hipError_t launch_f32_nc(F32Args &a, bool split, int nc, int batch, int units, hipStream_t stream)
+template <int NB> hipError_t launch_f32_nc(F32Args &a, bool split, int nc, const F32Batch &b, hipStream_t stream)
 {
     a.slices = a.P / (16 * nc);
     constexpr int kMost = NB <= 2 ? 4 : 2;  // four slices only with small states
-    if (nc == 4)
-        return split ? launch_split<NB, NB == 8 ? 1 : kMost>(a, batch, units, stream) : launch_f32<NB, kMost>(a, batch, stream);
     constexpr int kMostSplit = NB == 8 ? 1 : kMost;
+    if (nc == 4)
+        return split ? launch_split<NB, kMostSplit>(a, b, stream) : launch_f32<NB, kMost>(a, b, stream);
     if (nc == 2)
-        return split ? launch_split<NB, kMostSplit < 2 ? 1 : 2>(a, batch, units, stream)
-                     : launch_f32<NB, 2>(a, batch, stream);
-    return split ? launch_split<NB, 1>(a, batch, units, stream) : launch_f32<NB, 1>(a, batch, stream);
+        return split ? launch_split<NB, kMostSplit < 2 ? 1 : 2>(a, b, stream) : launch_f32<NB, 2>(a, b, stream);
+    return split ? launch_split<NB, 1>(a, b, stream) : launch_f32<NB, 1>(a, b, stream);
 }
 
 // ================================================================ vector ALUs, any shape
@@ -1141,7 +1232,7 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     // more workgroups.  Products per tile times rounds of 256 workgroups, the smaller the better.
     const bool split = plan->shape.io_dtype == SSM_DT_BF16;
     const int nb = args.N / 16, all = args.P / 16;
-    const int busy = ssm_plan_longer_than(plan, 0), longest = ssm_plan_tokens(plan, plan->order[0]);
+    const int busy = ssm_plan_longer_than(plan, 0);
     const long long streams = (long long)(busy < n_seqs ? busy : n_seqs) * args.H;
     a.units_per_tile = (plan->tile_tokens + kUnit - 1) / kUnit;
     int nc = 1;
@@ -1156,12 +1247,21 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
         if (c == 1 || cost <= best)
             nc = c, best = cost;
     }
-    const int units = (longest + kUnit - 1) / kUnit;
+    // the scan's units are the plan's tiles; the roll-forward cuts the tokens itself
+    const SsmSeq &lq = plan->seqs[plan->order[0]];
+    F32Batch batch = {n_seqs, lq.tile_end - lq.tile_begin, (long long)plan->tiles.size()};
+    if (roll) {
+        const int unit = split ? kUnit : kValuTileTokens;
+        batch.longest = (ssm_plan_tokens(plan, plan->order[0]) + unit - 1) / unit;
+        batch.units = 0;
+        for (int r = 0; r < n_seqs && r < busy; ++r)
+            batch.units += (ssm_plan_tokens(plan, plan->order[r]) + unit - 1) / unit;
+    }
     switch (nb) {
-    case 1: return launch_f32_nc<1>(a, split, nc, n_seqs, units, stream);
-    case 2: return launch_f32_nc<2>(a, split, nc, n_seqs, units, stream);
-    case 4: return launch_f32_nc<4>(a, split, nc, n_seqs, units, stream);
-    default: return launch_f32_nc<8>(a, split, nc, n_seqs, units, stream);
+    case 1: return launch_f32_nc<1>(a, split, nc, batch, stream);
+    case 2: return launch_f32_nc<2>(a, split, nc, batch, stream);
+    case 4: return launch_f32_nc<4>(a, split, nc, batch, stream);
+    default: return launch_f32_nc<8>(a, split, nc, batch, stream);
     }
 }
 

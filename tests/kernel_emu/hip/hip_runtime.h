@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstddef>
 #include <cstdint>
+#include <cstdlib>
 #include <cstring>
 
 #define __global__
@@ -124,6 +125,7 @@ template <typename F> void launch(dim3 grid, dim3 block, size_t lds_bytes, F &&b
 #define __builtin_amdgcn_readfirstlane(v) emu::readfirstlane((v), __LINE__)
 #define __shfl(v, l, w) __uint_as_float((uint32_t)emu::shfl((int)__float_as_uint(v), (l), __LINE__))
 namespace emu {
+inline int env_int(const char *name) { return getenv(name) ? atoi(getenv(name)) : 0; }
 inline bool any_lane(bool v, int line)
 {
     bool any = false;
