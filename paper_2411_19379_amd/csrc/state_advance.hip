@@ -19,10 +19,20 @@ namespace {
 constexpr int kAdvThreads = 256;
 constexpr int kAdvMaxRows = 8;  // state rows per thread
 // A longer sequence is rolled forward by the matrix-core kernels of scan_valu.hip (fp32 as here): the token loop is one
-// chain of dependent loads, 1.8 us a token.  Three sequences of 17 to 256 tokens at 128 heads: 466 -> 37 us.  The
-// sequence's own length decides and nothing else of the batch, so that its bits do not depend on its neighbours; a batch
-// with both kinds takes two launches, each over its own sequences.
+// chain of dependent loads and sums, 1 to 2 us a token.  Three sequences of 17 to 256 tokens at 128 heads: 466 -> 37 us.
+// The sequence's own length decides and nothing else of the batch, so that its bits do not depend on its neighbours; a
+// batch with both kinds takes two launches, each over its own sequences.
+// Where the line lies, token recurrence against matrix cores, us per call (heads x 64 channels, d_state 128):
+//   bf16, 128 heads, fp32 states   1 sequence 4 tokens 12 / 7    8 x 5 tokens 22 / 23    64 x 5 137 / 159   64 x 8 185 / 165
+//   bf16, 80 heads, fp16 states    1 x 4  12 / 6                 8 x 5  18 / 14          64 x 4 63 / 72     64 x 5  73 / 72
+//   fp32, 80 heads                 1 x 5  14 / 9    8 x 5  18 / 21   8 x 7  21 / 21      64 x 5 79 / 105    64 x 8 102 / 107
+// With smaller states the matrix cores win from 2 to 5 tokens on at any number of sequences.
 constexpr int kAdvMaxTokens = 4;
+constexpr int kAdvMaxTokensF32Wide = 7;  // fp32 storage and d_state 128: the fp32 instruction is the slowest
+inline int advance_max_tokens(const ssm_shape_t &s)
+{
+    return s.io_dtype == SSM_DT_F32 && s.d_state >= 128 ? kAdvMaxTokensF32Wide : kAdvMaxTokens;
+}
 // States of more than this per call pass by the caches (non-temporal loads and stores): in a serving program every layer's
 // states come by between two steps, and two layers of this size do not fit the 256 MiB memory-side cache, so what a call
 // leaves there is gone before it is read again and only displaces.  64 sequences x 128 heads x 64 x 128 in fp32 (256 MiB),
@@ -287,7 +297,7 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
     if (plan->batch == 0 || plan->tiles.empty())
         return hipSuccess;
     const int busy = ssm_plan_longer_than(plan, 0);
-    const int n_long = scan_f32_supports(plan->shape) ? ssm_plan_longer_than(plan, kAdvMaxTokens) : 0;
+    const int n_long = scan_f32_supports(plan->shape) ? ssm_plan_longer_than(plan, advance_max_tokens(plan->shape)) : 0;
     if (n_long > 0) {
         ScanArgs roll = args;
         roll.init_ptrs = d_state_ptrs;

@@ -10,7 +10,7 @@ from workloads import LayerShape, make_workload
 from workloads.gen import _gen, draw_layer_inputs
 
 SHAPES = {"n128": (2, 32, 128, 1, 64), "n16": (4, 64, 16, 2, 64)}
-BATCHES = [[4, 5], [1, 70, 4, 0, 33, 5], [64, 1, 2]]
+BATCHES = [[4, 5], [7, 8], [1, 70, 4, 0, 33, 5], [64, 1, 2]]
 
 
 def _workload(dims, lens, device, io):
