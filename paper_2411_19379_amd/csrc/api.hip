@@ -354,7 +354,7 @@ extern "C" int ssm_state_advance(const ssm_plan_t *plan,
     if (e != hipSuccess)
         return hip_fail("upload of the state pointers", e);
     ScanArgs args;
-    args.host_ptrs = in_args ? state_ptrs : nullptr;
+    args.host_ptrs = state_ptrs;
     args.n_host_ptrs = in_args ? plan->batch : 0;
     args.x = x;
     args.dt = dt;

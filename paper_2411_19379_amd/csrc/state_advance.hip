@@ -34,12 +34,19 @@ inline int advance_max_tokens(const ssm_shape_t &s)
     return s.io_dtype == SSM_DT_F32 && s.d_state >= 128 ? kAdvMaxTokensF32Wide : kAdvMaxTokens;
 }
 // States of more than this per call pass by the caches (non-temporal loads and stores): in a serving program every layer's
-// states come by between two steps, and two layers of this size do not fit the 256 MiB memory-side cache, so what a call
-// leaves there is gone before it is read again and only displaces.  64 sequences x 128 heads x 64 x 128 in fp32 (256 MiB),
-// other states in every call: 106 -> 93 us (5.0 -> 5.8 TB/s); 128 of them 212 -> 188 us.  Smaller calls gain as much on
-// cold states (64 MiB 33 -> 27 us) but lose on states that are still cached (160 MiB in fp16 69 -> 92 us), and below the
-// limit a model of few layers may find them there.
-constexpr long long kAdvStreamBytes = 128ll << 20;
+// states come by between two steps, so what a call leaves in the 256 MiB memory-side cache is gone before it is read again
+// and only displaces.  The price is paid by a program whose states do stay there, one that advances few layers in turn.
+// One token per sequence at 128 heads x 64 x 128, us per call through the caches / past them:
+//                    132 MiB   192 MiB   256 MiB   320 MiB of states
+//   fp32   other    59 / 49   84 / 72  106 / 94  136 / 119     (other: each call advances other ones of 1 GiB of buffers)
+//          same     45 / 48   63 / 71   83 / 93  118 / 118     (same: the same buffers in every call)
+//   bf16   other    85 / 72  117 / 108 155 / 144 197 / 181
+//          same     66 / 73   90 / 107 142 / 144 192 / 181
+//   fp16   other    79 / 73  114 / 107 148 / 142 188 / 178
+//          same     58 / 73   80 / 106 129 / 142 187 / 177
+// In fp32 and bf16 the limit is where a second call's states no longer fit the cache beside the first's.  In fp16 the gain
+// is small and the price high, so there it lies where not even the same states stay cached.
+constexpr long long kAdvStreamBytes = 128ll << 20, kAdvStreamBytesF16 = 272ll << 20;
 constexpr float kAdvLog2e = 1.4426950408889634f;
 
 #define ADV_DPP(v, ctrl, row_mask)                                                                            \
@@ -321,7 +328,11 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
     a.P = args.P;
     a.N = args.N;
     a.G = args.G;
-    a.stream = (long long)plan->batch * a.H * a.P * a.N * (state_type == ADV_STATE_F32 ? 4 : 2) > kAdvStreamBytes;
+    long long advanced = busy - n_long;
+    for (int r = n_long; args.host_ptrs && r < busy; ++r)
+        advanced -= args.host_ptrs[plan->order[r]] == nullptr;
+    const long long bytes = advanced * a.H * a.P * a.N * (state_type == ADV_STATE_F32 ? 4 : 2);
+    a.stream = bytes > (state_type == ADV_STATE_F16 ? kAdvStreamBytesF16 : kAdvStreamBytes);
     const int n_seqs = n_long > 0 ? busy - n_long : plan->batch;
     return plan->shape.io_dtype == SSM_DT_F32 ? launch_io<float>(a, n_seqs, state_type, stream)
                                               : launch_io<bf16_t>(a, n_seqs, state_type, stream);

@@ -9,7 +9,9 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("state_dtype,tdt,batch", [("f32", torch.float32, 34), ("f16", torch.float16, 66),
-                                                   ("bf16", torch.bfloat16, 66)])
+                                                   ("bf16", torch.bfloat16, 66), ("f32", torch.float32, 33),
+                                                   ("f32", torch.float32, 65), ("f16", torch.float16, 137),
+                                                   ("f16", torch.float16, 138)])
 def test_large_batches_equal_small_ones(state_dtype, tdt, batch):
     import paper_2411_19379_amd as ssm
     print(f"decode of {batch} sequences in one call and in thirds, {state_dtype}", flush=True)
