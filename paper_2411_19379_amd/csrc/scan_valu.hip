@@ -173,6 +173,8 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ bool finite(float v) { return __builtin_fabsf(v) < __builtin_inff(); }
+
 struct F32Wave {          // private to one wave
     double ell[16];       // l_i
     float ei[16];         // e^{l_i}
@@ -187,8 +189,14 @@ template <int NB, int NC, int NW> struct F32Lds {
     F32Wave wv[NW];
 };
 
+// Waves per SIMD: what the registers of the common path leave room for (the paths for values that are not finite would
+// take a wave away).
+constexpr int f32_waves_per_simd(int nb, int nc)
+{
+    return nb == 8 ? 2 : nb * nc == 8 ? 3 : nb * nc == 4 ? 4 : 5;
+}
 template <int NB, int NC, int NW>
-__global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_f32_kernel(F32Args a)
+__global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_f32_kernel(F32Args a)
 {
     typedef float IO;
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -255,7 +263,7 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_f32_kernel(
             const SsmTile t = a.tiles[sq.tile_begin + k];
             tok0 = t.tok0, len = t.len, ckpt = t.ckpt_slot;
         }
-        // rows past the end of a partial tile re-read its last row: their weights are zero
+        // rows past the end of a partial tile re-read its last row
         const size_t row = (size_t)tok0 + (li < len ? li : len - 1);
         const float dtl = li < len ? IoTraits<IO>::load(dt + row * H + h) : 0.f;
         float Cf[4 * NB], Bf[4 * NB], Bt[4][NB], xv[NC][4];
@@ -285,6 +293,18 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_f32_kernel(
         const float4 wt4 = *reinterpret_cast<const float4 *>(&W.wt[4 * kq]);
         const float wt[4] = {wt4.x, wt4.y, wt4.z, wt4.w};
 
+        if (len < 16) {  // rows past the end add nothing: their weights are zero, but what was read may not be finite
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool in = 4 * kq + r < len;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    Bt[r][nb] = in ? Bt[r][nb] : 0.f;
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    xv[c][r] = in ? xv[c][r] : 0.f;
+            }
+        }
         f32x4 Sl[NC * NB];  // [slice][block]
 #pragma unroll
         for (int c = 0; c < NC * NB; ++c)
@@ -387,13 +407,13 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_f32_kernel(
             for (int r = 0; r < 4; ++r)
                 Y0 = mfma_f32(gm[r], xv[c][r], Y0);
             // a token whose x is not finite has reached every query of its channel, the earlier ones as 0 * inf: these
-            // take the products without such tokens
-            if (__any(!(__builtin_fabsf(Y0[0]) < __builtin_inff()))) {
+            // take the products without such tokens (between two such tokens of a tile an infinity becomes NaN)
+            if (__builtin_expect(__any(!finite(Y0[0])), 0)) {
                 int first = 16;
                 f32x4 Y2 = before;
 #pragma unroll
                 for (int r = 3; r >= 0; --r)
-                    first = !(__builtin_fabsf(xv[c][r]) < __builtin_inff()) ? 4 * kq + r : first;
+                    first = !finite(xv[c][r]) ? 4 * kq + r : first;
                 W.first_bad[lane] = first;
                 lds_wait();
 #pragma unroll
@@ -402,7 +422,7 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_f32_kernel(
                 lds_wait();
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    Y2 = mfma_f32(gm[r], __builtin_fabsf(xv[c][r]) < __builtin_inff() ? xv[c][r] : 0.f, Y2);
+                    Y2 = mfma_f32(gm[r], finite(xv[c][r]) ? xv[c][r] : 0.f, Y2);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     Y0[r] = 4 * kq + r < first ? Y2[r] : Y0[r];
@@ -564,9 +584,15 @@ template <int NB, int NC, int NW> struct SplitLds {
     SplitWave wv[NW];
 };
 
-// Waves per SIMD that the registers are budgeted for: two, so that the workgroups of a launch share a compute unit.
+// Waves per SIMD: what the registers of the common path leave room for.  Without the bound the paths for values that are
+// not finite, which are all but never taken, would cost a wave (64 heads x 32 channels, d_state 16: 1.1 to 1.5 times the
+// time); with it they spill a few registers of their own.
+constexpr int split_waves_per_simd(int nb, int nc, int nw)
+{
+    return nb * nc <= 2 ? (nc == 2 && nw == 1 ? 3 : 4) : nb * nc == 4 && nc < 4 ? 3 : 2;
+}
 template <int NB, int NC, int NW>
-__global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kernel(F32Args a)
+__global__ __launch_bounds__(64 * NW, split_waves_per_simd(NB, NC, NW)) void ssm_scan_split_kernel(F32Args a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     SplitLds<NB, NC, NW> &L = *reinterpret_cast<SplitLds<NB, NC, NW> *>(lds_raw);
@@ -777,6 +803,43 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
                         Sl[c * NB + nb] = mfma_b16(bo[nb], wx[s], Sl[c * NB + nb]);
             }
         }
+        // A value that is not finite has no split, and times the zero of a part or of a row past the end it is NaN.  In B it
+        // has reached every channel, in x every state index of its channel; what it has reached is summed token by token.
+        {
+            float z = 0.f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int nb = 0; nb < (c == 0 ? NB : 1); ++nb)
+#pragma unroll
+                    for (int rr = 0; rr < (c == 0 ? 4 : 1); ++rr)
+                        z = __builtin_fmaf(Sl[c * NB + nb][rr], 0.f, z);
+            if (__builtin_expect(__any(z != 0.f), 0)) {
+                const __amdgpu_buffer_rsrc_t xs = split_rsrc(x + (size_t)tok0 * hp_b, (uint32_t)(len - 1) * hp_b + 32 * NC);
+                const __amdgpu_buffer_rsrc_t bs = split_rsrc(Bg + (size_t)tok0 * gn_b, (uint32_t)(len - 1) * gn_b + 2 * N);
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma nounroll
+                        for (int j = 0; j < len; ++j) {
+                            uint32_t xw, bw;
+                            load_words<2>(xs, 2 * NC * li + 2 * c, (uint32_t)j * hp_b, &xw);
+                            const float v = W.wt[j] * __uint_as_float(xw << 16);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                load_words<2>(bs, 2 * kRun * kq + 2 * (NB * r + nb), (uint32_t)j * gn_b, &bw);
+                                sum[r] += v * __uint_as_float(bw << 16);
+                            }
+                        }
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            Sl[c * NB + nb][r] = finite(Sl[c * NB + nb][r]) ? Sl[c * NB + nb][r] : sum[r];
+                    }
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
         // ---- masked, decayed scores as split operands: queries 0..15 have keys 0..15 (two parts share a product),
         // queries 16..31 all of them
@@ -882,6 +945,7 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
         const float4 ei0 = *reinterpret_cast<const float4 *>(&W.ei[4 * kq]);
         const float4 ei1 = *reinterpret_cast<const float4 *>(&W.ei[16 + 4 * kq]);
         const f32x4 ei[2] = {{ei0.x, ei0.y, ei0.z, ei0.w}, {ei1.x, ei1.y, ei1.z, ei1.w}};
+        float rows_z = 0.f;                 // NaN if an output of the first channel is not finite
         float Yf[2][8];                     // the present channel and the one before it
         uint32_t out[(NC + 1) / 2][8];
 #pragma unroll
@@ -918,9 +982,15 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
                 Y[e >> 2][e & 3] *= ei[e >> 2][e & 3];
             const f32x4 in0 = Y[0], in1 = Y[1];
             intra(make_uint4(xpair(c, 0), xpair(c, 1), xpair(c, 2), xpair(c, 3)), Y[0], Y[1]);
-            // a token whose x is not finite has reached every query of its channel, the earlier ones as 0 * inf
-            const bool bad = !(__builtin_fabsf(Y[0][0]) < __builtin_inff()) || !(__builtin_fabsf(Y[1][0]) < __builtin_inff());
-            if (__any(bad)) {
+            // an x or a state that is not finite has reached every query of its channel (the queries before such a token as
+            // 0 * inf), a B or C that is not every channel of its queries
+            float z = c == 0 ? 0.f : rows_z;
+#pragma unroll
+            for (int e = 0; e < 8; e += c == 0 ? 1 : 4)
+                z = __builtin_fmaf(Y[e >> 2][e & 3], 0.f, z);
+            if (c == 0)
+                rows_z = z;
+            if (__builtin_expect(__any(z != 0.f), 0)) {
                 int first = kUnit;  // the channel's first such token
                 uint32_t u[8];
 #pragma unroll
@@ -942,8 +1012,41 @@ __global__ __launch_bounds__(64 * NW, NW <= 8 ? 2 : 4) void ssm_scan_split_kerne
                 intra(make_uint4(upper2(u[0], u[1]), upper2(u[2], u[3]), upper2(u[4], u[5]), upper2(u[6], u[7])), c0, c1);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    Y[0][r] = r < first ? c0[r] : Y[0][r];
-                    Y[1][r] = 16 + r < first ? c1[r] : Y[1][r];
+                    Y[0][r] = r < first && finite(c0[r]) ? c0[r] : Y[0][r];
+                    Y[1][r] = 16 + r < first && finite(c1[r]) ? c1[r] : Y[1][r];
+                }
+                // what is still not finite is infinite or NaN as the sum of its terms is: of a query 16 ih + 4 kq + r the lanes
+                // 16 q + li hold the state and the tokens, the lanes 16 q + 4 kq + r the scores (their first parts will do)
+                const __amdgpu_buffer_rsrc_t cs = split_rsrc(Cg + (size_t)tok0 * gn_b, (uint32_t)(len - 1) * gn_b + 2 * N);
+#pragma nounroll
+                for (int e = 0; e < 8; ++e) {
+                    const int i = 16 * (e >> 2) + 4 * kq + (e & 3);
+                    float inter = 0.f, sum = 0.f;
+#pragma nounroll
+                    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                        for (int f = 0; f < kRun; ++f) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            const float4 &v = sp[c][f / 4];
+                            const float s = f % 4 == 0 ? v.x : f % 4 == 1 ? v.y : f % 4 == 2 ? v.z : v.w;
+                            uint32_t cw;
+                            load_words<2>(cs, (i < len ? i : len - 1) * gn_b + 2 * f, 2 * kRun * q, &cw);
+                            inter += __uint_as_float(cw << 16) * __shfl(s, 16 * q + li, 64);
+                        }
+#pragma unroll
+                        for (int k2 = 0; k2 < 8; ++k2) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            const uint32_t hi = e >= 4 ? (k2 < 2 ? g_hi[0].x : k2 < 4 ? g_hi[0].y : k2 < 6 ? g_hi[0].z : g_hi[0].w)
+                                                       : (k2 < 2 ? g_hm.x : k2 < 4 ? g_hm.y : 0u);
+                            const float g = __shfl(__uint_as_float((k2 & 1) ? hi & 0xffff0000u : hi << 16), 16 * q + 4 * kq + (e & 3), 64);
+                            const float xv = __shfl(xval(c, k2), 16 * q + li, 64);
+                            sum += 16 * (k2 >> 2) + 4 * q + (k2 & 3) <= i ? g * xv : 0.f;
+                        }
+                    }
+                    const float v = W.ei[i] * inter + sum;
+#pragma unroll
+                    for (int k2 = 0; k2 < 8; ++k2)
+                        Y[k2 >> 2][k2 & 3] = k2 == e && !finite(Y[k2 >> 2][k2 & 3]) ? v : Y[k2 >> 2][k2 & 3];
                 }
             }
 #pragma unroll
