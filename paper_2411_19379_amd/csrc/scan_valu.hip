@@ -76,7 +76,8 @@ struct F32Args {
     bool roll;                      // roll-forward in place
     const SsmTile *tiles;
     const SsmSeq *seqs;
-    const int32_t *order;           // the launch's k-th sequence is order[k]; null: k
+    const int32_t *order;           // the launch's k-th sequence is order[first + k]; null: first + k
+    int first;
     int H, P, G, slices, state_dtype;
     int units_per_tile = 1;         // split-operand kernel: units of 32 tokens per tile of the plan
 };
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
     const int H = a.H, P = a.P, G = a.G, st = a.state_dtype;
     const int slice = blockIdx.x % a.slices;
     const int h = (blockIdx.x / a.slices) % H;
-    const int rank = blockIdx.x / (a.slices * H), seq = a.order ? a.order[rank] : rank;
+    const int rank = a.first + (int)(blockIdx.x / (unsigned)(a.slices * H)), seq = a.order ? a.order[rank] : rank;
     const int g = h / (H / G);
     const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -603,7 +604,7 @@ __global__ __launch_bounds__(64 * NW, split_waves_per_simd(NB, NC, NW)) void ssm
     const int H = a.H, P = a.P, G = a.G, st = a.state_dtype;
     const int slice = blockIdx.x % a.slices;
     const int h = (blockIdx.x / a.slices) % H;
-    const int rank = blockIdx.x / (a.slices * H), seq = a.order ? a.order[rank] : rank;
+    const int rank = a.first + (int)(blockIdx.x / (unsigned)(a.slices * H)), seq = a.order ? a.order[rank] : rank;
     const int g = h / (H / G);
     const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1077,9 +1078,10 @@ __global__ __launch_bounds__(64 * NW, split_waves_per_simd(NB, NC, NW)) void ssm
     }
 }
 
-// What a launch covers: `seqs` sequences of `units` units (tiles of 16 tokens, units of 32) in all, `longest` in one.
+// What a launch covers: `seqs` sequences, `busy` of them not empty, of `units` units (tiles of 16 tokens, units of 32) in
+// all, `longest` in one.
 struct F32Batch {
-    int seqs, longest;
+    int seqs, busy, longest;
     long long units;
 };
 
@@ -1094,7 +1096,7 @@ struct F32Batch {
 // channels, d_state 128, 140 -> 74 us with fp16 states, 288 -> 107 us in fp32.
 inline int scan_waves(const F32Batch &b, long long streams_per_seq, int resident, int least, int most)
 {
-    const long long wgs = b.seqs * streams_per_seq, per_wave = (b.units * streams_per_seq + resident - 1) / resident;
+    const long long wgs = b.busy * streams_per_seq, per_wave = (b.units * streams_per_seq + resident - 1) / resident;
     int nw = wgs <= 768 ? 4 : least;
     while (nw < most && nw < b.longest) {
         const bool in_turn = nw >= 4 && 2ll * nw * wgs > resident;  // workgroups of twice the waves would have to queue
@@ -1109,11 +1111,29 @@ inline int scan_waves(const F32Batch &b, long long streams_per_seq, int resident
     return nw;
 }
 
-template <int NB, int NC, int NW> hipError_t launch_f32_nw(const F32Args &a, const F32Batch &b, hipStream_t stream)
+// A launch has fewer than 2^32 threads: a batch that needs more (tens of thousands of sequences) takes several.
+#ifndef SSM_F32_MOST_THREADS
+#define SSM_F32_MOST_THREADS (1ll << 31)
+#endif
+template <typename Launch> hipError_t in_launches(F32Args a, const F32Batch &b, int threads, Launch launch)
 {
-    hipLaunchKernelGGL((ssm_scan_f32_kernel<NB, NC, NW>), dim3((unsigned)b.seqs * (unsigned)a.H * (unsigned)a.slices),
-                       dim3(64 * NW), sizeof(F32Lds<NB, NC, NW>), stream, a);
-    return hipGetLastError();
+    const long long per_seq = (long long)a.H * a.slices;
+    const long long most = SSM_F32_MOST_THREADS / (per_seq * threads);
+    const int step = most < 1 ? 1 : most < b.seqs ? (int)most : b.seqs;
+    for (; a.first < b.seqs; a.first += step) {
+        const int n = b.seqs - a.first < step ? b.seqs - a.first : step;
+        launch(a, dim3((unsigned)(n * per_seq)));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
+}
+template <int NB, int NC, int NW> hipError_t launch_f32_nw(const F32Args &args, const F32Batch &b, hipStream_t stream)
+{
+    return in_launches(args, b, 64 * NW, [&](const F32Args &a, dim3 grid) {
+        hipLaunchKernelGGL((ssm_scan_f32_kernel<NB, NC, NW>), grid, dim3(64 * NW), sizeof(F32Lds<NB, NC, NW>), stream, a);
+    });
 }
 template <int NB, int NC> hipError_t launch_f32(const F32Args &a, const F32Batch &b, hipStream_t stream)
 {
@@ -1127,11 +1147,11 @@ template <int NB, int NC> hipError_t launch_f32(const F32Args &a, const F32Batch
     }
 }
 
-template <int NB, int NC, int NW> hipError_t launch_split_nw(const F32Args &a, const F32Batch &b, hipStream_t stream)
+template <int NB, int NC, int NW> hipError_t launch_split_nw(const F32Args &args, const F32Batch &b, hipStream_t stream)
 {
-    hipLaunchKernelGGL((ssm_scan_split_kernel<NB, NC, NW>), dim3((unsigned)b.seqs * (unsigned)a.H * (unsigned)a.slices),
-                       dim3(64 * NW), sizeof(SplitLds<NB, NC, NW>), stream, a);
-    return hipGetLastError();
+    return in_launches(args, b, 64 * NW, [&](const F32Args &a, dim3 grid) {
+        hipLaunchKernelGGL((ssm_scan_split_kernel<NB, NC, NW>), grid, dim3(64 * NW), sizeof(SplitLds<NB, NC, NW>), stream, a);
+    });
 }
 template <int NB, int NC> hipError_t launch_split(const F32Args &a, const F32Batch &b, hipStream_t stream)
 {
@@ -1329,6 +1349,7 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     a.tiles = args.tiles;
     a.seqs = args.seqs;
     a.order = n_seqs < plan->batch ? args.order : nullptr;
+    a.first = 0;
     a.H = args.H, a.P = args.P, a.G = args.G;
     a.state_dtype = args.state_dtype;
     // Slices of 16 channels per workgroup: more of them share the scores (4 nb of a tile's products in fp32), fewer leave
@@ -1352,7 +1373,7 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     }
     // the scan's units are the plan's tiles; the roll-forward cuts the tokens itself
     const SsmSeq &lq = plan->seqs[plan->order[0]];
-    F32Batch batch = {n_seqs, lq.tile_end - lq.tile_begin, (long long)plan->tiles.size()};
+    F32Batch batch = {n_seqs, busy < n_seqs ? busy : n_seqs, lq.tile_end - lq.tile_begin, (long long)plan->tiles.size()};
     if (roll) {
         const int unit = split ? kUnit : kValuTileTokens;
         batch.longest = (ssm_plan_tokens(plan, plan->order[0]) + unit - 1) / unit;

@@ -68,7 +68,7 @@ def _build(tmp_path_factory, name, mfma_source, extra_flags=(), extra_sources=()
     _convert(mfma_source, os.path.join(d, "scan_mfma.cpp"))
     _convert(os.path.join(CSRC, "scan_valu.hip"), os.path.join(d, "scan_valu.cpp"))
     flags = ["-std=c++17", "-O2", "-fno-strict-aliasing", "-ffp-contract=off", "-Wno-psabi", "-Wno-unused-value",
-             "-DSSM_F32_WAVES=emu::env_int(\"EMU_F32_WAVES\")",
+             "-DSSM_F32_WAVES=emu::env_int(\"EMU_F32_WAVES\")", "-DSSM_F32_MOST_THREADS=2048ll",
              "-I", EMU, "-I", os.path.join(ROOT, "include"), "-I", CSRC, *extra_flags]
     _convert(os.path.join(CSRC, "state_advance.hip"), os.path.join(d, "state_advance.cpp"))
     srcs = [os.path.join(d, "scan_mfma.cpp"), os.path.join(d, "scan_valu.cpp"), os.path.join(d, "state_advance.cpp"),

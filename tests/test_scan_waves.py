@@ -70,3 +70,21 @@ def test_gpu_many_short_sequences(dims, lens, io):
     few.ckpt_pos = wl.ckpt_pos[:n]
     y1, st1, _ = gpu_run(few, wl.init_state[:n])
     assert torch.equal(y1, y[:T]) and torch.equal(st1, st[:st1.shape[0]])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_gpu_more_threads_than_a_launch_takes(io):
+    """One long sequence among 65535 empty ones at 128 heads: with its waves for every sequence, 2^32 threads and more."""
+    print(f"65536 sequences, {io}", flush=True)
+    lens = [0] * 65536
+    lens[40000] = 2100
+    wl = _workload((128, 16, 16, 1, 64), lens[40000:40001], "cuda:0", io=io)
+    wl.ckpt_pos = [[2100]]
+    y1, st1, _ = gpu_run(wl, wl.init_state[:1])
+    wl.seqlens, wl.cu_seqlens = lens, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    wl.ckpt_pos = [[n] if n else [] for n in lens]
+    init = [None] * len(lens)
+    init[40000] = wl.init_state[0]
+    y, st, info = gpu_run(wl, init)
+    assert info.path == 0 and torch.equal(y, y1) and torch.equal(st, st1)
