@@ -191,7 +191,7 @@ def _ptr_array(plan: int, ptrs):
     batch = ssm_plan_info(plan).batch
     if len(ptrs) != batch:
         raise ValueError(f"expected one state pointer per sequence ({batch}), got {len(ptrs)}")
-    return (ctypes.c_void_p * max(batch, 1))(*ptrs)
+    return (ctypes.c_void_p * max(batch, 1))(*[p or None for p in ptrs])  # null in any form
 
 
 def ssm_prefill(plan: int, x: int, dt: int, A: int, B: int, C: int, D: int,
