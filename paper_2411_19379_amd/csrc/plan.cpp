@@ -189,6 +189,23 @@ int32_t ssm_plan_longer_than(const ssm_plan *plan, int32_t tokens)
                      plan->order.begin());
 }
 
+// More slices of a workgroup share the scores (4 nb of a tile's products in fp32), fewer leave more workgroups: products
+// per tile times rounds of 256 workgroups, the smaller the better.  At most what the registers hold: with d_state 128 two
+// split slices spill (the roll-forward of three sequences of 17 to 256 tokens 47 us instead of 37).
+extern "C" int ssm_f32_slices(int split, int d_state, int headdim, int64_t streams)
+{
+    const int nb = d_state / 16, all = headdim / 16, most = nb <= 2 ? 4 : split && nb == 8 ? 1 : 2;
+    int nc = 1;
+    int64_t best = 0;
+    for (int c = 1; c <= most && all % c == 0; c *= 2) {
+        const int64_t rounds = (streams * (all / c) + 255) / 256;
+        const int64_t cost = rounds * (split ? c * (6 * nb + 8) + 2 * nb + 8 : c * (8 * nb + 4) + 4 * nb);
+        if (c == 1 || cost <= best)
+            nc = c, best = cost;
+    }
+    return nc;
+}
+
 static void ssm_plan_order_sequences(ssm_plan *plan);
 
 void ssm_plan_build_stretches(ssm_plan *plan, int64_t per_round, int32_t min_tiles)

@@ -130,6 +130,10 @@ inline int32_t ssm_plan_tokens(const ssm_plan *plan, int32_t i)
 // How many sequences have more than `tokens` tokens: they are the first ones of plan->order.
 int32_t ssm_plan_longer_than(const ssm_plan *plan, int32_t tokens);
 
+// Slices of 16 channels per workgroup of the fp32 matrix-core scans (1, 2 or 4) for a launch over `streams` pairs of a
+// sequence and a head; split: bf16 storage.
+extern "C" int ssm_f32_slices(int split, int d_state, int headdim, int64_t streams);
+
 // Where the parts of the matrix-core scan's workspace start (bytes from its base), and its size.
 struct SsmMfmaWorkspace {
     size_t images = 0;      // per (tile, group): kMfmaTileGroupBytes

@@ -1352,25 +1352,16 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     a.first = 0;
     a.H = args.H, a.P = args.P, a.G = args.G;
     a.state_dtype = args.state_dtype;
-    // Slices of 16 channels per workgroup: more of them share the scores (4 nb of a tile's products in fp32), fewer leave
-    // more workgroups.  Products per tile times rounds of 256 workgroups, the smaller the better.
     const bool split = plan->shape.io_dtype == SSM_DT_BF16;
-    const int nb = args.N / 16, all = args.P / 16;
+    const int nb = args.N / 16;
     const int busy = ssm_plan_longer_than(plan, 0);
     const long long streams = (long long)(busy < n_seqs ? busy : n_seqs) * args.H;
     a.units_per_tile = (plan->tile_tokens + kUnit - 1) / kUnit;
-    int nc = 1;
-    long long best = 0;
-    // What the registers hold: with d_state 128 two split slices spill (the roll-forward 47 us instead of 37).
-    const int most = nb <= 2 ? 4 : split && nb == 8 ? 1 : 2;
-    for (int c = 1; c <= most; c *= 2) {
-        if (all % c != 0)
-            break;
-        const long long rounds = (streams * (all / c) + 255) / 256;
-        const long long cost = rounds * (split ? c * (6 * nb + 8) + 2 * nb + 8 : c * (8 * nb + 4) + 4 * nb);
-        if (c == 1 || cost <= best)
-            nc = c, best = cost;
-    }
+    int nc = ssm_f32_slices(split, args.N, args.P, streams);
+#ifdef SSM_F32_SLICES  // the emulator's: so many for every launch, 0: the rule
+    if (SSM_F32_SLICES)
+        nc = SSM_F32_SLICES;
+#endif
     // the scan's units are the plan's tiles; the roll-forward cuts the tokens itself
     const SsmSeq &lq = plan->seqs[plan->order[0]];
     F32Batch batch = {n_seqs, busy < n_seqs ? busy : n_seqs, lq.tile_end - lq.tile_begin, (long long)plan->tiles.size()};

@@ -61,7 +61,17 @@ def _convert(src: str, dst: str) -> None:
     open(dst, "w").write(text)
 
 
+_objects = {}
+_built = {}  # modules that import the fixtures below share their builds
+
+
 def _build(tmp_path_factory, name, mfma_source, extra_flags=(), extra_sources=()):
+    if name not in _built:
+        _built[name] = _build_once(tmp_path_factory, name, mfma_source, extra_flags, extra_sources)
+    return _built[name]
+
+
+def _build_once(tmp_path_factory, name, mfma_source, extra_flags=(), extra_sources=()):
     if not os.path.exists(CLANG):
         pytest.skip("no clang++ with bf16 vector support found")
     d = str(tmp_path_factory.mktemp(name))
@@ -69,6 +79,7 @@ def _build(tmp_path_factory, name, mfma_source, extra_flags=(), extra_sources=()
     _convert(os.path.join(CSRC, "scan_valu.hip"), os.path.join(d, "scan_valu.cpp"))
     flags = ["-std=c++17", "-O2", "-fno-strict-aliasing", "-ffp-contract=off", "-Wno-psabi", "-Wno-unused-value",
              "-DSSM_F32_WAVES=emu::env_int(\"EMU_F32_WAVES\")", "-DSSM_F32_MOST_THREADS=2048ll",
+             "-DSSM_F32_SLICES=emu::env_int(\"EMU_F32_SLICES\")",
              "-I", EMU, "-I", os.path.join(ROOT, "include"), "-I", CSRC, *extra_flags]
     _convert(os.path.join(CSRC, "state_advance.hip"), os.path.join(d, "state_advance.cpp"))
     srcs = [os.path.join(d, "scan_mfma.cpp"), os.path.join(d, "scan_valu.cpp"), os.path.join(d, "state_advance.cpp"),
@@ -79,8 +90,14 @@ def _build(tmp_path_factory, name, mfma_source, extra_flags=(), extra_sources=()
     objs = []
     procs = []
     for s in srcs:
-        o = os.path.join(d, os.path.basename(s) + ".o")
+        # the extra flags are the matrix-core scan's: whatever else is compiled already is shared
+        shared = None if s.endswith("scan_mfma.cpp") or extra_sources else os.path.basename(s)
+        o = _objects.get(shared) or os.path.join(d, os.path.basename(s) + ".o")
         objs.append(o)
+        if shared in _objects:
+            continue
+        if shared:
+            _objects[shared] = o
         procs.append(subprocess.Popen([CLANG, *flags, "-c", s, "-o", o], stderr=subprocess.PIPE, text=True))
     for p in procs:
         _, err = p.communicate()
@@ -199,7 +216,10 @@ CASES = {
     "tiny": ((2, 64, 128, 1, 64), 2, dict(batch=2, len_range=(1, 3))),
     # one 32-channel slice per head, several groups with several heads each, 32-token tiles
     "p32_groups": ((4, 32, 128, 2, 32), 2, dict(batch=2, len_range=(20, 120))),
-    # seven heads per group: the four workgroups per (tile, group) of the kernel in front of the scan share them 1, 2, 2, 2
+    # 72 (tile, group) pairs: four workgroups each of the kernel in front of the scan (eight below 64 pairs), of which one
+    # shares the three heads of a group with none
+    "pairs72": ((24, 32, 128, 8, 16), 2, dict(batch=2, len_range=(66, 72))),
+    # seven heads per group: the four workgroups per (tile, group) that transpose dt in front of the scan share them 1, 2, 2, 2
     "heads7": ((7, 32, 128, 1, 64), 2, dict(batch=2, len_range=(40, 150))),
     # one head, 21 tiles: cut in two, the second stretch is longer than the 8 tiles that the small build of the
     # second kernel gives workgroups of their own, so its coarse groups get the rest

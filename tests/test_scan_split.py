@@ -1,12 +1,15 @@
-"""The split-operand scan (bf16 storage, fp32 results) at the edges of its dispatch: every block count of d_state, one to
-four 16-channel slices, units of 32 tokens with every kind of remainder, tiles of 16 and 32 tokens, and the same kernel as
+"""The split-operand scan (bf16 storage, fp32 results) at the edges of its dispatch: every block count of d_state, heads of
+one to eight 16-channel slices, units of 32 tokens with every kind of remainder, tiles of 16 and 32 tokens, and the same kernel as
 the roll-forward; on the CPU emulator (wave orders, bounds, unwritten outputs) and on the GPU.  Every product is exact and
 added up in fp32 as in the fp32 kernel, so the bounds are the fp32 ones: 1e-5, and 2^-8 of the value where y is rounded to
 bf16.  Then what a token whose x is not finite may reach: its own channel, from its own position on."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
+from paper_2411_19379_amd.binding import load_library
 from helpers import gpu_run, oracle_on_heads, rel_err
 from test_kernel_emulation import _emulate, _oracle, emu_binary  # noqa: F401  (the fixture that builds the emulator)
 from workloads import LayerShape, make_workload
@@ -104,7 +107,10 @@ GPU_CASES.update({
     "n64_two_slices_shared": ((150, 64, 64, 1, 256), [33, 180]),
     "n64_eight_waves": ((2, 64, 64, 1, 256), [300]),
     "odd_slices": ((5, 80, 32, 5, 32), [95, 32]),
+    "n16_packed": ((32, 64, 16, 1, 256), [300, 64, 17, 128, 33, 250, 90, 512]),
+    "n16_two_slices": ((64, 32, 16, 1, 256), [100, 33, 40, 70]),
 })
+GPU_SLICES = {"n16_packed": 4, "n16_two_slices": 2, "n32_four_slices": 4, "n64_two_slices_shared": 2, "n16_many": 2}
 
 
 @pytest.mark.gpu
@@ -115,6 +121,9 @@ def test_gpu_scan(case):
     init = [None if s is None else s.cpu().numpy() for s in wl.init_state]
     y, st, info = gpu_run(wl, wl.init_state)
     assert info.path == 0
+    if case in GPU_SLICES:  # several slices per workgroup
+        (H, P, N, _, _), lens = GPU_CASES[case]
+        assert load_library().ssm_f32_slices(1, N, P, ctypes.c_int64(len(lens) * H)) == GPU_SLICES[case]
     y_ref, st_ref = oracle_on_heads(wl, None, init)
     assert max(rel_err(y.float().cpu().numpy(), y_ref)) <= Y_TOL
     for k in range(st_ref.shape[0]):

@@ -1,7 +1,8 @@
 """The fp32 and split-operand scans with every number of waves per workgroup that their launch rule can pick (few where the
-launch fills the GPU with short sequences; one wave alone keeps the state in its registers), and the roll-forward through
-the same kernels: on the emulator with the number fixed, on the GPU with batches that the rule sends there.  Against the
-oracle with the bounds of the other tests of these kernels, and bit-identical whatever the number of waves."""
+launch fills the GPU with short sequences; one wave alone keeps the state in its registers) and every number of 16-channel
+slices, and the roll-forward through the same kernels: on the emulator with both numbers fixed, on the GPU with batches that
+the rules send there.  Against the oracle with the bounds of the other tests of these kernels, and bit-identical whatever
+the numbers."""
 import numpy as np
 import pytest
 import torch
@@ -15,17 +16,24 @@ Y_TOL = {"bf16": 2.0 ** -8 + 1e-5, "f32": 1e-5}
 CASES = {
     "n16": ((2, 64, 16, 1, 64), [70, 1, 0, 33]),
     "n32": ((2, 32, 32, 2, 16), [17, 40]),
+    "n32_wide": ((1, 64, 32, 1, 64), [33, 3]),
     "n64": ((1, 48, 64, 1, 64), [65, 5]),
+    "n64_wide": ((1, 64, 64, 1, 64), [17, 35]),
+    "n128_wide": ((1, 32, 128, 1, 64), [19]),
     "n128": ((1, 48, 128, 1, 64), [20, 49]),  # headdim 48: bf16 storage takes the split kernel at d_state 128 too
 }
 
 
-@pytest.mark.parametrize("waves", [1, 2])
-@pytest.mark.parametrize("advance", [False, True])
+@pytest.mark.parametrize("waves,slices,advance", [(1, 0, False), (2, 0, False), (0, 2, False), (1, 2, False), (8, 4, False),
+                                                  (1, 4, False), (1, 0, True), (2, 2, True)])
 @pytest.mark.parametrize("io", ["bf16", "f32"])
 @pytest.mark.parametrize("case", sorted(CASES))
-def test_emulated_waves(emu_binary, tmp_path, monkeypatch, case, io, advance, waves):  # noqa: F811
+def test_emulated_waves(emu_binary, tmp_path, monkeypatch, case, io, advance, waves, slices):  # noqa: F811
     dims, lens = CASES[case]
+    if slices and (dims[1] // 16 % slices or slices > (4 if dims[2] <= 32 else 1 if (io, dims[2]) == ("bf16", 128) else 2)):
+        pytest.skip("no such kernel")
+    if io == "bf16" and dims[1:3] == (32, 128) and not advance:
+        pytest.skip("not these kernels' shape")
     wl = _workload(dims, lens, "cpu", io=io)
     if advance:
         wl.ckpt_pos = [[n] if n else [] for n in lens]
@@ -35,6 +43,7 @@ def test_emulated_waves(emu_binary, tmp_path, monkeypatch, case, io, advance, wa
     sub = tmp_path / "waves"
     sub.mkdir()
     monkeypatch.setenv("EMU_F32_WAVES", str(waves))
+    monkeypatch.setenv("EMU_F32_SLICES", str(slices))
     for order, align in ((0, "end"), (1, "start")):
         y, st, raw = _emulate(emu_binary, wl, init, sub, order, align, advance=advance)
         assert np.array_equal(raw, want)
