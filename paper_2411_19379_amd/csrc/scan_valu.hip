@@ -2,8 +2,8 @@
 // the fp32 mode, of the shapes the fp16 / bf16 matrix-core kernel does not cover, and of the roll-forward over more
 // than a few tokens.
 //
-// Both work tile by tile; per tile of q <= 16 tokens starting after token s, with l_i = A * sum_{k<=i} dt_k inside the
-// tile:
+// All work tile by tile; per tile of q tokens (at most 16, or 32 for the split operands) starting after token s, with
+// l_i = A * sum_{k<=i} dt_k inside the tile:
 //
 //   y_i  = e^{l_i} (S_s C_i) + sum_{j<=i} (C_i.B_j) e^{l_i-l_j} dt_j x_j + D x_i
 //   S_e  = e^{l_q} S_s + sum_j e^{l_q-l_j} dt_j x_j B_j^T
@@ -79,10 +79,9 @@ struct F32Args {
     const int32_t *order;           // the launch's k-th sequence is order[first + k]; null: first + k
     int first;
     int H, P, G, slices, state_dtype;
-    int units_per_tile = 1;         // split-operand kernel: units of 32 tokens per tile of the plan
 };
 
-// n values (a multiple of 4, or 1 or 2) of the storage type as floats; p is aligned to the run's size, at most 16 bytes
+// NV values (a multiple of 4, or 1 or 2); p is aligned to the run's size, at most 16 bytes
 template <int NV> __device__ __forceinline__ void load_run(const float *p, float *v)
 {
     if (NV == 1) {
@@ -98,31 +97,6 @@ template <int NV> __device__ __forceinline__ void load_run(const float *p, float
         }
     }
 }
-template <int NV> __device__ __forceinline__ void load_run(const bf16_t *p, float *v)
-{
-    if (NV == 1) {
-        v[0] = bf16_to_f32(*p);
-    } else if (NV == 2) {
-        const uint32_t u = *reinterpret_cast<const uint32_t *>(p);
-        v[0] = __uint_as_float(u << 16), v[1] = __uint_as_float(u & 0xffff0000u);
-    } else if (NV == 4) {
-        const uint2 u = *reinterpret_cast<const uint2 *>(p);
-        v[0] = __uint_as_float(u.x << 16), v[1] = __uint_as_float(u.x & 0xffff0000u);
-        v[2] = __uint_as_float(u.y << 16), v[3] = __uint_as_float(u.y & 0xffff0000u);
-    } else {
-#pragma unroll
-        for (int e = 0; e < NV; e += 8) {
-            const uint4 u = *reinterpret_cast<const uint4 *>(p + e);
-            const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                v[e + 2 * k] = __uint_as_float(w[k] << 16);
-                v[e + 2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
-            }
-        }
-    }
-}
-
 // Four neighbouring elements of a cached state (index a multiple of four).
 typedef __attribute__((ext_vector_type(4))) _Float16 st_f16x4;
 __device__ __forceinline__ float4 state_load4(const void *base, size_t idx, int st)
@@ -199,7 +173,6 @@ constexpr int f32_waves_per_simd(int nb, int nc)
 template <int NB, int NC, int NW>
 __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_f32_kernel(F32Args a)
 {
-    typedef float IO;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     F32Lds<NB, NC, NW> &L = *reinterpret_cast<F32Lds<NB, NC, NW> *>(lds_raw);
     constexpr int N = 16 * NB;
@@ -224,11 +197,9 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
         n_tok = last.tok0 + last.len - tok_begin;
         n_tiles = (n_tok + 15) / 16;
     }
-    const IO *x = static_cast<const IO *>(a.x);
-    const IO *dt = static_cast<const IO *>(a.dt);
-    const IO *Bg = static_cast<const IO *>(a.B) + (size_t)g * N;
-    const IO *Cg = static_cast<const IO *>(a.C) + (size_t)g * N;
-    IO *y = static_cast<IO *>(a.y);
+    const float *x = static_cast<const float *>(a.x), *dt = static_cast<const float *>(a.dt);
+    const float *Bg = static_cast<const float *>(a.B) + (size_t)g * N, *Cg = static_cast<const float *>(a.C) + (size_t)g * N;
+    float *y = static_cast<float *>(a.y);
     const float Ah = a.A[h], Dh = a.D[h];
     // channel li of slice c, state indices 4 NB kq .. 4 NB kq + 4 NB - 1
     const size_t state_row = ((size_t)h * P + 16 * NC * slice + li) * N + 4 * NB * kq;
@@ -266,7 +237,7 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
         }
         // rows past the end of a partial tile re-read its last row
         const size_t row = (size_t)tok0 + (li < len ? li : len - 1);
-        const float dtl = li < len ? IoTraits<IO>::load(dt + row * H + h) : 0.f;
+        const float dtl = li < len ? dt[row * H + h] : 0.f;
         float Cf[4 * NB], Bf[4 * NB], Bt[4][NB], xv[NC][4];
         load_run<4 * NB>(Bg + row * GN + 4 * NB * kq, Bf);
         load_run<4 * NB>(Cg + row * GN + 4 * NB * kq, Cf);
@@ -276,7 +247,7 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
             load_run<NB>(Bg + tok * GN + NB * li, Bt[r]);
 #pragma unroll
             for (int c = 0; c < NC; ++c)
-                xv[c][r] = IoTraits<IO>::load(x + tok * HP + xcol + 16 * c);
+                xv[c][r] = x[tok * HP + xcol + 16 * c];
         }
         const double ell = row_inclusive_sum((double)dtl * (double)Ah);  // padded tokens add nothing
         if (lane < 16) {
@@ -431,8 +402,7 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (4 * kq + r < len)
-                    IoTraits<IO>::store(y + ((size_t)tok0 + 4 * kq + r) * HP + xcol + 16 * c,
-                                        __builtin_fmaf(Dh, xv[c][r], Y0[r]));
+                    y[((size_t)tok0 + 4 * kq + r) * HP + xcol + 16 * c] = __builtin_fmaf(Dh, xv[c][r], Y0[r]);
         }
         keep_state();
     }
@@ -446,8 +416,8 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
 // 64 bits it is no further off than the fp32 instruction was.
 //
 // One workgroup per (sequence, head, NC slices of 16 channels); its waves take units of 32 tokens round-robin and each
-// computes all of its unit, the state handed from wave to wave through LDS as in the fp32 kernel above.  A unit is a
-// whole tile of the plan, or half of a 64-token one; the roll-forward cuts the sequence's tokens itself.
+// computes all of its unit, the state handed from wave to wave through LDS as in the fp32 kernel above.  A unit is a tile
+// of the plan; the roll-forward cuts the sequence's tokens itself.
 //
 // Layouts (kq = lane / 16, li = lane % 16; an operand holds row or column li, k = 8 kq + e; a result element r is row
 // 4 kq + r, column li).  Any order of the k index will do as long as both operands use the same one, so every operand is
@@ -609,12 +579,11 @@ __global__ __launch_bounds__(64 * NW, split_waves_per_simd(NB, NC, NW)) void ssm
     const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool roll = a.roll;
-    const int per_tile = roll ? 1 : a.units_per_tile;
     const SsmSeq sq = a.seqs[seq];
     const void *from = uniform_ptr(a.init.of(seq));
     if (sq.tile_end <= sq.tile_begin || (roll && !from))
         return;  // nothing to scan; the whole workgroup leaves
-    int tok_begin = 0, n_tok = 0, n_units = (sq.tile_end - sq.tile_begin) * per_tile;
+    int tok_begin = 0, n_tok = 0, n_units = sq.tile_end - sq.tile_begin;
     if (roll) {
         const SsmTile last = a.tiles[sq.tile_end - 1];
         tok_begin = a.tiles[sq.tile_begin].tok0;
@@ -688,22 +657,12 @@ __global__ __launch_bounds__(64 * NW, split_waves_per_simd(NB, NC, NW)) void ssm
             tok0 = tok_begin + kUnit * k;
             len = n_tok - kUnit * k < kUnit ? n_tok - kUnit * k : kUnit;
         } else {
-            const SsmTile t = a.tiles[sq.tile_begin + (per_tile == 2 ? k >> 1 : k)];
-            const int off = per_tile == 2 ? kUnit * (k & 1) : 0, left = t.len - off;
-            tok0 = t.tok0 + off;
-            len = left < kUnit ? left : kUnit;
-            ckpt = left <= kUnit ? t.ckpt_slot : -1;
+            const SsmTile t = a.tiles[sq.tile_begin + k];
+            tok0 = t.tok0, len = t.len, ckpt = t.ckpt_slot;
         }
         tok0 = __builtin_amdgcn_readfirstlane(tok0);
         len = __builtin_amdgcn_readfirstlane(len);
         ckpt = __builtin_amdgcn_readfirstlane(ckpt);
-        if (len <= 0) {  // the second half of a tile that has none: the state passes through
-            if constexpr (NW > 1) {
-                f32_wait_counter(&L.done, k);
-                f32_publish_counter(&L.done, k + 1, lane);
-            }
-            continue;
-        }
         // ---- the unit's operands as they come from device memory.  Rows past the end of a partial unit re-read its last
         // row: their weights are zero, and an x there that is not finite is treated like the last token's own.
         float dtl;
@@ -1356,7 +1315,6 @@ hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll
     const int nb = args.N / 16;
     const int busy = ssm_plan_longer_than(plan, 0);
     const long long streams = (long long)(busy < n_seqs ? busy : n_seqs) * args.H;
-    a.units_per_tile = (plan->tile_tokens + kUnit - 1) / kUnit;
     int nc = ssm_f32_slices(split, args.N, args.P, streams);
 #ifdef SSM_F32_SLICES  // the emulator's: so many for every launch, 0: the rule
     if (SSM_F32_SLICES)
