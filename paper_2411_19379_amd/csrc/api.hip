@@ -108,7 +108,7 @@ static int device_tables(const ssm_plan *plan, hipStream_t stream, ssm_plan::Dev
     e = upload_table(t.tiles, plan->tiles.data(), plan->tiles.size() * sizeof(SsmTile), stream);
     if (e == hipSuccess)
         e = upload_table(t.seqs, plan->seqs.data(), plan->seqs.size() * sizeof(SsmSeq), stream);
-    if (e == hipSuccess)
+    if (e == hipSuccess && state_advance_mixes(plan))
         e = upload_table(t.order, plan->order.data(), plan->order.size() * sizeof(int32_t), stream);
     if (e == hipSuccess)
         e = upload_table(t.scan_seqs, plan->scan_seqs.data(), plan->scan_seqs.size() * sizeof(SsmScanSeq), stream);

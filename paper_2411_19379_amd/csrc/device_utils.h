@@ -122,6 +122,7 @@ hipError_t launch_scan_mfma(const ssm_plan *plan, const ScanArgs &args, void *wo
 // (nullptr: none)
 hipEvent_t ssm_profile_event(int which);
 bool state_advance_supports(const ssm_shape_t &s);
+bool state_advance_mixes(const ssm_plan *plan);
 hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void *const *d_state_ptrs,
                                 hipStream_t stream);
 bool conv1d_supports(int channels, int K, int io_dtype);

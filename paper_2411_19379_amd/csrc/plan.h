@@ -102,7 +102,7 @@ struct ssm_plan {
         int device = -1;
         void *tiles = nullptr;  // SsmTile[n_tiles]
         void *seqs = nullptr;   // SsmSeq[batch]
-        void *order = nullptr;  // int32_t[batch], in the same allocation
+        void *order = nullptr;  // int32_t[batch], in the same allocation; filled only if a roll-forward needs it
         void *scan_seqs = nullptr;  // SsmScanSeq[stretches]
         void *ptrs = nullptr;   // void*[batch], rewritten by every call that passes states
     };

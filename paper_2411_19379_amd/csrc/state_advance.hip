@@ -291,9 +291,22 @@ bool state_advance_supports(const ssm_shape_t &s)
     return n >= 4 && n <= 256 && (n & (n - 1)) == 0;
 }
 
+// How many sequences of the plan are rolled forward by the matrix-core kernels: the first ones of plan->order.
+static int longer_ones(const ssm_plan *plan)
+{
+    return scan_f32_supports(plan->shape) ? ssm_plan_longer_than(plan, advance_max_tokens(plan->shape)) : 0;
+}
+
+// True if a roll-forward of the plan takes both kinds of kernels and so needs the order of its sequences on the GPU.
+bool state_advance_mixes(const ssm_plan *plan)
+{
+    const int n_long = longer_ones(plan);
+    return n_long > 0 && n_long < ssm_plan_longer_than(plan, 0);
+}
+
 // Advance the state of every sequence of the plan in place by the sequence's tokens; `d_state_ptrs` is a device array
 // of plan->batch device pointers to states in the plan's state type (not needed if args.host_ptrs is set).  y may be null.
-// args.order is needed.
+// args.order is needed where both kinds of kernels are (state_advance_mixes).
 // Checkpoints of the plan are ignored (the result is the in-place state after the last token).
 hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void *const *d_state_ptrs,
                                 hipStream_t stream)
@@ -304,7 +317,7 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
     if (plan->batch == 0 || plan->tiles.empty())
         return hipSuccess;
     const int busy = ssm_plan_longer_than(plan, 0);
-    const int n_long = scan_f32_supports(plan->shape) ? ssm_plan_longer_than(plan, advance_max_tokens(plan->shape)) : 0;
+    const int n_long = longer_ones(plan);
     if (n_long > 0) {
         ScanArgs roll = args;
         roll.init_ptrs = d_state_ptrs;
