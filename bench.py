@@ -42,9 +42,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # --calibrate-copy.  Keyed by the hash of the kernel source the counters were
 # taken on: once that source changes the figure is reported as null.
 MEASURED_TRAFFIC = {
-    "09ebaa5b38e19117bfe1aefad4dbf491f5e77987": {
-        "cfg3_7b_32k_bf16": {"fetch_bytes": 845699359, "write_bytes": 546151619},
-        "cfg4_7b_128k_ckpt4096_bf16": {"fetch_bytes": 3466112151, "write_bytes": 2289241906},
+    "682cfa135dec00dc869f78d1da5d7f28963480dd": {
+        "cfg3_7b_32k_bf16": {"fetch_bytes": 842566718, "write_bytes": 546155867},
+        "cfg4_7b_128k_ckpt4096_bf16": {"fetch_bytes": 3464737562, "write_bytes": 2289232919},
     },
 }
 
@@ -320,7 +320,7 @@ def main() -> int:
                    "call_ms_min": float(call_ms.min()), "ms_per_step_with_events": events_ms_per_step},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "ssm_scan_mfma_kernel" if mfma else "ssm_scan_valu_kernel",
+                     "kernel": "ssm_scan_mfma_kernel" if mfma else "ssm_scan_f32_kernel",
                      "kernel_ms": kern_ms, "kernel_ms_median": float(np.median(scan_ms)),
                      "kernel_ms_min": float(scan_ms.min()),
                      "prep_kernel": "ssm_prep_kernel" if mfma else None, "prep_kernel_ms": float(prep_ms.mean()),

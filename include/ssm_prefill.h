@@ -78,7 +78,7 @@ typedef struct {
     int32_t n_tiles;       /* token tiles the kernels walk (sequence-local, split at checkpoints) */
     int32_t tile_tokens;   /* upper bound of a tile's length */
     int32_t path;          /* SSM_PATH_* */
-    int32_t n_workgroups;  /* grid size of the scan kernel */
+    int32_t n_workgroups;  /* grid size of the matrix-core scan; (sequence, head) pairs on the fp32 path */
     int32_t n_stretches;   /* stretches the scan walks: one per sequence, more when long sequences are cut
                               (ssm_plan_stretch) */
 } ssm_plan_info_t;

@@ -35,7 +35,7 @@ namespace {
 // What bounds it: the matrix cores, whose fp32 rate is a sixteenth of their bf16 one (NC (8 NB + 4) + 4 NB products of
 // 32 cycles per tile; the 4 NB of the scores are the same for every slice, hence NC > 1), and the chain of hand-offs.
 // Against the vector-ALU kernel below (one workgroup per head, five barriers per 16 tokens, dot products from LDS), per
-// call: 80 heads x 64 channels, d_state 128, 2048 tokens 8180 -> 146 us; 4 heads x 16 channels, d_state 16, 256 tokens
+// call: 80 heads x 64 channels, d_state 128, 2048 tokens 8180 -> 141 us; 4 heads x 16 channels, d_state 16, 256 tokens
 // 64 -> 12 us.
 constexpr int kF32SpinLimit = 1 << 16;  // polls of the hand-off counter before a wave gives up waiting (milliseconds)
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -429,10 +429,10 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
 // With d_state 16 a lane holds four state indices per product and the other four slots take the second part of the
 // split; the first 16 queries of a unit have only 16 keys and do the same.
 //
-// What bounds it: the vector ALUs that split and mask (three to four times the cycles of the products).  Per call, this
+// What bounds it: the vector ALUs that split and mask (counters: three to four times the cycles of the products).  Per call, this
 // kernel against the fp32 instruction on the same storage: 32 heads x 64 channels, d_state 16, eight requests of 18 K
 // tokens in all, 107 -> 67 us; roll-forward of three sequences of 17 to 256 tokens, 128 heads x 64 channels, d_state 128,
-// 52 -> 37 us.
+// 52 -> 35 us.
 constexpr int kUnit = 32;
 typedef __attribute__((ext_vector_type(8))) __bf16 split_bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 split_bf16x2;

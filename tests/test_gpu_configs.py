@@ -79,7 +79,7 @@ def test_cfg4_128k_fine_grained_checkpoints():
 
 
 def test_fp32_mode_at_the_2p7b_layer_shape():
-    """fp32 mode (tolerance 1e-4) at P=64, N=128: 8192 state elements per head, 32 per thread of the vector-ALU
+    """fp32 mode (tolerance 1e-4) at P=64, N=128: 8192 state elements per head, the largest state of the fp32
     kernel.  8 heads in 2 groups, cached initial states, checkpoints inside and at the ends of tiles."""
     from workloads import LayerShape
     say("fp32 mode: H=8 P=64 N=128 G=2, 3 requests, random initial states, mid-tile checkpoints")
@@ -92,7 +92,7 @@ def test_fp32_mode_at_the_2p7b_layer_shape():
 
 
 def test_fp32_mode_of_cfg1_at_full_size():
-    """The 2.7B-shaped 2K-token configuration with fp32 inputs and outputs (fp32 vector-ALU kernel, all 80 heads,
+    """The 2.7B-shaped 2K-token configuration with fp32 inputs and outputs (fp32 matrix-core kernel, all 80 heads,
     cached 1024-token prefix): the 1e-4 tolerance of the fp32 mode at a full layer."""
     from workloads import LayerShape
     say("cfg1 in fp32 mode: H=80 P=64 N=128 G=1, T=2048 after a 1024-token cached prefix; all 80 heads")

@@ -1,5 +1,5 @@
 """GPU parity with cached states kept in fp16 or bf16 (a cache that stores its entries in half the bytes), and at
-d_state = 16 (the state width of the first-generation selective SSM layers), which the vector-ALU kernel serves.
+d_state = 16 (the state width of the first-generation selective SSM layers), which the split-operand kernel serves.
 
 The oracle starts from the initial states as the cache holds them (rounded to the storage type), so what is compared
 is the scan itself plus one rounding of each checkpoint to the storage type."""
@@ -21,7 +21,7 @@ STATE_TOL = {"f32": 2e-2, "f16": 2e-2, "bf16": 2.5e-2}
 SHAPES = {
     # the matrix-core kernel: the 7B layer's head shape on 8 heads in 2 groups
     "mfma_p64_n128": (LayerShape(8, 64, 128, 2, 256, "bf16"), 1),
-    # d_state = 16: served by the fp32 vector-ALU kernel, bf16 storage
+    # d_state = 16: served by the split-operand kernel, bf16 storage
     "valu_p64_n16": (LayerShape(32, 64, 16, 1, 256, "bf16"), 0),
 }
 
