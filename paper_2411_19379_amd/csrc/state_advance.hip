@@ -21,7 +21,7 @@ constexpr int kAdvMaxRows = 8;  // state rows per thread
 // A longer sequence is rolled forward by the matrix-core kernels of scan_valu.hip (fp32 as here): the token loop is one
 // chain of dependent loads and sums, 1 to 2 us a token.  Three sequences of 17 to 256 tokens at 128 heads: 466 -> 37 us.
 // The sequence's own length decides and nothing else of the batch, so that its bits do not depend on its neighbours; a
-// batch with both kinds takes two launches, each over its own sequences.
+// batch with both kinds takes two launches (workgroups of the other kind's sequences leave this kernel's at once).
 // Where the line lies, token recurrence against matrix cores, us per call (heads x 64 channels, d_state 128):
 //   bf16, 128 heads, fp32 states   1 sequence 4 tokens 12 / 7    8 x 5 tokens 22 / 23    64 x 5 137 / 159   64 x 8 185 / 165
 //   bf16, 80 heads, fp16 states    1 x 4  12 / 6                 8 x 5  18 / 14          64 x 4 63 / 72     64 x 5  73 / 72
@@ -158,14 +158,15 @@ struct AdvanceArgs {
     StatePtrs states;          // [batch] device pointers, each [H,P,N] in the state type; null = leave the sequence alone
     const SsmTile *tiles;
     const SsmSeq *seqs;
-    const int32_t *order;      // the launch's k-th sequence is order[k]; null: k
     int H, P, N, G;
     int rows_per_thread;       // 1..kAdvMaxRows
     int slices;                // workgroups per (sequence, head)
+    int most_tokens;           // longer sequences belong to another launch (Mixed); 0: there are none
     bool stream;               // the states pass by the caches
 };
 
-template <typename IO, int LPR, int ST, bool NT>
+// Mixed: the batch also has sequences that another launch advances (a look at the tile table that a decode step does without).
+template <typename IO, int LPR, int ST, bool NT, bool Mixed>
 __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
 {
     typedef typename StateVec<ST>::elem state_t;
@@ -173,17 +174,22 @@ __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
     const int H = a.H, P = a.P, N = a.N, G = a.G;
     const int slice = blockIdx.x % a.slices;
     const int h = (blockIdx.x / a.slices) % H;
-    const int rank = blockIdx.x / (a.slices * H), seq = a.order ? a.order[rank] : rank;
+    const int seq = blockIdx.x / (a.slices * H);
     const int g = h / (H / G);
     const int c = threadIdx.x % LPR;   // this thread holds state columns 4c .. 4c+3
     const int rs = threadIdx.x / LPR;  // row slot inside a pass
     const int R = a.rows_per_thread;
     const int p_first = slice * kRowsPerPass * R + rs;  // rows p_first + kRowsPerPass * r
 
-    const SsmSeq sq = a.seqs[seq];
     state_t *state = static_cast<state_t *>(const_cast<void *>(a.states.of(seq)));
+    const SsmSeq sq = a.seqs[seq];
     if (sq.tile_end <= sq.tile_begin || state == nullptr)
         return;  // nothing to advance; the whole workgroup leaves
+    if constexpr (Mixed) {
+        const SsmTile last = a.tiles[sq.tile_end - 1];
+        if (last.tok0 + last.len - a.tiles[sq.tile_begin].tok0 > a.most_tokens)
+            return;
+    }
 
     const IO *x = static_cast<const IO *>(a.x);
     const IO *dt = static_cast<const IO *>(a.dt);
@@ -239,13 +245,22 @@ __global__ __launch_bounds__(kAdvThreads) void ssm_advance_kernel(AdvanceArgs a)
     }
 }
 
+template <typename IO, int LPR, int ST, bool NT>
+void launch_nt(const AdvanceArgs &a, dim3 grid, hipStream_t stream)
+{
+    if (a.most_tokens > 0)
+        hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ST, NT, true>), grid, dim3(kAdvThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ST, NT, false>), grid, dim3(kAdvThreads), 0, stream, a);
+}
+
 template <typename IO, int LPR, int ST>
 void launch_st(const AdvanceArgs &a, dim3 grid, hipStream_t stream)
 {
     if (a.stream)
-        hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ST, true>), grid, dim3(kAdvThreads), 0, stream, a);
+        launch_nt<IO, LPR, ST, true>(a, grid, stream);
     else
-        hipLaunchKernelGGL((ssm_advance_kernel<IO, LPR, ST, false>), grid, dim3(kAdvThreads), 0, stream, a);
+        launch_nt<IO, LPR, ST, false>(a, grid, stream);
 }
 
 template <typename IO, int LPR>
@@ -336,7 +351,7 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
     a.states = state_ptrs_of(d_state_ptrs, args.host_ptrs, args.n_host_ptrs);
     a.tiles = args.tiles;
     a.seqs = args.seqs;
-    a.order = n_long > 0 ? args.order + n_long : nullptr;
+    a.most_tokens = n_long > 0 ? advance_max_tokens(plan->shape) : 0;
     a.H = args.H;
     a.P = args.P;
     a.N = args.N;
@@ -346,7 +361,6 @@ hipError_t launch_state_advance(const ssm_plan *plan, const ScanArgs &args, void
         advanced -= args.host_ptrs[plan->order[r]] == nullptr;
     const long long bytes = advanced * a.H * a.P * a.N * (state_type == ADV_STATE_F32 ? 4 : 2);
     a.stream = bytes > (state_type == ADV_STATE_F16 ? kAdvStreamBytesF16 : kAdvStreamBytes);
-    const int n_seqs = n_long > 0 ? busy - n_long : plan->batch;
-    return plan->shape.io_dtype == SSM_DT_F32 ? launch_io<float>(a, n_seqs, state_type, stream)
-                                              : launch_io<bf16_t>(a, n_seqs, state_type, stream);
+    return plan->shape.io_dtype == SSM_DT_F32 ? launch_io<float>(a, plan->batch, state_type, stream)
+                                              : launch_io<bf16_t>(a, plan->batch, state_type, stream);
 }
