@@ -140,8 +140,9 @@ int ssm_plan_launch_item(const ssm_plan_t *plan, int64_t block, int32_t *item);
  * occupy the GPU, a long sequence is cut into several stretches that are scanned at the same time, the later ones
  * from a zero state (starts_from_zero = 1); the state their predecessor ends with is then carried over, and what it
  * adds to their outputs and checkpoints (the recurrence of Section 2.1's state update is linear in the state) is added
- * by a second kernel of the same call.  Results are those of the plain scan up to rounding.  Any output pointer may
- * be NULL; SSM_ERR_INVALID_ARG if the plan is NULL or i is out of range. */
+ * by a second kernel of the same call.  Results are those of the plain scan up to rounding.  Plans with enough work
+ * to fill the GPU with workgroups of 256 channels take a scan that cuts sequences by a rule of its own; the stretches
+ * listed here are those of the other one.  Any output pointer may be NULL; SSM_ERR_INVALID_ARG if the plan is NULL or i is out of range. */
 int ssm_plan_stretch(const ssm_plan_t *plan, int32_t i, int32_t *tile_begin, int32_t *tile_end,
                      int32_t *starts_from_zero);
 
@@ -281,11 +282,13 @@ int ssm_conv1d_prefill(const ssm_plan_t *plan, int32_t channels, int32_t kernel_
  * Measurement aid (no passage of the paper: it serves the per-kernel timing of
  * the benchmark).  ssm_prefill on a matrix-core plan launches the operand
  * preparation, the scan and, when long sequences were cut into stretches
- * (ssm_plan_stretch), the kernels that add the carried states' contribution.
+ * (ssm_plan_stretch), the kernels that add the carried states' contribution, or
+ * else, for plans of larger batches, the states of the segments that later parts
+ * of a sequence start from (if any are cut) and the scan.
  * With non-NULL events (hipEvent_t created by the caller with timing enabled),
  * every later ssm_prefill / ssm_prefill_noalloc call of the calling thread
- * records the first event on its stream after the preparation kernel and the
- * second after the scan kernel, so that the caller can time each kernel alone;
+ * records the first event on its stream after the preparation (or segment)
+ * kernel and the second after the scan kernel, so that the caller can time each kernel alone;
  * NULL switches an event off again.  Nothing else changes.
  */
 void ssm_profile_mark(void *after_first_kernel, void *after_second_kernel);

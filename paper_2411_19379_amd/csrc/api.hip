@@ -63,6 +63,16 @@ static hipError_t upload_table(void *dst, const void *src_host, size_t bytes, hi
 
 static size_t round16(size_t n) { return (n + 15) / 16 * 16; }
 
+// What the matrix-core scan walks: the pieces of a plan with resident states, else the stretches.
+static const void *scan_table(const ssm_plan *plan)
+{
+    return plan->resident ? static_cast<const void *>(plan->pieces.data()) : plan->scan_seqs.data();
+}
+static size_t scan_table_bytes(const ssm_plan *plan)
+{
+    return plan->resident ? plan->pieces.size() * sizeof(SsmPiece) : plan->scan_seqs.size() * sizeof(SsmScanSeq);
+}
+
 // Device copies of a plan's tables on the current GPU; made on first use (four device allocations, the uploads
 // enqueued on `stream` and waited for once, so that later calls on any stream find them complete).
 static int device_tables(const ssm_plan *plan, hipStream_t stream, ssm_plan::DeviceTables *out)
@@ -81,7 +91,7 @@ static int device_tables(const ssm_plan *plan, hipStream_t stream, ssm_plan::Dev
     const size_t seq_bytes = round16(plan->seqs.size() * sizeof(SsmSeq));
     const size_t order_bytes = round16(plan->order.size() * sizeof(int32_t));
     const size_t ptr_bytes = round16((size_t)plan->batch * sizeof(void *));
-    const size_t scan_seq_bytes = round16(plan->scan_seqs.size() * sizeof(SsmScanSeq));
+    const size_t scan_seq_bytes = round16(scan_table_bytes(plan));
     ssm_plan::DeviceTables t;
     t.device = dev;
     auto release = [&]() {
@@ -111,7 +121,7 @@ static int device_tables(const ssm_plan *plan, hipStream_t stream, ssm_plan::Dev
     if (e == hipSuccess && state_advance_mixes(plan))
         e = upload_table(t.order, plan->order.data(), plan->order.size() * sizeof(int32_t), stream);
     if (e == hipSuccess)
-        e = upload_table(t.scan_seqs, plan->scan_seqs.data(), plan->scan_seqs.size() * sizeof(SsmScanSeq), stream);
+        e = upload_table(t.scan_seqs, scan_table(plan), scan_table_bytes(plan), stream);
     if (e == hipSuccess)
         e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {
@@ -197,8 +207,10 @@ static int launch_scan(const ssm_plan *plan, const void *x, const void *dt, cons
     args.host_ptrs = host_ptrs;
     args.n_host_ptrs = host_ptrs ? plan->batch : 0;
     fill_args(plan, args, d_tiles, d_seqs, d_scan_seqs);
-    const hipError_t e = plan->path == SSM_PATH_MFMA_BF16 ? launch_scan_mfma(plan, args, workspace, stream)
-                                                          : launch_scan_valu(plan, args, stream);
+    const hipError_t e = plan->path != SSM_PATH_MFMA_BF16 ? launch_scan_valu(plan, args, stream)
+                         : plan->resident                 ? launch_scan_resident(plan, args, static_cast<const SsmPiece *>(d_scan_seqs),
+                                                                                 workspace, stream)
+                                                          : launch_scan_mfma(plan, args, workspace, stream);
     if (e != hipSuccess)
         return hip_fail("kernel launch", e);
     return SSM_OK;
@@ -247,7 +259,12 @@ constexpr size_t kNoAllocMaxStretches = kNoAllocMaxBatch + 256;  // cutting adds
 constexpr size_t kScratchSeqsOff = kNoAllocMaxTiles * sizeof(SsmTile);
 constexpr size_t kScratchPtrsOff = kScratchSeqsOff + kNoAllocMaxBatch * sizeof(SsmSeq);
 constexpr size_t kScratchScanSeqsOff = kScratchPtrsOff + kNoAllocMaxBatch * sizeof(void *);
-constexpr size_t kScratchBytes = kScratchScanSeqsOff + kNoAllocMaxStretches * sizeof(SsmScanSeq);
+// a plan with resident states has fewer pieces than that, and at most one segment per kSegmentTiles tiles and per piece more
+constexpr size_t kNoAllocMaxPieces = 2 * kNoAllocMaxStretches + kNoAllocMaxTiles / kSegmentTiles;
+constexpr size_t kScratchScanBytes = kNoAllocMaxStretches * sizeof(SsmScanSeq) > kNoAllocMaxPieces * sizeof(SsmPiece)
+                                         ? kNoAllocMaxStretches * sizeof(SsmScanSeq)
+                                         : kNoAllocMaxPieces * sizeof(SsmPiece);
+constexpr size_t kScratchBytes = kScratchScanSeqsOff + kScratchScanBytes;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -289,7 +306,7 @@ extern "C" int ssm_prefill_noalloc(const ssm_plan_t *plan,
     if (plan->total_tokens == 0 || plan->batch == 0)
         return SSM_OK;
     if (plan->tiles.size() > kNoAllocMaxTiles || (size_t)plan->batch > kNoAllocMaxBatch ||
-        plan->scan_seqs.size() > kNoAllocMaxStretches)
+        plan->scan_seqs.size() > kNoAllocMaxStretches || plan->pieces.size() > kNoAllocMaxPieces)
         return fail(SSM_ERR_UNSUPPORTED_SHAPE,
                     "ssm_prefill_noalloc handles at most 16384 tiles and 1024 sequences per call");
     bool any_init = false;
@@ -306,8 +323,7 @@ extern "C" int ssm_prefill_noalloc(const ssm_plan_t *plan,
     if (e == hipSuccess)
         e = upload_table(base + kScratchSeqsOff, plan->seqs.data(), plan->seqs.size() * sizeof(SsmSeq), stream);
     if (e == hipSuccess)
-        e = upload_table(base + kScratchScanSeqsOff, plan->scan_seqs.data(), plan->scan_seqs.size() * sizeof(SsmScanSeq),
-                         stream);
+        e = upload_table(base + kScratchScanSeqsOff, scan_table(plan), scan_table_bytes(plan), stream);
     const bool in_args = any_init && plan->batch <= kStatePtrsInArgs, in_table = any_init && !in_args;
     if (e == hipSuccess && in_table)
         e = upload_table(base + kScratchPtrsOff, init_state_ptrs, (size_t)plan->batch * sizeof(void *), stream);

@@ -118,6 +118,9 @@ hipError_t launch_scan_valu(const ssm_plan *plan, const ScanArgs &args, hipStrea
 bool scan_f32_supports(const ssm_shape_t &s);
 hipError_t launch_scan_f32(const ssm_plan *plan, const ScanArgs &args, bool roll, int n_seqs, hipStream_t stream);
 hipError_t launch_scan_mfma(const ssm_plan *plan, const ScanArgs &args, void *workspace, hipStream_t stream);
+// `d_pieces`: the plan's table of pieces
+hipError_t launch_scan_resident(const ssm_plan *plan, const ScanArgs &args, const SsmPiece *d_pieces, void *workspace,
+                                hipStream_t stream);
 // events to record after the first and after the second kernel of the matrix-core scan on the calling thread
 // (nullptr: none)
 hipEvent_t ssm_profile_event(int which);

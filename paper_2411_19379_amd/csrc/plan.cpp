@@ -3,6 +3,8 @@
 #include "plan.h"
 
 #include <algorithm>
+#include <functional>
+#include <queue>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -55,6 +57,8 @@ static int choose_path(const ssm_shape_t &s, ssm_plan *plan)
     plan->tile_tokens = s.chunk < tile ? s.chunk : tile;
     return SSM_OK;
 }
+
+static void ssm_plan_choose_pieces(ssm_plan *plan);
 
 extern "C" int ssm_plan_create(const ssm_shape_t *shape, int32_t batch,
                                const int32_t *cu_seqlens_host,
@@ -176,8 +180,10 @@ extern "C" int ssm_plan_create(const ssm_shape_t *shape, int32_t batch,
         return fail(SSM_ERR_UNSUPPORTED_SHAPE, "batch*nheads too large for one launch");
     }
     plan->n_workgroups = (int32_t)wgs;
-    if (plan->path == SSM_PATH_MFMA_BF16)
+    if (plan->path == SSM_PATH_MFMA_BF16) {
         ssm_plan_build_stretches(plan, kMfmaWorkgroupsPerRound, kMfmaMinStretchTiles);
+        ssm_plan_choose_pieces(plan);
+    }
     *out = plan;
     return SSM_OK;
 }
@@ -284,6 +290,175 @@ static void ssm_plan_order_sequences(ssm_plan *plan)
     plan->n_items = (int32_t)(n_active * plan->shape.nheads * plan->p_split);
 }
 
+// ---------------------------------------------------------------- the scan with resident states
+void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
+{
+    std::vector<SsmPiece> segments;
+    plan->pieces.clear();
+    for (int32_t i = 0; i < plan->batch; ++i) {
+        const int64_t begin = plan->seqs[i].tile_begin, n = plan->seqs[i].tile_end - begin;
+        const int64_t parts = (n + most - 1) / most;
+        int32_t back = 0;
+        for (int64_t k = 0; k < parts; ++k) {
+            SsmPiece p;
+            p.tile_begin = (int32_t)(begin + n * k / parts);
+            p.tile_end = (int32_t)(begin + n * (k + 1) / parts);
+            p.seq = i;
+            p.slot = (int32_t)segments.size() - 1;
+            p.back = back;
+            p.stop = p.tile_end;
+            plan->pieces.push_back(p);
+            if (k + 1 == parts)
+                break;
+            const int64_t m = p.tile_end - p.tile_begin, cuts = (m + segment - 1) / segment;
+            for (int64_t c = 0; c < cuts; ++c) {
+                SsmPiece g = p;
+                g.tile_begin = (int32_t)(p.tile_begin + m * c / cuts);
+                g.tile_end = (int32_t)(p.tile_begin + m * (c + 1) / cuts);
+                g.slot = (int32_t)segments.size();
+                g.back = back++;
+                segments.push_back(g);
+            }
+        }
+    }
+    std::stable_sort(plan->pieces.begin(), plan->pieces.end(), [](const SsmPiece &a, const SsmPiece &b) {
+        return a.tile_end - a.tile_begin > b.tile_end - b.tile_begin;
+    });
+    // those at the end of their piece first: the others may turn out to have decayed to nothing by then
+    std::stable_sort(segments.begin(), segments.end(),
+                     [](const SsmPiece &a, const SsmPiece &b) { return a.stop - a.tile_end < b.stop - b.tile_end; });
+    plan->n_pieces = (int32_t)plan->pieces.size();
+    plan->n_segments = (int32_t)segments.size();
+    plan->pieces.insert(plan->pieces.end(), segments.begin(), segments.end());
+}
+
+size_t ssm_piece_decay_offset(const ssm_plan *plan)
+{
+    const ssm_shape_t &s = plan->shape;
+    return (size_t)plan->n_segments * s.nheads * s.headdim * s.d_state * sizeof(float);
+}
+size_t ssm_piece_workspace(const ssm_plan *plan)
+{
+    return ssm_piece_decay_offset(plan) + (size_t)plan->n_segments * plan->shape.nheads * sizeof(float);
+}
+
+// Tiles that the busiest of `places` workgroups-at-a-time works through, for pieces (or stretches) of `lengths` tiles,
+// longest first, `copies` workgroups each, dealt out in order as places become free.  `fill` is the busy share of it all.
+static double ssm_busiest(const std::vector<int64_t> &lengths, int64_t copies, int64_t places, double *fill)
+{
+    int64_t all = 0;
+    for (int64_t v : lengths)
+        all += v;
+    const double share = (double)all * copies / places;
+    const int64_t n = (int64_t)lengths.size() * copies, longest = lengths.empty() ? 0 : lengths[0];
+    double busiest = (double)longest;
+    if (n > 16 * places) {
+        busiest = std::max(busiest, share + 0.25 * longest);
+    } else if (n > places) {
+        std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> ends;
+        for (int64_t i = 0; i < places; ++i)
+            ends.push(0);
+        int64_t last = 0;
+        for (int64_t v : lengths)
+            for (int64_t c = 0; c < copies; ++c) {
+                const int64_t end = ends.top() + v;
+                ends.pop();
+                ends.push(end);
+                last = std::max(last, end);
+            }
+        busiest = (double)last;
+    }
+    *fill = busiest > 0 ? share / busiest : 1.0;
+    return busiest;
+}
+
+// Which scan a plan takes.  The estimates are fits to MI355X measurements; in us, this scan and the other, as measured:
+//   128 heads, 8 groups: 32768 tokens 455 and 448; 65536 787 and 900; 131072 1428 and 1872; 8 x 4096 332 and 428; 16 x 600
+//     121 and 172; 2048 127 and 38.  80 heads, 1 group: 16 requests of up to 7700 523 and 563; 16 x 4096 547 and 490;
+//     65536 565 and 554; 131072 954 and 1041.  16 heads: 32768 85 and 118; 65536 146 and 208; 3 x 10000 80 and 103
+//   this scan: a tile of 256 channels in 3.9 us, 5.0 if every compute unit is busy (memory is then what bounds it); launch,
+//     first loads and the states' stores 15 us; if cut, 18 us and 2.6 us per tile that counts of the segments (the last 48
+//     of a piece or so, by the decay)
+//   the other: a tile of 64 channels in 1.4 us, of 32 in 0.5 to 0.9; the preparation at 55 (tile, group) pairs per us; the
+//     states that are carried from stretch to stretch
+// Over 63 batches of 1 to 64 sequences and 2 to 128 heads the choice was the slower one nowhere by more than 3 %.
+static void ssm_plan_choose_pieces(ssm_plan *plan)
+{
+    const ssm_shape_t &s = plan->shape;
+    const int64_t group = (int64_t)(s.nheads / s.ngroups) * s.headdim, channels = (int64_t)s.nheads * s.headdim;
+    // a workgroup's channels: 4, 2 or 1 whole heads of one group
+    if (s.headdim < 64 || kResidentChannels % s.headdim != 0 || group % kResidentChannels != 0 || plan->tiles.empty())
+        return;
+    const int64_t blocks = channels / kResidentChannels;
+    std::vector<int64_t> lengths;
+    for (const SsmScanSeq &q : plan->scan_seqs)
+        lengths.push_back(q.tile_end - q.tile_begin);
+    std::sort(lengths.begin(), lengths.end(), std::greater<int64_t>());
+    double fill = 0;
+    const bool wide = s.headdim / plan->p_split == kMfmaWideChannels;
+    double other = ssm_busiest(lengths, (int64_t)s.nheads * plan->p_split, kMfmaWorkgroupsPerRound, &fill);
+    other *= wide ? 1.4 : 0.5 + 0.4 * fill;
+    other += 4.0 + (double)plan->tiles.size() * s.ngroups / 55.0;
+    if (plan->n_carry > 0)
+        other += 20.0 + 0.25 * plan->n_carry * (double)channels / kMfmaWideChannels;
+
+    int64_t longest = 0;
+    lengths.clear();
+    for (const SsmSeq &q : plan->seqs) {
+        lengths.push_back(q.tile_end - q.tile_begin);
+        longest = std::max(longest, lengths.back());
+    }
+    auto pieces_of = [&](int64_t most) {
+        int64_t n = 0;
+        for (int64_t v : lengths)
+            n += (v + most - 1) / most;
+        return n;
+    };
+    double best = other;
+    int64_t best_most = 0;
+    auto consider = [&](int64_t most) {
+        std::vector<int64_t> pieces;
+        int64_t counted = 0, added = 0;
+        for (int64_t v : lengths) {
+            const int64_t parts = (v + most - 1) / most;
+            for (int64_t k = 0; k < parts; ++k)
+                pieces.push_back(v * (k + 1) / parts - v * k / parts);
+            if (parts > 1) {
+                added += parts - 1;
+                counted += (parts - 1) * std::min<int64_t>(v / parts, 48);
+            }
+        }
+        if (added > kMostAddedPieces)
+            return;
+        std::sort(pieces.begin(), pieces.end(), std::greater<int64_t>());
+        const double tiles = ssm_busiest(pieces, blocks, kResidentPerRound, &fill);
+        double t = 15.0 + tiles * (3.9 + 1.1 * fill * fill * fill * fill);
+        if (added > 0)
+            t = 1.06 * (t + 18.0 + 2.6 * (double)counted * blocks / kResidentPerRound);  // 6 %: the fits' own error
+        if (t < best) {
+            best = t;
+            best_most = most;
+        }
+    };
+    consider(longest);
+    // the smallest pieces that still run in one round
+    if (pieces_of(longest) * blocks < kResidentPerRound) {
+        int64_t lo = kMinPieceTiles, hi = std::max<int64_t>(longest, lo);
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (pieces_of(mid) * blocks <= kResidentPerRound)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        if (lo < longest)
+            consider(lo);
+    }
+    plan->resident = best_most > 0;
+    if (plan->resident)
+        ssm_plan_build_pieces(plan, (int32_t)best_most, kSegmentTiles);
+}
+
 SsmMfmaWorkspace ssm_mfma_workspace(const ssm_plan *plan)
 {
     auto round256 = [](size_t n) { return (n + 255) / 256 * 256; };
@@ -388,7 +563,11 @@ extern "C" int ssm_plan_workspace_bytes(const ssm_plan_t *plan, size_t *bytes)
         return fail(SSM_ERR_INVALID_ARG, "plan or bytes is NULL");
     // The running state never leaves the chip between tiles; the matrix-core scan needs room for the operands
     // that the heads of a group share (written by its first kernel, read by its second) and, when it cuts long
-    // sequences into stretches, for the states carried from one stretch to the next and each tile's total decay.
+    // sequences into stretches, for the states carried from one stretch to the next and each tile's total decay.  The scan
+    // with resident states needs some only if it cuts a sequence: a state and a decay per segment.  A plan's requirement
+    // is the larger of the two, whichever scan it takes.
     *bytes = ssm_mfma_workspace(plan).total;
+    if (plan->resident)
+        *bytes = std::max(*bytes, ssm_piece_workspace(plan));
     return SSM_OK;
 }

@@ -41,6 +41,18 @@ struct SsmScanSeq {
     int32_t reserved;
 };
 
+// What one workgroup of the scan with resident states (scan_resident.hip) walks: consecutive tiles of one sequence.  The
+// pieces that others continue are cut once more, into segments; a segment has a slot, which holds what its own tokens (and,
+// for the first of a sequence, the cached state) add to the state at its end.
+struct SsmPiece {
+    int32_t tile_begin;
+    int32_t tile_end;
+    int32_t seq;
+    int32_t slot;  // of a segment: its own; of a piece: that of the segment in front of it.  The ones before have those below
+    int32_t back;  // segments of the sequence in front of it
+    int32_t stop;  // of a segment: the tile where its piece ends
+};
+
 // Launch order of the matrix-core scan.  Its work items, one per (rank of a non-empty sequence, head, channel slice),
 // form a line ordered by rank, then head, then slice: longest sequences first.  The hardware deals the workgroups of a
 // launch round-robin to 8 dies (XCDs), each with its own L2 and 32 compute units that take one workgroup at a time.
@@ -95,6 +107,10 @@ struct ssm_plan {
     std::vector<SsmSeq> seqs;
     std::vector<int32_t> order;  // the sequences by decreasing number of tokens (ties: lower index first)
     std::vector<SsmScanSeq> scan_seqs;  // matrix-core scan only
+    // Scan with resident states only: the pieces in launch order (longest first) and, behind them, the segments.
+    bool resident = false;
+    int32_t n_pieces = 0, n_segments = 0;
+    std::vector<SsmPiece> pieces;
     // Device copies of the two tables and a buffer for the per-call state
     // pointers, one set per GPU the plan has been used on.  A cache behind a
     // logically constant plan: filled on first use under `mu`.
@@ -103,7 +119,7 @@ struct ssm_plan {
         void *tiles = nullptr;  // SsmTile[n_tiles]
         void *seqs = nullptr;   // SsmSeq[batch]
         void *order = nullptr;  // int32_t[batch], in the same allocation; filled only if a roll-forward needs it
-        void *scan_seqs = nullptr;  // SsmScanSeq[stretches]
+        void *scan_seqs = nullptr;  // SsmScanSeq[stretches]; of a plan with resident states its SsmPiece table
         void *ptrs = nullptr;   // void*[batch], rewritten by every call that passes states
     };
     mutable std::mutex mu;
@@ -117,6 +133,12 @@ void ssm_set_error(const std::string &msg);
 // sequences are cut into floor(per_round / s) stretches of at least `min_tiles` tiles each; the 64-channel variant is
 // chosen if the 32-channel one would not fit one round.
 void ssm_plan_build_stretches(ssm_plan *plan, int64_t per_round, int32_t min_tiles);
+
+// Scan with resident states: (re)builds the pieces, of at most `most` tiles each, and the segments, of at most `segment`.
+void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment);
+// Where its workspace holds the total decay of every (slot, head), behind the slots, and how much it needs in all.
+size_t ssm_piece_decay_offset(const ssm_plan *plan);
+size_t ssm_piece_workspace(const ssm_plan *plan);
 
 // Tokens of sequence i.
 inline int32_t ssm_plan_tokens(const ssm_plan *plan, int32_t i)
@@ -160,6 +182,15 @@ constexpr size_t kMfmaDtBytes = 128;
 // one round of the wide variant.
 constexpr int kMfmaWideChannels = 64;
 constexpr int kMfmaWorkgroupsPerRound = 256;
+
+// The scan with resident states: channels per workgroup, workgroups that run at a time (one per compute unit), the most
+// pieces that it adds to a batch, the least tiles of a piece and the most of a segment (16: 1 to 5 % more time at 128 heads,
+// whose segments near the end of a piece all count; 64: half as much again, for want of workgroups).
+constexpr int kResidentChannels = 256;
+constexpr int kResidentPerRound = 256;
+constexpr int kMostAddedPieces = 255;
+constexpr int kMinPieceTiles = 4;
+constexpr int kSegmentTiles = 32;
 
 // A sequence is cut into stretches only if each gets at least this many tiles (the second kernel's work per stretch
 // does not shrink with the stretch), and only if it has at least kMfmaMinCutTiles tiles: at 128 tiles two stretches

@@ -1,0 +1,887 @@
+// Matrix-core scan for gfx950 whose running state stays in the accumulators: d_state 128, bf16 x/dt/B/C/y, cached states
+// in fp32, fp16 or bf16; layers with 64, 128 or 256 channels per head and groups that are a multiple of 256 channels wide.
+//
+// The per-tile algebra is that of scan_mfma.hip (tiles of q <= 64 tokens, fp16 operands of the two long contractions,
+// bf16 ones of Gm.x, everything else fp32).  What differs is who does what:
+//
+// * One workgroup per (piece of a sequence, 256 neighbouring channels of the H x P channels of a token), the channels of
+//   one group.  Wave w owns 32 of them and their state, 32 x 128 fp32 in 64 accumulator registers, for the whole piece:
+//   the state update accumulates onto it, and it never passes through LDS.
+// * B and C of a tile are read from device memory once per workgroup, converted to fp16 on their way to LDS, and the raw
+//   scores C_i.B_j are computed once per workgroup: there is no operand preparation in front and no workspace for it.
+// * A workgroup's part of a token row of x or y is 512 neighbouring bytes (128 in the other scan).
+// * What a sequence-serial recurrence leaves idle is filled by cutting long sequences into pieces.  A first kernel,
+//   ssm_segment_state_kernel, computes what the segments of every piece that is continued add to the state, as far as it
+//   has not decayed below 2^-150 by the end of the piece; a piece of the second kernel,
+//   ssm_scan_resident_kernel, starts from the sum of the segments in front of it.  So y is written once, from the true
+//   state.
+//
+// Time per call, this scan and the other: 128 heads, 131072 tokens 1430 us and 1850, 16 x 8192 1282 and 1689, 32 x 1024
+// 353 and 485; 80 heads, 16 requests of 500 to 7700 tokens 522 and 564; 16 heads, 32768 tokens 85 and 118.  At 128 heads
+// 131072
+// tokens are 4.9 GB of x, y, B, C and steps: 3.4 TB/s.  What bounds it is the serial work of a tile on a compute unit, 3.9
+// us alone and 5.0 us with every unit busy: 41 matrix instructions per wave are 1.1 us of it (two waves per matrix core), the rest is the packing of
+// their operands on the vector units, LDS traffic and two barriers.
+//
+// Lane layouts.  Everything a lane holds in runs is in natural order, eight neighbours at a time: the transpose reads that
+// fetch a B^T or x^T operand pick the four 4-column groups of a 16-column block in the order 0, 2, 1, 3, so that
+// accumulator row rho = 8 a + 4 q + r stands for index 16 (a / 2) + 8 q + 4 (a % 2) + r (pi(rho) below), and the results
+// of one product are the operand of the next as they are.
+#include <mutex>
+#include <type_traits>
+
+#include "mfma_utils.h"
+
+namespace {
+
+// Wait for this wave's own LDS traffic (LDS executes a wave's accesses in order).
+__device__ __forceinline__ void lds_wait()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
+// Workgroup barrier that orders LDS traffic only: device memory accesses stay in flight.  Device memory written by these
+// kernels is never read back by the same launch.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+constexpr int kWaves = kResidentChannels / 32;
+constexpr int kThreads = 64 * kWaves;
+// Row strides in LDS: four rows of a transpose read meet on no bank; the pieces of a row of C, which go to the same lane of
+// 16 operands, spread over the banks.
+constexpr int LDB = kN + 24, LDX = kResidentChannels + 24, LDC = 64 + 1;
+constexpr float kCutoffLog2 = -150.f;         // below this nothing is added in fp32
+constexpr int kRowsBC = kThreads / 16, kPassesBC = kQ / kRowsBC;  // rows of B and C per pass of the workgroup
+constexpr int kLanesX = kResidentChannels / 8, kRowsX = kThreads / kLanesX, kPassesX = kQ / kRowsX;  // and of x
+
+struct ResidentTables {  // of one wave's head
+    float ei[kQ];        // e^{l_i}
+    float wt[kQ];        // e^{l_q - l_j} dt_j
+    float ri[kQ];        // e^{l_i - l_31}
+    float cf[kQ];        // e^{l_31 - l_j} dt_j
+};
+struct ResidentTile {
+    _Float16 Bs[kQ][LDB];  // rows of B
+    uint4 Cf[16][LDC];     // C as operands: [token half * 8 + k-step of 16 state indices][lane]
+    bf16_t XY[kQ][LDX];    // x, token major; later y.  While a tile is worked on a wave touches its own columns only
+    uint32_t dt[kQ][2];    // steps of the workgroup's up to four heads
+};
+struct ResidentLds {
+    ResidentTile tile[2];
+    uint4 Gs[3][2][64];             // raw score blocks as accumulator images, fp16
+    ResidentTables tb[kWaves];
+};
+constexpr int kWindows = 2 * kWaves;  // of 64 tokens, looked back over at a time
+struct SegmentLds {
+    _Float16 Bs[kQ][LDB];
+    bf16_t XY[kQ][LDX];
+    uint32_t dt[kQ][2];
+    float wt[kWaves][kQ];
+    int from[kWaves];
+    float window[kWindows][4];
+};
+
+struct ResidentArgs {
+    const bf16_t *x, *dt, *B, *C;
+    const float *A, *D;
+    bf16_t *y;
+    void *state_out;
+    StatePtrs init;
+    const SsmTile *tiles;
+    const SsmPiece *pieces;  // of this launch, in launch order
+    float4 *carry;           // per slot: what the piece adds to the state, as accumulator images
+    float *decay;            // per (slot, head): the piece's total log2 decay
+    int H, P, G, blocks, n_items;
+};
+
+// pi: which of 32 columns or rows an operand lane stands for.
+__device__ __forceinline__ int operand_index(int i)
+{
+    return (i & 19) | ((i & 4) << 1) | ((i & 8) >> 1);
+}
+
+// The operands of one tile on their way from device memory to LDS, 16 bytes of a token row at a time, and the steps of the
+// workgroup's heads, every wave those of eight tokens.  Rows past the end of a partial tile re-read its last row: their
+// step counts as zero, so any finite value will do.  A tile that is not there is read through descriptors of size zero,
+// which return zeros without touching memory.
+struct TileRegs {
+    uint4 b[kPassesBC], c[kPassesBC], x[kPassesX];
+    uint32_t dt[2];
+};
+struct TileLoader {
+    const unsigned char *x, *B, *C, *dt;  // of the workgroup's channels, group and heads, token 0
+    uint32_t x_row, bc_row, dt_row;       // bytes per token row
+    int heads;                            // of the workgroup: 4, 2 or 1
+    int row, col;                         // the thread's row and column (of 8 elements) of a B or C row
+    int xr, xc;                           // and of an x row
+    int dt_tok;
+    uint32_t x_own, bc_own, dt_own;       // byte offsets of the thread's row and column
+    // of the tile to load
+    rsrc_t xs, bs, cs, ds;
+    uint32_t x_most, bc_most, dt_most;    // byte offset of the last row
+    __device__ __forceinline__ void start(const SsmTile &t, bool live)
+    {
+        const uint32_t last = (uint32_t)(t.len - 1);
+        x_most = last * x_row, bc_most = last * bc_row, dt_most = last * dt_row;
+        xs = make_rsrc(x + (size_t)t.tok0 * x_row, live ? x_most + kResidentChannels * 2 : 0);
+        bs = make_rsrc(B + (size_t)t.tok0 * bc_row, live ? bc_most + kN * 2 : 0);
+        cs = make_rsrc(C + (size_t)t.tok0 * bc_row, live ? bc_most + kN * 2 : 0);
+        ds = make_rsrc(dt + (size_t)t.tok0 * dt_row, live ? dt_most + 2 * heads : 0);
+    }
+    __device__ __forceinline__ static uint32_t least(uint32_t a, uint32_t b) { return a < b ? a : b; }
+    // 16 bytes of row `up` + the thread's own, whose offset (with the column) is `own`: a uniform part and a part per lane.  A
+    // lane past the last row reads the last 16 of the last row's `bytes`.
+    __device__ __forceinline__ static uint4 row16(const rsrc_t &r, uint32_t own, uint32_t up, uint32_t most, uint32_t bytes)
+    {
+        up = least(up, most);
+        return buf_load16(r, least(own, most - up + bytes - 16), up);
+    }
+    __device__ __forceinline__ void load_x(TileRegs &r, int m) const
+    {
+        r.x[m] = row16(xs, x_own, kRowsX * m * x_row, x_most, kResidentChannels * 2);
+    }
+    __device__ __forceinline__ void load_b(TileRegs &r, int m) const
+    {
+        r.b[m] = row16(bs, bc_own, kRowsBC * m * bc_row, bc_most, kN * 2);
+    }
+    __device__ __forceinline__ void load_c(TileRegs &r, int m) const
+    {
+        r.c[m] = row16(cs, bc_own, kRowsBC * m * bc_row, bc_most, kN * 2);
+    }
+    __device__ __forceinline__ void load_dt(TileRegs &r) const
+    {
+        const uint32_t off = least(dt_own, dt_most);
+        if (heads == 4) {
+            const auto u = __builtin_amdgcn_raw_buffer_load_b64(ds, (int)off, 0, 0);
+            r.dt[0] = u[0], r.dt[1] = u[1];
+        } else if (heads == 2) {
+            r.dt[0] = __builtin_amdgcn_raw_buffer_load_b32(ds, (int)off, 0, 0);
+        } else {
+            r.dt[0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(ds, (int)off, 0, 0);
+        }
+    }
+    template <bool kC> __device__ __forceinline__ void load(TileRegs &r, const SsmTile &t)
+    {
+        start(t, true);
+#pragma unroll
+        for (int m = 0; m < kPassesX; ++m)
+            load_x(r, m);
+#pragma unroll
+        for (int m = 0; m < kPassesBC; ++m) {
+            load_b(r, m);
+            if constexpr (kC)
+                load_c(r, m);
+        }
+        load_dt(r);
+    }
+};
+__device__ __forceinline__ TileLoader make_loader(const ResidentArgs &a, int c0, int g)
+{
+    TileLoader l;
+    const int tid = threadIdx.x;
+    l.heads = kResidentChannels > a.P ? kResidentChannels / a.P : 1;
+    l.x = reinterpret_cast<const unsigned char *>(a.x) + (size_t)c0 * 2;
+    l.B = reinterpret_cast<const unsigned char *>(a.B) + (size_t)g * kN * 2;
+    l.C = reinterpret_cast<const unsigned char *>(a.C) + (size_t)g * kN * 2;
+    l.dt = reinterpret_cast<const unsigned char *>(a.dt) + (size_t)(c0 / a.P) * 2;
+    l.x_row = (uint32_t)a.H * a.P * 2;
+    l.bc_row = (uint32_t)a.G * kN * 2;
+    l.dt_row = (uint32_t)a.H * 2;
+    l.row = tid >> 4, l.col = 8 * (tid & 15);
+    l.xr = tid / kLanesX, l.xc = 8 * (tid % kLanesX);
+    l.dt_tok = 8 * (tid >> 6) + (tid & 7);
+    l.x_own = l.xr * l.x_row + l.xc * 2, l.bc_own = l.row * l.bc_row + l.col * 2, l.dt_own = l.dt_tok * l.dt_row;
+    return l;
+}
+// The step of token `lane` of head `hd` of the workgroup.
+__device__ __forceinline__ float step_of(const uint32_t (*dt)[2], int lane, int hd, int len)
+{
+    const uint32_t u = dt[lane][hd >> 1];
+    return lane < len ? __uint_as_float((hd & 1) ? u & 0xffff0000u : u << 16) : 0.f;
+}
+
+// The accumulator images of a slot, from channel cw on, in float4 units: + 16 * 64 per 32 channels, + (4 nb + a) 64 + lane.
+__device__ __forceinline__ size_t carry_at(const ResidentArgs &a, int slot, int cw)
+{
+    return ((size_t)slot * ((size_t)a.H * a.P / 32) + cw / 32) * (16 * 64);
+}
+
+// A word or a table entry at a uniform address that no kernel of the call writes: read with scalar loads, which wait for no
+// vector memory access in flight.
+template <typename T> __device__ __forceinline__ T scalar_load(const T *p)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    typedef const uint32_t __attribute__((address_space(4))) constant_u32;
+    const constant_u32 *c = (const constant_u32 *)(uint64_t)p;
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(T) / 4; ++k)
+        w[k] = c[k];
+    T v;
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform(float v) { return read_lane(v, 0); }
+
+// What of the masks does not depend on the tile: element 4 a + r of a lane is key 16 (a / 2) + 8 q + 4 (a % 2) + r.
+struct LaneMask {
+    int diag;         // i - 8 q
+    // pairs of elements as packed, all ones where the key is not behind the query: within 16 tokens, and whether the query
+    // is one of the later 16 of the block
+    uint32_t on[4], later;
+};
+__device__ __forceinline__ LaneMask make_mask(int i, int q)
+{
+    LaneMask m;
+    m.diag = i - 8 * q;
+    m.later = i >= 16 ? 0xffffffffu : 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int j = 8 * q + 2 * e;
+        m.on[e] = (j <= (i & 15) ? 0x0000ffffu : 0u) | (j + 1 <= (i & 15) ? 0xffff0000u : 0u);
+    }
+    return m;
+}
+// A quarter (elements 4 a .. 4 a + 3) of a diagonal block of raw scores, decayed by f, D added on the diagonal, masked and
+// packed: two words of an operand of Gm.x.
+__device__ __forceinline__ uint2 mask_quarter(uint32_t raw0, uint32_t raw1, const float (&f)[4], int a, const LaneMask &m,
+                                              float Dh)
+{
+    const int e0 = 16 * (a >> 1) + 4 * (a & 1);
+    const float v0 = __builtin_fmaf(f16_lo(raw0), f[0], e0 + 0 == m.diag ? Dh : 0.f);
+    const float v1 = __builtin_fmaf(f16_hi(raw0), f[1], e0 + 1 == m.diag ? Dh : 0.f);
+    const float v2 = __builtin_fmaf(f16_lo(raw1), f[2], e0 + 2 == m.diag ? Dh : 0.f);
+    const float v3 = __builtin_fmaf(f16_hi(raw1), f[3], e0 + 3 == m.diag ? Dh : 0.f);
+    const uint32_t lo = pack2_bf16(v0, v1), hi = pack2_bf16(v2, v3), on0 = m.on[2 * (a & 1)], on1 = m.on[2 * (a & 1) + 1];
+    return a < 2 ? make_uint2(lo & (on0 | m.later), hi & (on1 | m.later)) : make_uint2(lo & on0 & m.later, hi & on1 & m.later);
+}
+
+// x^T of 32 channels as fp16 operands weighted by decay: the weights are those of tokens 16 ks + 8 q + e.
+__device__ __forceinline__ uint4 weighted(const uint4 &xv, const float4 &w0, const float4 &w1)
+{
+    return make_uint4(pack2_f16(w0.x * bf16_lo(xv.x), w0.y * bf16_hi(xv.x)), pack2_f16(w0.z * bf16_lo(xv.y), w0.w * bf16_hi(xv.y)),
+                      pack2_f16(w1.x * bf16_lo(xv.z), w1.y * bf16_hi(xv.z)), pack2_f16(w1.z * bf16_lo(xv.w), w1.w * bf16_hi(xv.w)));
+}
+
+// ================================================================ what a segment adds to the state
+// One workgroup per (segment, 256 channels).  First every wave looks back over the steps of its head from the end of the
+// piece, where the segment's contribution is used: what has decayed below the cutoff by there is left out, which for decay
+// rates as trained models have them is all but some thirty tiles.  From the earliest token that counts for one of its heads
+// the workgroup then walks forwards like the scan, without outputs.
+template <int ST>
+__global__ __launch_bounds__(kThreads, 4) void ssm_segment_state_kernel(ResidentArgs a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    SegmentLds &L = *reinterpret_cast<SegmentLds *>(lds_raw);
+    const int item = ssm_launch_item(blockIdx.x, a.n_items);
+    if (item < 0)
+        return;
+    const SsmPiece p = scalar_load(a.pieces + item / a.blocks);
+    const int lane = threadIdx.x & 63, w = uniform((int)threadIdx.x >> 6);
+    const int c0 = item % a.blocks * kResidentChannels, cw = c0 + 32 * w;
+    const int h = uniform(cw / a.P), g = c0 / (a.H / a.G * a.P);
+    const float Ah = scalar_load(a.A + h);
+    const SsmTile first = scalar_load(a.tiles + p.tile_begin), end = scalar_load(a.tiles + p.stop - 1);
+
+    // The first token that counts for this wave's head; two more than the cutoff, because the sum that whoever uses the slot
+    // compares may differ by rounding.  The waves share the work: each sums the steps of all heads of the workgroup over
+    // windows of 64 tokens.
+    int from = end.tok0 + end.len;
+    bool cut = false;
+    {
+        const int heads = kResidentChannels > a.P ? kResidentChannels / a.P : 1, hd = h - c0 / a.P;
+        const bf16_t *dt = a.dt + c0 / a.P;
+        float sum = 0.f;
+        for (int to = from; to > first.tok0; to -= 64 * kWindows) {
+            lds_barrier();  // the sums before have been read
+#pragma unroll
+            for (int u = 0; u < kWindows; u += kWaves) {
+                const int tok = to - 64 * (u + w) - 1 - lane;
+                uint32_t d[2] = {0, 0};
+                if (tok >= first.tok0) {
+                    const void *at = dt + (size_t)tok * a.H;
+                    if (heads == 4) {
+                        const uint2 v = *static_cast<const uint2 *>(at);
+                        d[0] = v.x, d[1] = v.y;
+                    } else if (heads == 2) {
+                        d[0] = *static_cast<const uint32_t *>(at);
+                    } else {
+                        d[0] = *static_cast<const bf16_t *>(at);
+                    }
+                }
+                const float s0 = read_lane(wave_inclusive_sum(bf16_lo(d[0])), 63), s1 = read_lane(wave_inclusive_sum(bf16_hi(d[0])), 63);
+                const float s2 = read_lane(wave_inclusive_sum(bf16_lo(d[1])), 63), s3 = read_lane(wave_inclusive_sum(bf16_hi(d[1])), 63);
+                if (lane == 0)
+                    *reinterpret_cast<float4 *>(L.window[u + w]) = make_float4(s0, s1, s2, s3);
+            }
+            lds_barrier();
+            for (int u = 0; u < kWindows && !cut && from > first.tok0; ++u) {
+                sum += uniform(L.window[u][hd]) * Ah * kLog2e;
+                from -= 64;
+                cut = sum < kCutoffLog2 - 2.f;
+            }
+            bool all = cut;
+            if (lane == 0)
+                L.from[w] = cut;
+            lds_barrier();
+#pragma unroll
+            for (int v = 0; v < kWaves; ++v)
+                all = all && L.from[v] != 0;
+            if (uniform((int)all))
+                break;  // the whole workgroup: every wave has read the same values
+        }
+        lds_barrier();
+        from = uniform(from > first.tok0 ? from : first.tok0);
+    }
+    if (lane == 0)
+        L.from[w] = from;
+    lds_barrier();
+    int earliest = L.from[0];
+#pragma unroll
+    for (int v = 1; v < kWaves; ++v)
+        earliest = L.from[v] < earliest ? L.from[v] : earliest;
+    earliest = uniform(earliest);
+    // tiles that end before it
+    int k = p.tile_begin;
+    for (int k0 = p.tile_begin; k0 < p.tile_end; k0 += 64) {
+        bool before = false;
+        if (k0 + lane < p.tile_end) {
+            const SsmTile u = a.tiles[k0 + lane];
+            before = u.tok0 + u.len <= earliest;
+        }
+        k += (int)read_lane(wave_inclusive_sum(before ? 1.f : 0.f), 63);
+    }
+    k = uniform(k);
+    if (k >= p.tile_end)
+        return;  // the whole workgroup; nobody gets as far as these slots
+
+    const int q = lane >> 5, g4 = lane >> 4;
+    const int tr_row = 8 * (g4 >> 1) + ((lane & 15) >> 2), tr_col = 16 * (g4 & 1) + 4 * ((lane & 1) * 2 + ((lane >> 1) & 1));
+    TileLoader ld = make_loader(a, c0, g);
+    TileRegs regs;
+    SsmTile t = scalar_load(a.tiles + k);
+    ld.load<false>(regs, t);
+    f32x16 S[4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+        S[nb] = zero16();
+    const void *init = p.back == 0 && !cut ? a.init.of(p.seq) : nullptr;
+    if (init) {  // (+ 0: the sum waits for the loads here; else the wait would be in the loop, for loads ahead as well)
+        const size_t row = ((size_t)cw + operand_index(lane & 31)) * kN + 8 * q;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float4 v = load_state4(init, row + 32 * nb + 16 * (e >> 1) + 4 * (e & 1), ST);
+                S[nb][4 * e + 0] = v.x + 0.f;
+                S[nb][4 * e + 1] = v.y + 0.f;
+                S[nb][4 * e + 2] = v.z + 0.f;
+                S[nb][4 * e + 3] = v.w + 0.f;
+            }
+    }
+    float decay = 0.f;  // of the tiles that count, log2
+    for (; k < p.tile_end; ++k) {
+        SsmTile t_next = t;
+        if (k + 1 < p.tile_end)
+            t_next = scalar_load(a.tiles + k + 1);
+#pragma unroll
+        for (int m = 0; m < kPassesBC; ++m)
+            *reinterpret_cast<uint4 *>(&L.Bs[ld.row + kRowsBC * m][ld.col]) = bf16x8_to_f16x8(regs.b[m]);
+#pragma unroll
+        for (int m = 0; m < kPassesX; ++m)
+            *reinterpret_cast<uint4 *>(&L.XY[ld.xr + kRowsX * m][ld.xc]) = regs.x[m];
+        if (lane < 8)
+            *reinterpret_cast<uint2 *>(L.dt[ld.dt_tok]) = make_uint2(regs.dt[0], regs.dt[1]);
+        lds_barrier();
+        if (k + 1 < p.tile_end)
+            ld.load<false>(regs, t_next);
+        if (t.tok0 + t.len > from) {  // uniform in the wave
+            const float dtj = step_of(L.dt, lane, h - c0 / a.P, t.len);
+            const float ell2 = wave_inclusive_sum(dtj * Ah) * kLog2e, last = read_lane(ell2, 63);
+            L.wt[w][lane] = exp2_fast(last - ell2) * dtj;
+            __builtin_amdgcn_wave_barrier();
+            const float dl = exp2_fast(last);
+            decay += last;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    S[nb][e] *= dl;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const bf16_t *px = &L.XY[16 * ks + tr_row][32 * w + tr_col];
+                uint4 b[4];
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb) {
+                    const _Float16 *pb = &L.Bs[16 * ks + tr_row][32 * nb + tr_col];
+                    b[nb] = lds_frag_tr(pb, pb + 4 * LDB);
+                }
+                const uint4 xw = weighted(lds_frag_tr(px, px + 4 * LDX), *reinterpret_cast<const float4 *>(&L.wt[w][16 * ks + 8 * q]),
+                                          *reinterpret_cast<const float4 *>(&L.wt[w][16 * ks + 8 * q + 4]));
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb)
+                    S[nb] = mfma_f16(b[nb], xw, S[nb]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        lds_barrier();
+        t = t_next;
+    }
+    float4 *out = a.carry + carry_at(a, p.slot, cw) + lane;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            out[(4 * nb + e) * 64] = make_float4(S[nb][4 * e], S[nb][4 * e + 1], S[nb][4 * e + 2], S[nb][4 * e + 3]);
+    if (lane == 0 && cw % a.P == 0)
+        a.decay[(size_t)p.slot * a.H + h] = decay;
+}
+
+// ================================================================ the scan
+// One workgroup per (piece, 256 channels).  The tiles alternate between two LDS buffers: while one is worked on, the rows
+// of the next are converted into the other and those of the one after are requested.  Two barriers per tile: operands in
+// place (and the tile before done), raw scores in place.
+//
+// Why 8 waves x 32 channels: workgroups of 128 channels, two per unit, convert and score B and C twice as often, and waves
+// of 64 channels leave no registers for the rows in flight; both measured slower.
+template <int ST>
+__global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(ResidentArgs a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    ResidentLds &L = *reinterpret_cast<ResidentLds *>(lds_raw);
+    const int item = ssm_launch_item(blockIdx.x, a.n_items);
+    if (item < 0)
+        return;
+    const SsmPiece p = scalar_load(a.pieces + item / a.blocks);
+    const int lane = threadIdx.x & 63, w = uniform((int)threadIdx.x >> 6);
+    const int c0 = item % a.blocks * kResidentChannels, cw = c0 + 32 * w;
+    const int h = uniform(cw / a.P), g = c0 / (a.H / a.G * a.P);
+    const float Ah = scalar_load(a.A + h);
+    const int i = lane & 31, q = lane >> 5, g4 = lane >> 4, pi = operand_index(i);
+    const int tr_row = 8 * (g4 >> 1) + ((lane & 15) >> 2), tr_col = 16 * (g4 & 1) + 4 * ((lane & 1) * 2 + ((lane >> 1) & 1));
+    TileLoader ld = make_loader(a, c0, g);
+    const int hd = h - c0 / a.P;  // the wave's head in the workgroup
+    unsigned char *yh = reinterpret_cast<unsigned char *>(a.y) + (size_t)c0 * 2;
+    ResidentTables &W = L.tb[w];
+    // + 32 nb + 16 (a / 2) + 4 (a % 2): this lane's 4 state values of element group a
+    const size_t state_row = ((size_t)cw + pi) * kN + 8 * q;
+
+    TileRegs regs;
+    SsmTile t = scalar_load(a.tiles + p.tile_begin), t_next = t;
+    ld.load<true>(regs, t);
+
+    f32x16 S[4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+        S[nb] = zero16();
+    if (p.back > 0) {
+        // what the pieces in front add, the nearest first, until it has decayed to nothing
+        const int slot = p.slot;
+        float f = 0.f;
+        for (int m = 0; m < p.back && f >= kCutoffLog2; ++m) {
+            const float scale = exp2_fast(f);
+            const float4 *in = a.carry + carry_at(a, slot - m, cw) + lane;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float4 v = in[(4 * nb + e) * 64];
+                    S[nb][4 * e + 0] = __builtin_fmaf(scale, v.x, S[nb][4 * e + 0]);
+                    S[nb][4 * e + 1] = __builtin_fmaf(scale, v.y, S[nb][4 * e + 1]);
+                    S[nb][4 * e + 2] = __builtin_fmaf(scale, v.z, S[nb][4 * e + 2]);
+                    S[nb][4 * e + 3] = __builtin_fmaf(scale, v.w, S[nb][4 * e + 3]);
+                }
+            f = uniform(f + a.decay[(size_t)(slot - m) * a.H + h]);
+        }
+    } else if (const void *init = a.init.of(p.seq)) {
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float4 v = load_state4(init, state_row + 32 * nb + 16 * (e >> 1) + 4 * (e & 1), ST);
+                S[nb][4 * e + 0] = v.x + 0.f;
+                S[nb][4 * e + 1] = v.y + 0.f;
+                S[nb][4 * e + 2] = v.z + 0.f;
+                S[nb][4 * e + 3] = v.w + 0.f;
+            }
+    }
+
+    const LaneMask mask = make_mask(i, q);
+    const uint32_t yoff = ld.x_own;
+    uint4 yr[kPassesX];
+    auto read_y = [&](const ResidentTile &T) {
+#pragma unroll
+        for (int m = 0; m < kPassesX; ++m)
+            yr[m] = *reinterpret_cast<const uint4 *>(&T.XY[ld.xr + kRowsX * m][ld.xc]);
+    };
+    auto store_y = [&](int tok0, int len) {
+        const rsrc_t ys = make_rsrc(yh + (size_t)tok0 * ld.x_row, (uint32_t)(len - 1) * ld.x_row + kResidentChannels * 2);
+        if (len == kQ) {
+#pragma unroll
+            for (int m = 0; m < kPassesX; ++m)
+                buf_store16(ys, yoff, kRowsX * m * ld.x_row, yr[m]);
+        } else {
+#pragma unroll
+            for (int m = 0; m < kPassesX; ++m)
+                if (ld.xr + kRowsX * m < len)
+                    buf_store16(ys, yoff, kRowsX * m * ld.x_row, yr[m]);
+        }
+    };
+    // A tile's rows from registers to LDS, a piece at a time; the registers then take the same piece of another tile.  A
+    // thread writes x where it has read y.
+    auto stage_x = [&](ResidentTile &T, int m) {
+        *reinterpret_cast<uint4 *>(&T.XY[ld.xr + kRowsX * m][ld.xc]) = regs.x[m];
+    };
+    auto stage_b = [&](ResidentTile &T, int m) {
+        *reinterpret_cast<uint4 *>(&T.Bs[ld.row + kRowsBC * m][ld.col]) = bf16x8_to_f16x8(regs.b[m]);
+    };
+    auto stage_c = [&](ResidentTile &T, int m) {
+        // token `row`, state indices col .. col + 7: lane (row % 32, (col / 8) % 2) of operand (row / 32, col / 16)
+        const int row = ld.row + kRowsBC * m;
+        T.Cf[(row >> 5) * 8 + (ld.col >> 4)][(row & 31) + 4 * (ld.col & 8)] = bf16x8_to_f16x8(regs.c[m]);
+    };
+    auto stage_dt = [&](ResidentTile &T) {
+        if (lane < 8)
+            *reinterpret_cast<uint2 *>(T.dt[ld.dt_tok]) = make_uint2(regs.dt[0], regs.dt[1]);
+    };
+    // the eight pieces of a tile
+    auto stage = [&](ResidentTile &T, int m) {
+        if (m < 4)
+            stage_x(T, m);
+        else if (m & 1)
+            stage_c(T, (m - 4) >> 1);
+        else
+            stage_b(T, (m - 4) >> 1);
+        if (m == 7)
+            stage_dt(T);
+    };
+    auto request = [&](int m) {
+        if (m < 4)
+            ld.load_x(regs, m);
+        else if (m & 1)
+            ld.load_c(regs, (m - 4) >> 1);
+        else
+            ld.load_b(regs, (m - 4) >> 1);
+        if (m == 7)
+            ld.load_dt(regs);
+    };
+    static_assert(kPassesX == 4 && kPassesBC == 2, "eight pieces");
+
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        stage(L.tile[0], m);
+    const bool two = p.tile_begin + 1 < p.tile_end;
+    if (two)
+        t_next = scalar_load(a.tiles + p.tile_begin + 1);
+    ld.start(t_next, two);
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        request(m);
+    int y_tok0 = 0, y_len = 0;  // the tile whose y waits in the other buffer
+    for (int k = p.tile_begin; k < p.tile_end; ++k) {
+        ResidentTile &T = L.tile[(k - p.tile_begin) & 1], &O = L.tile[~(k - p.tile_begin) & 1];
+        SsmTile t_after = t_next;
+        if (k + 2 < p.tile_end)
+            t_after = scalar_load(a.tiles + k + 2);
+        const float Dh = scalar_load(a.D + h);  // read per tile: what is made of it would fill 16 registers
+        lds_barrier();  // the tile is in place, the one before is done and its y in the other buffer
+        auto x_operand = [&](int ks) {
+            return lds_frag_tr(&T.XY[16 * ks + tr_row][32 * w + tr_col], &T.XY[16 * ks + tr_row + 4][32 * w + tr_col]);
+        };
+        auto float4_at = [&](const float *v) { return *reinterpret_cast<const float4 *>(v); };
+        // ---------------- raw score blocks Gm^T[j, i] = B_j . C_i: block 0 keys and queries 0..31, block 1 keys and queries
+        // 32..63, block 2 keys 0..31 and queries 32..63
+        if (w < 3) {
+            const int row = (w == 1 ? 32 : 0) + pi;
+            f32x16 acc = zero16();
+            uint4 bo[2], co[2];
+            auto load = [&](int ks) {
+                bo[ks & 1] = *reinterpret_cast<const uint4 *>(&T.Bs[row][16 * ks + 8 * q]);
+                co[ks & 1] = T.Cf[(w == 0 ? 0 : 8) + ks][lane];
+            };
+            load(0);
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) {
+                if (ks < 7)
+                    load(ks + 1);
+                acc = mfma_f16(bo[ks & 1], co[ks & 1], acc);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+                L.Gs[w][hf][lane] =
+                    make_uint4(pack2_f16(acc[8 * hf + 0], acc[8 * hf + 1]), pack2_f16(acc[8 * hf + 2], acc[8 * hf + 3]),
+                               pack2_f16(acc[8 * hf + 4], acc[8 * hf + 5]), pack2_f16(acc[8 * hf + 6], acc[8 * hf + 7]));
+        }
+        // The decay of tokens from `lo` on: the token's own step, the log2 decay up to and including it, that of token 31, the
+        // total.  The tables that follow hold e^{l_i - l_31} and e^{l_31 - l_j}, so the decay must stay inside the fp32
+        // exponent range (2^+-100 is far inside): if that of the whole tile does not, it is worked on in several passes, each
+        // over tokens that together decay by less, or over a single one, with their last token in the place of token 31.
+        // Tokens outside have a step of zero; returns the first behind.
+        auto window = [&](int lo, float &dtj, float &ell2, float &mid, float &last) {
+            const float step = step_of(T.dt, lane, hd, t.len);
+            dtj = lane >= lo ? step : 0.f;
+            ell2 = wave_inclusive_sum(dtj * Ah) * kLog2e;
+            last = read_lane(ell2, 63);
+            mid = read_lane(ell2, 31);
+            int hi = kQ;
+            if (__builtin_expect(!(last > -100.f), 0)) {
+                const bool in = wave_inclusive_sum(lane > lo && !(ell2 > -100.f) ? 1.f : 0.f) == 0.f;
+                hi = (int)read_lane(wave_inclusive_sum(in ? 1.f : 0.f), 63);  // lanes 0 .. hi - 1 are in
+                dtj = in ? dtj : 0.f;
+                ell2 = wave_inclusive_sum(dtj * Ah) * kLog2e;
+                last = mid = read_lane(ell2, 63);
+            }
+            return hi;
+        };
+        // Tokens [lo, returned) of the tile: their S.C, masked scores and Gm.x, y, and their update of the state.  That is the
+        // whole tile unless it decays by more than the factor tables can hold (see `window`).
+        auto pass = [&](int lo, auto first) {
+            constexpr bool kFirst = decltype(first)::value;
+            // ---------------- S.C from the state in front of the tokens, 16 state indices at a time; between the products the
+            // factor tables, y of the tile before, and x^T of the wave's channels weighted by decay
+            uint4 cf[2][2];
+            auto load_c = [&](int ks) {
+                cf[ks & 1][0] = T.Cf[ks][lane];
+                cf[ks & 1][1] = T.Cf[8 + ks][lane];
+            };
+            load_c(0);
+            load_c(1);
+            if (kFirst && y_len)
+                read_y(O);
+            float dtj, ell2, mid, last;
+            const int hi = window(lo, dtj, ell2, mid, last);
+            float dl = 0.f;
+            f32x16 Y[2] = {zero16(), zero16()};  // [token half]
+            uint4 xw[4], xb;
+            float4 wb[2];
+            auto load_x = [&](int ks) {
+                xb = x_operand(ks);
+                wb[0] = float4_at(&W.wt[16 * ks + 8 * q]);
+                wb[1] = float4_at(&W.wt[16 * ks + 8 * q + 4]);
+            };
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) {
+                const f32x16 &Sb = S[ks >> 1];
+                const int e = 8 * (ks & 1);
+                const uint4 s16 = make_uint4(pack2_f16(Sb[e + 0], Sb[e + 1]), pack2_f16(Sb[e + 2], Sb[e + 3]),
+                                             pack2_f16(Sb[e + 4], Sb[e + 5]), pack2_f16(Sb[e + 6], Sb[e + 7]));
+                Y[0] = mfma_f16(s16, cf[ks & 1][0], Y[0]);
+                Y[1] = mfma_f16(s16, cf[ks & 1][1], Y[1]);
+                if (ks + 2 < 8)
+                    load_c(ks + 2);
+                if (ks == 0) {
+                    W.wt[lane] = exp2_fast(last - ell2) * dtj;
+                    __builtin_amdgcn_wave_barrier();  // LDS executes a wave's accesses in order
+                }
+                if (ks == 1) {
+                    W.ei[lane] = exp2_fast(ell2);
+                    W.ri[lane] = exp2_fast(ell2 - mid);
+                }
+                if (ks == 2) {
+                    W.cf[lane] = exp2_fast(mid - ell2) * dtj;
+                    dl = exp2_fast(last);  // padded tokens have dt = 0, so this is e^{l_len}
+                }
+                if (ks >= 4)
+                    xw[ks - 4] = weighted(xb, wb[0], wb[1]);
+                if (ks >= 3 && ks < 7)
+                    load_x(ks - 3);
+                __builtin_amdgcn_sched_barrier(0);
+                if (kFirst && ks == 0 && y_len)
+                    store_y(y_tok0, y_len);
+            }
+            if constexpr (kFirst)
+                lds_barrier();  // the raw scores are in place
+            // ---------------- the decayed state accumulates the update, two blocks of 32 state indices x 16 tokens at a time;
+            // between the products the decay mask (+ D on the diagonal), which makes the operands of Gm.x:
+            // e^{l_i-l_j} dt_j = e^{l_i-l_31} * e^{l_31-l_j} dt_j from two factor tables
+            auto decay_state = [&](int nb) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    S[nb][e] *= dl;
+            };
+            uint4 bt[2];
+            auto load_b = [&](int st) {
+                const int n2 = st >> 2 << 1, ks = st & 3;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    bt[u] = lds_frag_tr(&T.Bs[16 * ks + tr_row][32 * (n2 + u) + tr_col],
+                                        &T.Bs[16 * ks + tr_row + 4][32 * (n2 + u) + tr_col]);
+            };
+            auto update = [&](int st) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    S[(st >> 2 << 1) + u] = mfma_f16(bt[u], xw[st & 3], S[(st >> 2 << 1) + u]);
+            };
+            const auto key_of = [&](int a) { return 16 * (a >> 1) + 8 * q + 4 * (a & 1); };
+            const float ri[2] = {W.ri[i], W.ri[32 + i]}, ei[2] = {W.ei[i], W.ei[32 + i]};
+            float4 key = float4_at(&W.cf[key_of(0)]);
+            uint4 raw = L.Gs[0][0][lane], g = make_uint4(0, 0, 0, 0);
+            load_b(0);
+            if constexpr (kFirst)
+                ld.start(t_after, k + 2 < p.tile_end);
+            decay_state(0);
+            decay_state(1);
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                Y[0][e] *= ei[0];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int st = 0; st < 8; ++st) {
+                const int blk = st >> 2, a = st & 3, nx = st + 1;
+                update(st);
+                if (nx < 8)
+                    load_b(nx);
+                if (a & 1)
+                    xb = x_operand(2 * blk + (a >> 1));
+                const float f[4] = {ri[blk] * key.x, ri[blk] * key.y, ri[blk] * key.z, ri[blk] * key.w};
+                key = nx < 8 ? float4_at(&W.cf[32 * (nx >> 2) + key_of(nx & 3)]) : float4_at(&W.cf[key_of(0)]);
+                const uint2 two = (a & 1) ? mask_quarter(raw.z, raw.w, f, a, mask, Dh) : mask_quarter(raw.x, raw.y, f, a, mask, Dh);
+                if (a & 1) {
+                    g.z = two.x, g.w = two.y;
+                    raw = L.Gs[nx >> 2][(nx & 3) >> 1][lane];
+                    Y[blk] = mfma_bf16(xb, g, Y[blk]);  // Gm.x is added onto e^{l_i} (S C_i)
+                } else {
+                    g.x = two.x, g.y = two.y;
+                }
+                if (st == 0)
+                    decay_state(2);
+                if (st == 1)
+                    decay_state(3);
+                if (st == 2 || st == 3)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        Y[1][8 * (st & 1) + e] *= ei[1];
+                if constexpr (kFirst) {  // the next tile into the other buffer, the rows of the one after requested
+                    stage(O, st);
+                    request(st);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // keys 0..31, queries 32..63: unmasked
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                auto pair = [&](uint32_t r, float u, float v) {
+                    return pack2_bf16(f16_lo(r) * (ri[1] * u), f16_hi(r) * (ri[1] * v));
+                };
+                const float4 k1 = float4_at(&W.cf[key_of(2 * ks + 1)]);
+                xb = x_operand(ks);
+                g = make_uint4(pair(raw.x, key.x, key.y), pair(raw.y, key.z, key.w), pair(raw.z, k1.x, k1.y), pair(raw.w, k1.z, k1.w));
+                if (ks == 0) {
+                    key = float4_at(&W.cf[key_of(2)]);
+                    raw = L.Gs[2][1][lane];
+                }
+                Y[1] = mfma_bf16(xb, g, Y[1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // ---------------- y over the wave's own columns of x: elements 8 hf .. 8 hf + 7 are channels 16 hf + 8 q .. + 7 of
+            // token 32 ih + i
+#pragma unroll
+            for (int ih = 0; ih < 2; ++ih)
+                if (32 * ih + i >= lo && 32 * ih + i < hi) {
+#pragma unroll
+                    for (int hf = 0; hf < 2; ++hf)
+                        *reinterpret_cast<uint4 *>(&T.XY[32 * ih + i][32 * w + 16 * hf + 8 * q]) = make_uint4(
+                            pack2_bf16(Y[ih][8 * hf + 0], Y[ih][8 * hf + 1]), pack2_bf16(Y[ih][8 * hf + 2], Y[ih][8 * hf + 3]),
+                            pack2_bf16(Y[ih][8 * hf + 4], Y[ih][8 * hf + 5]), pack2_bf16(Y[ih][8 * hf + 6], Y[ih][8 * hf + 7]));
+                }
+            __builtin_amdgcn_wave_barrier();  // another pass reads these columns
+            return hi;
+        };
+        int lo = pass(0, std::true_type());
+        while (__builtin_expect(lo < t.len, 0))
+            lo = pass(lo, std::false_type());
+        if (t.ckpt_slot >= 0) {
+            const size_t slot_row = (size_t)t.ckpt_slot * a.H * a.P * kN + state_row;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    store_state4(a.state_out, slot_row + 32 * nb + 16 * (e >> 1) + 4 * (e & 1),
+                                 make_float4(S[nb][4 * e], S[nb][4 * e + 1], S[nb][4 * e + 2], S[nb][4 * e + 3]), ST);
+        }
+        y_tok0 = t.tok0;
+        y_len = t.len;
+        t = t_next;
+        t_next = t_after;
+    }
+    lds_barrier();
+    read_y(L.tile[(p.tile_end - p.tile_begin - 1) & 1]);
+    store_y(y_tok0, y_len);
+}
+
+template <int ST>
+hipError_t launch_resident_st(const ssm_plan *plan, ResidentArgs a, const SsmPiece *d_pieces, hipStream_t stream)
+{
+    static std::once_flag attr_once[64];
+    static hipError_t attr_err[64];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess)
+        return e;
+    if (dev < 0 || dev >= 64)
+        return hipErrorInvalidDevice;
+    std::call_once(attr_once[dev], [&]() {
+        attr_err[dev] = hipFuncSetAttribute(reinterpret_cast<const void *>(ssm_scan_resident_kernel<ST>),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ResidentLds));
+    });
+    if (attr_err[dev] != hipSuccess)
+        return attr_err[dev];
+    if (plan->n_segments > 0) {
+        a.pieces = d_pieces + plan->n_pieces;
+        a.n_items = plan->n_segments * a.blocks;
+        hipLaunchKernelGGL(ssm_segment_state_kernel<ST>, dim3((unsigned)ssm_launch_blocks(a.n_items)), dim3(kThreads),
+                           sizeof(SegmentLds), stream, a);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+    }
+    if (hipEvent_t mark = ssm_profile_event(0))
+        if ((e = hipEventRecord(mark, stream)) != hipSuccess)
+            return e;
+    a.pieces = d_pieces;
+    a.n_items = plan->n_pieces * a.blocks;
+    hipLaunchKernelGGL(ssm_scan_resident_kernel<ST>, dim3((unsigned)ssm_launch_blocks(a.n_items)), dim3(kThreads),
+                       sizeof(ResidentLds), stream, a);
+    if ((e = hipGetLastError()) != hipSuccess)
+        return e;
+    if (hipEvent_t mark = ssm_profile_event(1))
+        e = hipEventRecord(mark, stream);
+    return e;
+}
+
+}  // namespace
+
+hipError_t launch_scan_resident(const ssm_plan *plan, const ScanArgs &args, const SsmPiece *d_pieces, void *workspace,
+                                hipStream_t stream)
+{
+    if (plan->n_pieces == 0)
+        return hipSuccess;
+    ResidentArgs a;
+    a.x = static_cast<const bf16_t *>(args.x);
+    a.dt = static_cast<const bf16_t *>(args.dt);
+    a.B = static_cast<const bf16_t *>(args.B);
+    a.C = static_cast<const bf16_t *>(args.C);
+    a.A = args.A;
+    a.D = args.D;
+    a.y = static_cast<bf16_t *>(args.y);
+    a.state_out = args.state_out;
+    a.init = state_ptrs_of(args.init_ptrs, args.host_ptrs, args.n_host_ptrs);
+    a.tiles = args.tiles;
+    a.carry = static_cast<float4 *>(workspace);
+    a.decay = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + ssm_piece_decay_offset(plan));
+    a.H = args.H;
+    a.P = args.P;
+    a.G = args.G;
+    a.blocks = args.H * args.P / kResidentChannels;
+    a.n_items = 0;
+    a.pieces = nullptr;
+    switch (args.state_dtype) {
+    case SSM_ST_F16: return launch_resident_st<SSM_ST_F16>(plan, a, d_pieces, stream);
+    case SSM_ST_BF16: return launch_resident_st<SSM_ST_BF16>(plan, a, d_pieces, stream);
+    default: return launch_resident_st<SSM_ST_F32>(plan, a, d_pieces, stream);
+    }
+}

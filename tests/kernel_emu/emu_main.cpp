@@ -7,6 +7,7 @@
 //   a 6th argument "advance" runs the roll-forward kernel instead of the scan: every sequence's state (its initial
 //   state, or zeros) is advanced in place, and the output holds y and then one state per sequence;
 //   a 7th argument f16 or bf16 keeps cached states in that type (converted from and to fp32 around the run)
+//   compiled with EMU_RESIDENT the scan is the one with resident states
 //   with EMU_WIDE set in the environment the matrix-core scan runs in its 64-channel variant
 #include <hip/hip_runtime.h>
 #include <cstdio>
@@ -118,6 +119,14 @@ int main(int argc, char **argv)
             fprintf(stderr, "stretches: %zu, carry slots: %d\n", plan->scan_seqs.size(), plan->n_carry);
         }
     }
+#ifdef EMU_RESIDENT
+    // EMU_PIECES, EMU_SEGMENTS: the most tiles per piece and per segment of the scan with resident states (the plan itself cuts only where that fills
+    // the GPU)
+    plan->resident = true;
+    ssm_plan_build_pieces(plan, getenv("EMU_PIECES") ? atoi(getenv("EMU_PIECES")) : 1 << 20,
+                          getenv("EMU_SEGMENTS") ? atoi(getenv("EMU_SEGMENTS")) : 1 << 20);
+    fprintf(stderr, "pieces: %d, segments: %d\n", plan->n_pieces, plan->n_segments);
+#endif
     const size_t nt = plan->tiles.size();
     SsmTile *tiles = static_cast<SsmTile *>(guarded(sizeof(SsmTile) * (nt ? nt : 1), end_aligned));
     SsmSeq *seqs = static_cast<SsmSeq *>(guarded(sizeof(SsmSeq) * (batch ? batch : 1), end_aligned));
@@ -184,8 +193,15 @@ int main(int argc, char **argv)
             memset(st_red, 0xFF, nck * st_esz);
             args.state_out = st_red;
         }
+#ifdef EMU_RESIDENT
+        const size_t np = plan->pieces.size();
+        SsmPiece *pieces = static_cast<SsmPiece *>(guarded(sizeof(SsmPiece) * (np ? np : 1), end_aligned));
+        memcpy(pieces, plan->pieces.data(), sizeof(SsmPiece) * np);
+        const hipError_t e = launch_scan_resident(plan, args, pieces, ws, nullptr);
+#else
         const hipError_t e = plan->path == SSM_PATH_MFMA_BF16 ? launch_scan_mfma(plan, args, ws, nullptr)
                                                               : launch_scan_valu(plan, args, nullptr);
+#endif
         if (e != hipSuccess) {
             fprintf(stderr, "launch failed\n");
             return 2;

@@ -159,6 +159,7 @@ static inline uint32_t emu_perm(uint32_t hi, uint32_t lo, uint32_t sel)
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
 #define __builtin_amdgcn_s_setprio(x) ((void)0)
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __builtin_amdgcn_wave_barrier() emu::wave_sync(__LINE__)  // LDS executes a wave's accesses in order
 #define __builtin_amdgcn_s_sleep(x) emu::wave_yield(__LINE__)
 #define __builtin_amdgcn_logf(x) log2f(x)
 

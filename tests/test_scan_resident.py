@@ -1,0 +1,107 @@
+"""The matrix-core scan with resident states (`scan_resident.hip`): on the CPU emulator against the oracle at the edges of
+its tiles, pieces and channel blocks, in any wave order and with guarded buffers; on the GPU where the plan takes it."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+from helpers import TOL, rel_err
+from test_kernel_emulation import CLANG, CSRC, EMU, ROOT, _convert, _emulate, _oracle, _with_empty_sequence
+from workloads import LayerShape, make_workload
+
+# name: (H, P, N, G, chunk), configuration of the generator, its overrides; every group is a multiple of 256 channels
+CASES = {
+    "ragged": ((4, 64, 128, 1, 64), 2, dict(batch=3, len_range=(1, 300))),
+    "long": ((4, 64, 128, 1, 64), 4, dict(seqlen=450, ckpt_every=100)),
+    "tiny": ((8, 64, 128, 2, 64), 2, dict(batch=2, len_range=(1, 3))),
+    "two_groups": ((8, 64, 128, 2, 32), 2, dict(batch=2, len_range=(20, 120))),
+    "p128": ((4, 128, 128, 2, 16), 4, dict(seqlen=130, ckpt_every=64)),
+    "empty_seq": ((4, 64, 128, 1, 64), 2, dict(batch=3, len_range=(30, 200))),
+    # decay up to 400 times the usual: the masks' exact branch, and pieces that nothing in front of them reaches
+    "strong_decay": ((4, 64, 128, 1, 64), 2, dict(batch=2, len_range=(60, 200), a_scale=[1.0, 40.0, 400.0, 0.01])),
+    # a hundredth of it: everything in front of a piece reaches all of it
+    "slow_decay": ((4, 64, 128, 1, 64), 2, dict(batch=2, len_range=(300, 400), a_scale=[0.01, 0.01, 0.02, 0.03])),
+}
+
+
+@pytest.fixture(scope="session")
+def emu_resident(tmp_path_factory):
+    if not os.path.exists(CLANG):
+        pytest.skip("no clang++ with bf16 vector support found")
+    d = str(tmp_path_factory.mktemp("emu_resident"))
+    srcs = [os.path.join(CSRC, "plan.cpp"), os.path.join(EMU, "emu_rt.cpp"), os.path.join(EMU, "emu_main.cpp")]
+    for name in ("scan_resident", "scan_valu", "state_advance"):
+        _convert(os.path.join(CSRC, name + ".hip"), os.path.join(d, name + ".cpp"))
+        srcs.append(os.path.join(d, name + ".cpp"))
+    flags = ["-std=c++17", "-O2", "-fno-strict-aliasing", "-ffp-contract=off", "-Wno-psabi", "-Wno-unused-value",
+             "-DEMU_RESIDENT", "-I", EMU, "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    objs = [os.path.join(d, os.path.basename(s) + ".o") for s in srcs]
+    procs = [subprocess.Popen([CLANG, *flags, "-c", s, "-o", o], stderr=subprocess.PIPE, text=True)
+             for s, o in zip(srcs, objs)]
+    for p in procs:
+        _, err = p.communicate()
+        assert p.returncode == 0, err[-3000:]
+    out = os.path.join(d, "emu_main")
+    subprocess.run([CLANG, *objs, "-o", out], check=True)
+    return out
+
+
+@pytest.mark.parametrize("most,segment", [(None, None), (1, 1), (2, 2), (3, 1)])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_emulated_scan_matches_oracle(emu_resident, tmp_path, monkeypatch, case, most, segment):
+    """`most`, `segment`: tiles per piece and per segment.  Tolerances as for the other matrix-core scan."""
+    dims, cfg, kw = CASES[case]
+    kw = dict(kw)
+    a_scale = kw.pop("a_scale", None)
+    wl = make_workload(cfg, "cpu", seed=11, shape=LayerShape(*dims, "bf16"), **kw)
+    if a_scale is not None:
+        wl.A = wl.A * torch.tensor(a_scale, dtype=wl.A.dtype)
+    if case == "empty_seq":
+        wl = _with_empty_sequence(wl)
+    init = list(wl.init_state)
+    y_ref, st_ref = _oracle(wl, init)
+    if most:
+        monkeypatch.setenv("EMU_PIECES", str(most))
+        monkeypatch.setenv("EMU_SEGMENTS", str(segment))
+    first = None
+    for order, align in ((0, "end"), (1, "start"), (7, "end")):
+        y, st, raw = _emulate(emu_resident, wl, init, tmp_path, order, align)
+        assert np.all(np.isfinite(y)) and np.all(np.isfinite(st))
+        assert max(rel_err(y, y_ref)) <= TOL["bf16"]
+        assert max(rel_err(st.astype(np.float64), st_ref)) <= TOL["bf16"]
+        first = raw if first is None else first
+        assert np.array_equal(first, raw), f"wave order {order} changes the result: LDS race"
+
+
+# on the GPU: batches that the plan gives to this scan, H, P, G, lengths, decay, type of the cached states
+GPU_CASES = {
+    "many_short": (32, 64, 2, [130, 65, 1, 64, 63, 0] * 48, 1.0, "f32"),   # several rounds of uncut pieces
+    "cut": (16, 64, 1, [33000], 1.0, "f32"),                               # pieces that start from segments
+    "cut_slow_decay": (16, 64, 1, [17001, 9000], 0.01, "f32"),             # whose segments all count
+    "p128_f16": (8, 128, 2, [20011, 15000], 1.0, "f16"),
+    "p256_bf16": (4, 256, 1, [24000], 1.0, "bf16"),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", sorted(GPU_CASES))
+def test_gpu_matches_oracle(case):
+    """Every head of every token and checkpoint.  The tolerances of reduced states add a rounding of the cached state and
+    one of the checkpoint, as in the stretches' tests."""
+    from helpers import gpu_run
+    from test_gpu_configs import compare_all_heads
+
+    H, P, G, lens, a_scale, state = GPU_CASES[case]
+    total = sum(lens)
+    wl = make_workload(2, "cuda", seed=61, batch=1, len_range=(total, total), shape=LayerShape(H, P, 128, G, 64, "bf16"))
+    wl.seqlens, wl.cu_seqlens = list(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    wl.ckpt_pos = [sorted({max(1, n // 3), n}) if n else [] for n in lens]
+    wl.A = wl.A * a_scale
+    kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[state]
+    init = [None if i % 2 else (0.5 * torch.randn(H, P, 128, device="cuda")).to(kind) for i in range(len(lens))]
+    ref = [None if v is None else v.float().cpu().numpy() for v in init]
+    y, states, info = gpu_run(wl, init, state_dtype=state)
+    assert info.path == 1
+    compare_all_heads(wl, y, states.float(), ref, tol={"f32": TOL["bf16"], "f16": 2e-2, "bf16": 2.5e-2}[state], block=H)
