@@ -25,6 +25,8 @@ constexpr int kConvThreads = 256;
 constexpr int kConvMaxK = 4;
 // Rows of a group.  177 VGPRs, two waves per SIMD; 4 rows (133 VGPRs, three) 282 us where 8 take 270 (below), 12 rows 275.
 constexpr int kAhead = 8;
+constexpr int kConvMostParts = 8;  // tiles have up to 64 tokens
+constexpr int kConvWorkgroups = 512;
 
 __device__ __forceinline__ uint4 load16(const void *p) { return *static_cast<const uint4 *>(p); }
 
@@ -68,20 +70,30 @@ struct ConvArgs {
     const SsmTile *tiles;
     const SsmSeq *seqs;
     int Cch, act, n_tiles, blocks_per_tile;
+    int parts;                      // a tile's tokens are dealt to this many workgroups per channel block
 };
 
 template <typename IO, int K>
 __global__ __launch_bounds__(kConvThreads, 2) void ssm_conv1d_kernel(ConvArgs a)
 {
     constexpr int V = ConvVec<IO>::kLanes;
-    const int tile = blockIdx.x / a.blocks_per_tile;
-    const int cb = blockIdx.x % a.blocks_per_tile;
+    const int cb = blockIdx.x % a.blocks_per_tile, part_of_all = blockIdx.x / a.blocks_per_tile;
+    const int tile = part_of_all / a.parts, part = part_of_all % a.parts;
     const int c0 = (cb * kConvThreads + threadIdx.x) * V;  // first channel of this thread
     const int Cch = a.Cch;
     if (tile >= a.n_tiles || c0 >= Cch)
         return;  // no barriers in this kernel: threads may leave on their own
-    const SsmTile t = a.tiles[tile];
+    SsmTile t = a.tiles[tile];
     const int seq_tok0 = a.tiles[a.seqs[t.seq].tile_begin].tok0;
+    if (a.parts > 1) {  // from here on the part is the tile: whole groups, the last part writes the checkpoint
+        const int own = (t.len + a.parts * kAhead - 1) / (a.parts * kAhead) * kAhead, skip = part * own;
+        if (skip >= t.len)
+            return;
+        const bool last = t.len - skip <= own;
+        t.tok0 += skip;
+        t.len = last ? t.len - skip : own;
+        t.ckpt_slot = last ? t.ckpt_slot : -1;
+    }
     const int lp = t.tok0 - seq_tok0;  // tokens of this sequence in front of the tile
 
     const IO *__restrict__ in = static_cast<const IO *>(a.in);  // the caller keeps in and out apart
@@ -100,6 +112,13 @@ __global__ __launch_bounds__(kConvThreads, 2) void ssm_conv1d_kernel(ConvArgs a)
     // hist[j] = the input j+1 tokens in front of the current one (j = 0 newest); K entries so that the state,
     // which also holds the input K-1 places back from its last token, can be written from registers
     float hist[K][V];
+    // [channel][entry] of the thread's channels: K pieces of 16 bytes (element by element 64 one-token sequences took 24 us
+    // where they take 11)
+    float state[K * V];
+#pragma unroll
+    for (int p = 0; p < K; ++p)
+        if (init && lp < K)
+            ConvVec<IO>::unpack(load16(init + (size_t)c0 * K + p * V), state + p * V);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
 #pragma unroll
@@ -109,13 +128,13 @@ __global__ __launch_bounds__(kConvThreads, 2) void ssm_conv1d_kernel(ConvArgs a)
         if (lp - back >= 0) {
             ConvVec<IO>::unpack(load16(in + (size_t)(t.tok0 - back) * Cch + c0), hist[j]);
         } else if (init) {
-            // sequence-local index lp + 1 - back <= 0 is entry K - 1 + (lp + 1 - back) of the cached state
-            const int m = K - 1 + (lp + 1 - back);
-            if (m >= 0) {
+            // sequence-local index lp - back < 0 is entry K + lp - back of the cached state
 #pragma unroll
-                for (int e = 0; e < V; ++e)
-                    hist[j][e] = IoTraits<IO>::load(init + (size_t)(c0 + e) * K + m);
-            }
+            for (int m = 0; m < K; ++m)
+                if (m == K + lp - back)
+#pragma unroll
+                    for (int e = 0; e < V; ++e)
+                        hist[j][e] = state[e * K + m];
         }
     }
 
@@ -177,7 +196,10 @@ __global__ __launch_bounds__(kConvThreads, 2) void ssm_conv1d_kernel(ConvArgs a)
         for (int e = 0; e < V; ++e)
 #pragma unroll
             for (int m = 0; m < K; ++m)
-                IoTraits<IO>::store(st + (size_t)e * K + m, hist[K - 1 - m][e]);
+                state[e * K + m] = hist[K - 1 - m][e];
+#pragma unroll
+        for (int p = 0; p < K; ++p)
+            ConvVec<IO>::store(st + p * V, state + p * V);
     }
 }
 
@@ -217,7 +239,15 @@ hipError_t launch_conv1d_prefill(const ssm_plan *plan, const SsmTile *d_tiles, c
     a.act = act;
     a.n_tiles = n_tiles;
     a.blocks_per_tile = (channels + kConvThreads * v - 1) / (kConvThreads * v);
-    const dim3 grid((unsigned)n_tiles * (unsigned)a.blocks_per_tile);
+    // Few tiles leave most of the chip idle, and each is a serial walk: they are cut into parts, of no less than a group of
+    // rows for tiles of average length, up to kConvWorkgroups workgroups in all.  Whole tiles and in parts, bf16: 500 tokens
+    // of 5376 channels 23 and 8 us, 2048 25 and 17 (1024 workgroups: 21), 4096 26 and 24 (32); 32768 tokens of 10240
+    // channels, 2560 workgroups, 270 and, cut in two, 274.
+    a.parts = 1;
+    while (a.parts < kConvMostParts && (int64_t)n_tiles * a.blocks_per_tile * a.parts * 2 <= kConvWorkgroups &&
+           plan->total_tokens > (int64_t)n_tiles * a.parts * kAhead)
+        a.parts *= 2;
+    const dim3 grid((unsigned)n_tiles * (unsigned)a.parts * (unsigned)a.blocks_per_tile);
     const bool f32 = plan->shape.io_dtype == SSM_DT_F32;
 #define SSM_CONV_LAUNCH(KW)                                                                                  \
     case KW:                                                                                                 \

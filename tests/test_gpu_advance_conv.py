@@ -105,3 +105,15 @@ def test_conv1d(io, case, K):
                                             ckpts, silu=True)
     assert max(rel_err(out.float().cpu().numpy(), out_ref)) <= (5e-3 if io == "bf16" else 1e-5)
     assert np.array_equal(st[:n_ck].float().cpu().numpy().astype(np.float64), st_ref)
+
+
+# Few tiles, which the kernel cuts into parts of whole groups of 8 tokens: lengths around a group, a part and a tile, and
+# checkpoints that end a part early.
+CONV["parts"] = ((2, 64, 128, 1, 64), [1, 7, 8, 9, 0, 16, 17, 33, 63, 64, 65, 130],
+                 [[1], [4, 7], [8], [], [], [15, 16], [17], [31, 32, 33], [60, 63], [64], [64, 65], [3, 9, 129]])
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4])
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_conv1d_of_tiles_in_parts(io, K):
+    test_conv1d(io, "parts", K)
