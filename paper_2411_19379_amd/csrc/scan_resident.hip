@@ -208,22 +208,6 @@ __device__ __forceinline__ size_t carry_at(const ResidentArgs &a, int slot, int 
     return ((size_t)slot * ((size_t)a.H * a.P / 32) + cw / 32) * (16 * 64);
 }
 
-// A word or a table entry at a uniform address that no kernel of the call writes: read with scalar loads, which wait for no
-// vector memory access in flight.
-template <typename T> __device__ __forceinline__ T scalar_load(const T *p)
-{
-    static_assert(sizeof(T) % 4 == 0, "whole words");
-    typedef const uint32_t __attribute__((address_space(4))) constant_u32;
-    const constant_u32 *c = (const constant_u32 *)(uint64_t)p;
-    uint32_t w[sizeof(T) / 4];
-#pragma unroll
-    for (unsigned k = 0; k < sizeof(T) / 4; ++k)
-        w[k] = c[k];
-    T v;
-    __builtin_memcpy(&v, w, sizeof(T));
-    return v;
-}
-
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float uniform(float v) { return read_lane(v, 0); }
 

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(64 * NW, f32_waves_per_simd(NB, NC)) void ssm_scan_
             tok0 = tok_begin + 16 * k;
             len = n_tok - 16 * k < 16 ? n_tok - 16 * k : 16;
         } else {
-            const SsmTile t = a.tiles[sq.tile_begin + k];
+            const SsmTile t = scalar_load(a.tiles + sq.tile_begin + k);
             tok0 = t.tok0, len = t.len, ckpt = t.ckpt_slot;
         }
         // rows past the end of a partial tile re-read its last row
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(64 * NW, split_waves_per_simd(NB, NC, NW)) void ssm
             tok0 = tok_begin + kUnit * k;
             len = n_tok - kUnit * k < kUnit ? n_tok - kUnit * k : kUnit;
         } else {
-            const SsmTile t = a.tiles[sq.tile_begin + k];
+            const SsmTile t = scalar_load(a.tiles + sq.tile_begin + k);
             tok0 = t.tok0, len = t.len, ckpt = t.ckpt_slot;
         }
         tok0 = __builtin_amdgcn_readfirstlane(tok0);
