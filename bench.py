@@ -39,19 +39,25 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # (profiles/ssm_scan_mfma_kernel_cfg3_cfg4_hbm_bytes.txt gives the commands and the raw
 # readings): FETCH_SIZE and WRITE_SIZE in KiB per dispatch, each divided by
 # what the same counter reads per KiB actually moved by the 1 GiB copy of
-# --calibrate-copy.  Keyed by the hash of the kernel source the counters were
-# taken on: once that source changes the figure is reported as null.
+# --calibrate-copy, and the kernel they were read of.  Keyed by the hash of the kernel
+# sources the counters were taken on: once those change the figure is reported as null.
+SCAN_SOURCES = ("scan_mfma.hip", "mfma_utils.h", "scan_resident.hip")
 MEASURED_TRAFFIC = {
-    "682cfa135dec00dc869f78d1da5d7f28963480dd": {
-        "cfg3_7b_32k_bf16": {"fetch_bytes": 842566718, "write_bytes": 546155867},
-        "cfg4_7b_128k_ckpt4096_bf16": {"fetch_bytes": 3464737562, "write_bytes": 2289232919},
+    "bfd83cbd3ddb42245a1968c8e90b6589b66cba77": {
+        "cfg2_varlen16_bf16": {"fetch_bytes": 755449856, "write_bytes": 691262464, "kernel": "ssm_scan_mfma_kernel"},
+        "cfg3_7b_32k_bf16": {"fetch_bytes": 843251712, "write_bytes": 546151424, "kernel": "ssm_scan_mfma_kernel"},
+        "cfg4_7b_128k_ckpt4096_bf16": {"fetch_bytes": 2772152320, "write_bytes": 2283274240,
+                                       "kernel": "ssm_scan_resident_kernel"},
     },
 }
 
 
 def kernel_source_hash() -> str:
-    with open(os.path.join(ROOT, "paper_2411_19379_amd", "csrc", "scan_mfma.hip"), "rb") as f:
-        return hashlib.sha1(f.read()).hexdigest()
+    digest = hashlib.sha1()
+    for name in SCAN_SOURCES:
+        with open(os.path.join(ROOT, "paper_2411_19379_amd", "csrc", name), "rb") as f:
+            digest.update(f.read())
+    return digest.hexdigest()
 
 
 def algorithmic_bytes(wl, n_ckpt: int) -> int:
@@ -293,10 +299,12 @@ def main() -> int:
     achieved = abytes / (kern_ms * 1e-3) / 1e9
     flops = algorithmic_flops(wl, plan.info.tile_tokens)
     traffic = None
+    # which of the two the plan took is not part of its interface; the counters say it
+    kernel = "ssm_scan_mfma_kernel or ssm_scan_resident_kernel" if mfma else "ssm_scan_f32_kernel"
     if mfma:
         m = MEASURED_TRAFFIC.get(kernel_source_hash(), {}).get(wl.name + ("_nockpt" if args.no_checkpoints else ""))
         if m:
-            traffic = m["fetch_bytes"] + m["write_bytes"]
+            traffic, kernel = m["fetch_bytes"] + m["write_bytes"], m["kernel"]
     out = {
         "metric": "SSM-layer prefill tokens/s (1 GPU) with state checkpoints",
         "value": T / (ms_per_step * 1e-3),
@@ -320,10 +328,10 @@ def main() -> int:
                    "call_ms_min": float(call_ms.min()), "ms_per_step_with_events": events_ms_per_step},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "ssm_scan_mfma_kernel" if mfma else "ssm_scan_f32_kernel",
+                     "kernel": kernel,
                      "kernel_ms": kern_ms, "kernel_ms_median": float(np.median(scan_ms)),
                      "kernel_ms_min": float(scan_ms.min()),
-                     "prep_kernel": "ssm_prep_kernel" if mfma else None, "prep_kernel_ms": float(prep_ms.mean()),
+                     "prep_kernel": None if not mfma else "ssm_segment_state_kernel" if "resident" in kernel else "ssm_prep_kernel", "prep_kernel_ms": float(prep_ms.mean()),
                      "carry_kernels_ms": float(tail_ms.mean()),
                      "algorithmic_bytes": abytes,
                      "whole_call_frac": abytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,

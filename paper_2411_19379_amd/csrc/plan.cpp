@@ -3,10 +3,10 @@
 #include "plan.h"
 
 #include <algorithm>
-#include <functional>
-#include <queue>
 #include <cstdio>
 #include <cstring>
+#include <functional>
+#include <map>
 #include <new>
 #include <numeric>
 
@@ -352,21 +352,23 @@ static double ssm_busiest(const std::vector<int64_t> &lengths, int64_t copies, i
     const double share = (double)all * copies / places;
     const int64_t n = (int64_t)lengths.size() * copies, longest = lengths.empty() ? 0 : lengths[0];
     double busiest = (double)longest;
-    if (n > 16 * places) {
+    if (n > 64 * places) {
         busiest = std::max(busiest, share + 0.25 * longest);
     } else if (n > places) {
-        std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> ends;
-        for (int64_t i = 0; i < places; ++i)
-            ends.push(0);
-        int64_t last = 0;
+        std::map<int64_t, int64_t> ends;  // when places become free: how many
+        ends[0] = places;
         for (int64_t v : lengths)
-            for (int64_t c = 0; c < copies; ++c) {
-                const int64_t end = ends.top() + v;
-                ends.pop();
-                ends.push(end);
-                last = std::max(last, end);
+            for (int64_t left = copies; v > 0 && left > 0;) {
+                const auto first = ends.begin();
+                const int64_t end = first->first + v, taken = std::min(left, first->second);
+                left -= taken;
+                if (taken == first->second)
+                    ends.erase(first);
+                else
+                    first->second -= taken;
+                ends[end] += taken;
             }
-        busiest = (double)last;
+        busiest = (double)ends.rbegin()->first;
     }
     *fill = busiest > 0 ? share / busiest : 1.0;
     return busiest;
