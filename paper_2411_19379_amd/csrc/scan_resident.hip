@@ -71,6 +71,7 @@ struct ResidentTile {
 struct ResidentLds {
     ResidentTile tile[2];
     uint4 Gs[3][2][64];             // raw score blocks as accumulator images, fp16
+    uint4 none[2][2][64];           // zeros in the place of the first two
     ResidentTables tb[kWaves];
 };
 constexpr int kWindows = 2 * kWaves;  // of 64 tokens, looked back over at a time
@@ -200,6 +201,13 @@ __device__ __forceinline__ float step_of(const uint32_t (*dt)[2], int lane, int 
 {
     const uint32_t u = dt[lane][hd >> 1];
     return lane < len ? __uint_as_float((hd & 1) ? u & 0xffff0000u : u << 16) : 0.f;
+}
+
+// l log2(e), rounded before anything is subtracted from it, as in the other scan: both give a token the same weight.
+__device__ __forceinline__ float to_log2(float l)
+{
+#pragma clang fp contract(off)
+    return l * kLog2e;
 }
 
 // The accumulator images of a slot, from channel cw on, in float4 units: + 16 * 64 per 32 channels, + (4 nb + a) 64 + lane.
@@ -555,6 +563,8 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
     };
     static_assert(kPassesX == 4 && kPassesBC == 2, "eight pieces");
 
+    for (int m = threadIdx.x; m < 4 * 64; m += kThreads)
+        L.none[0][0][m] = make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int m = 0; m < 8; ++m)
         stage(L.tile[0], m);
@@ -601,184 +611,181 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
                     make_uint4(pack2_f16(acc[8 * hf + 0], acc[8 * hf + 1]), pack2_f16(acc[8 * hf + 2], acc[8 * hf + 3]),
                                pack2_f16(acc[8 * hf + 4], acc[8 * hf + 5]), pack2_f16(acc[8 * hf + 6], acc[8 * hf + 7]));
         }
-        // The decay of tokens from `lo` on: the token's own step, the log2 decay up to and including it, that of token 31, the
-        // total.  The tables that follow hold e^{l_i - l_31} and e^{l_31 - l_j}, so the decay must stay inside the fp32
-        // exponent range (2^+-100 is far inside): if that of the whole tile does not, it is worked on in several passes, each
-        // over tokens that together decay by less, or over a single one, with their last token in the place of token 31.
-        // Tokens outside have a step of zero; returns the first behind.
-        auto window = [&](int lo, float &dtj, float &ell2, float &mid, float &last) {
-            const float step = step_of(T.dt, lane, hd, t.len);
-            dtj = lane >= lo ? step : 0.f;
-            ell2 = wave_inclusive_sum(dtj * Ah) * kLog2e;
-            last = read_lane(ell2, 63);
-            mid = read_lane(ell2, 31);
-            int hi = kQ;
-            if (__builtin_expect(!(last > -100.f), 0)) {
-                const bool in = wave_inclusive_sum(lane > lo && !(ell2 > -100.f) ? 1.f : 0.f) == 0.f;
-                hi = (int)read_lane(wave_inclusive_sum(in ? 1.f : 0.f), 63);  // lanes 0 .. hi - 1 are in
-                dtj = in ? dtj : 0.f;
-                ell2 = wave_inclusive_sum(dtj * Ah) * kLog2e;
-                last = mid = read_lane(ell2, 63);
-            }
-            return hi;
+        // ---------------- S.C from the state in front of the tokens, 16 state indices at a time; between the products the
+        // factor tables, y of the tile before, and x^T of the wave's channels weighted by decay
+        uint4 cf[2][2];
+        auto load_c = [&](int ks) {
+            cf[ks & 1][0] = T.Cf[ks][lane];
+            cf[ks & 1][1] = T.Cf[8 + ks][lane];
         };
-        // Tokens [lo, returned) of the tile: their S.C, masked scores and Gm.x, y, and their update of the state.  That is the
-        // whole tile unless it decays by more than the factor tables can hold (see `window`).
-        auto pass = [&](int lo, auto first) {
-            constexpr bool kFirst = decltype(first)::value;
-            // ---------------- S.C from the state in front of the tokens, 16 state indices at a time; between the products the
-            // factor tables, y of the tile before, and x^T of the wave's channels weighted by decay
-            uint4 cf[2][2];
-            auto load_c = [&](int ks) {
-                cf[ks & 1][0] = T.Cf[ks][lane];
-                cf[ks & 1][1] = T.Cf[8 + ks][lane];
-            };
-            load_c(0);
-            load_c(1);
-            if (kFirst && y_len)
-                read_y(O);
-            float dtj, ell2, mid, last;
-            const int hi = window(lo, dtj, ell2, mid, last);
-            float dl = 0.f;
-            f32x16 Y[2] = {zero16(), zero16()};  // [token half]
-            uint4 xw[4], xb;
-            float4 wb[2];
-            auto load_x = [&](int ks) {
-                xb = x_operand(ks);
-                wb[0] = float4_at(&W.wt[16 * ks + 8 * q]);
-                wb[1] = float4_at(&W.wt[16 * ks + 8 * q + 4]);
-            };
+        load_c(0);
+        load_c(1);
+        if (y_len)
+            read_y(O);
+        // The token's step, the log2 decay up to and including it, that of token 31, the total.
+        const float dtj = step_of(T.dt, lane, hd, t.len);
+        const float ell2 = to_log2(wave_inclusive_sum(dtj * Ah)), mid = read_lane(ell2, 31), last = read_lane(ell2, 63);
+        // The factors e^{l_i - l_31} and e^{l_31 - l_j} of the diagonal blocks must stay inside the fp32 exponent range
+        // (2^+-100 is far inside).  If they do not, the blocks' scores and their factors are zeros here, and what the
+        // blocks contribute is added behind the others; the factors of the third block are at most 1 whatever the decay.
+        const bool fast = mid > -100.f && last - mid > -100.f;
+        const uint4 *diag = fast ? &L.Gs[0][0][lane] : &L.none[0][0][lane];
+        float dl = 0.f;
+        f32x16 Y[2] = {zero16(), zero16()};  // [token half]
+        uint4 xw[4], xb;
+        float4 wb[2];
+        auto load_x = [&](int ks) {
+            xb = x_operand(ks);
+            wb[0] = float4_at(&W.wt[16 * ks + 8 * q]);
+            wb[1] = float4_at(&W.wt[16 * ks + 8 * q + 4]);
+        };
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                const f32x16 &Sb = S[ks >> 1];
-                const int e = 8 * (ks & 1);
-                const uint4 s16 = make_uint4(pack2_f16(Sb[e + 0], Sb[e + 1]), pack2_f16(Sb[e + 2], Sb[e + 3]),
-                                             pack2_f16(Sb[e + 4], Sb[e + 5]), pack2_f16(Sb[e + 6], Sb[e + 7]));
-                Y[0] = mfma_f16(s16, cf[ks & 1][0], Y[0]);
-                Y[1] = mfma_f16(s16, cf[ks & 1][1], Y[1]);
-                if (ks + 2 < 8)
-                    load_c(ks + 2);
-                if (ks == 0) {
-                    W.wt[lane] = exp2_fast(last - ell2) * dtj;
-                    __builtin_amdgcn_wave_barrier();  // LDS executes a wave's accesses in order
-                }
-                if (ks == 1) {
-                    W.ei[lane] = exp2_fast(ell2);
-                    W.ri[lane] = exp2_fast(ell2 - mid);
-                }
-                if (ks == 2) {
-                    W.cf[lane] = exp2_fast(mid - ell2) * dtj;
-                    dl = exp2_fast(last);  // padded tokens have dt = 0, so this is e^{l_len}
-                }
-                if (ks >= 4)
-                    xw[ks - 4] = weighted(xb, wb[0], wb[1]);
-                if (ks >= 3 && ks < 7)
-                    load_x(ks - 3);
-                __builtin_amdgcn_sched_barrier(0);
-                if (kFirst && ks == 0 && y_len)
-                    store_y(y_tok0, y_len);
+        for (int ks = 0; ks < 8; ++ks) {
+            const f32x16 &Sb = S[ks >> 1];
+            const int e = 8 * (ks & 1);
+            const uint4 s16 = make_uint4(pack2_f16(Sb[e + 0], Sb[e + 1]), pack2_f16(Sb[e + 2], Sb[e + 3]),
+                                         pack2_f16(Sb[e + 4], Sb[e + 5]), pack2_f16(Sb[e + 6], Sb[e + 7]));
+            Y[0] = mfma_f16(s16, cf[ks & 1][0], Y[0]);
+            Y[1] = mfma_f16(s16, cf[ks & 1][1], Y[1]);
+            if (ks + 2 < 8)
+                load_c(ks + 2);
+            if (ks == 0) {
+                W.wt[lane] = exp2_fast(last - ell2) * dtj;
+                __builtin_amdgcn_wave_barrier();  // LDS executes a wave's accesses in order
             }
-            if constexpr (kFirst)
-                lds_barrier();  // the raw scores are in place
-            // ---------------- the decayed state accumulates the update, two blocks of 32 state indices x 16 tokens at a time;
-            // between the products the decay mask (+ D on the diagonal), which makes the operands of Gm.x:
-            // e^{l_i-l_j} dt_j = e^{l_i-l_31} * e^{l_31-l_j} dt_j from two factor tables
-            auto decay_state = [&](int nb) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    S[nb][e] *= dl;
-            };
-            uint4 bt[2];
-            auto load_b = [&](int st) {
-                const int n2 = st >> 2 << 1, ks = st & 3;
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    bt[u] = lds_frag_tr(&T.Bs[16 * ks + tr_row][32 * (n2 + u) + tr_col],
-                                        &T.Bs[16 * ks + tr_row + 4][32 * (n2 + u) + tr_col]);
-            };
-            auto update = [&](int st) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    S[(st >> 2 << 1) + u] = mfma_f16(bt[u], xw[st & 3], S[(st >> 2 << 1) + u]);
-            };
-            const auto key_of = [&](int a) { return 16 * (a >> 1) + 8 * q + 4 * (a & 1); };
-            const float ri[2] = {W.ri[i], W.ri[32 + i]}, ei[2] = {W.ei[i], W.ei[32 + i]};
-            float4 key = float4_at(&W.cf[key_of(0)]);
-            uint4 raw = L.Gs[0][0][lane], g = make_uint4(0, 0, 0, 0);
-            load_b(0);
-            if constexpr (kFirst)
-                ld.start(t_after, k + 2 < p.tile_end);
-            decay_state(0);
-            decay_state(1);
+            if (ks == 1) {
+                W.ei[lane] = exp2_fast(ell2);
+                W.ri[lane] = exp2_fast(ell2 - mid);
+            }
+            if (ks == 2) {
+                W.cf[lane] = exp2_fast(mid - ell2) * dtj;
+                dl = exp2_fast(last);  // padded tokens have dt = 0, so this is e^{l_len}
+            }
+            if (ks >= 4)
+                xw[ks - 4] = weighted(xb, wb[0], wb[1]);
+            if (ks >= 3 && ks < 7)
+                load_x(ks - 3);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks == 0 && y_len)
+                store_y(y_tok0, y_len);
+            if (ks == 2 && __builtin_expect(!fast, 0)) {
+                W.ri[lane & 31] = 0.f;
+                W.cf[lane | 32] = 0.f;
+            }
+        }
+        lds_barrier();  // the raw scores are in place
+        // ---------------- the decayed state accumulates the update, two blocks of 32 state indices x 16 tokens at a time;
+        // between the products the decay mask (+ D on the diagonal), which makes the operands of Gm.x:
+        // e^{l_i-l_j} dt_j = e^{l_i-l_31} * e^{l_31-l_j} dt_j from two factor tables
+        auto decay_state = [&](int nb) {
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                Y[0][e] *= ei[0];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int st = 0; st < 8; ++st) {
-                const int blk = st >> 2, a = st & 3, nx = st + 1;
-                update(st);
-                if (nx < 8)
-                    load_b(nx);
-                if (a & 1)
-                    xb = x_operand(2 * blk + (a >> 1));
-                const float f[4] = {ri[blk] * key.x, ri[blk] * key.y, ri[blk] * key.z, ri[blk] * key.w};
-                key = nx < 8 ? float4_at(&W.cf[32 * (nx >> 2) + key_of(nx & 3)]) : float4_at(&W.cf[key_of(0)]);
-                const uint2 two = (a & 1) ? mask_quarter(raw.z, raw.w, f, a, mask, Dh) : mask_quarter(raw.x, raw.y, f, a, mask, Dh);
-                if (a & 1) {
-                    g.z = two.x, g.w = two.y;
-                    raw = L.Gs[nx >> 2][(nx & 3) >> 1][lane];
-                    Y[blk] = mfma_bf16(xb, g, Y[blk]);  // Gm.x is added onto e^{l_i} (S C_i)
-                } else {
-                    g.x = two.x, g.y = two.y;
-                }
-                if (st == 0)
-                    decay_state(2);
-                if (st == 1)
-                    decay_state(3);
-                if (st == 2 || st == 3)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        Y[1][8 * (st & 1) + e] *= ei[1];
-                if constexpr (kFirst) {  // the next tile into the other buffer, the rows of the one after requested
-                    stage(O, st);
-                    request(st);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // keys 0..31, queries 32..63: unmasked
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                auto pair = [&](uint32_t r, float u, float v) {
-                    return pack2_bf16(f16_lo(r) * (ri[1] * u), f16_hi(r) * (ri[1] * v));
-                };
-                const float4 k1 = float4_at(&W.cf[key_of(2 * ks + 1)]);
-                xb = x_operand(ks);
-                g = make_uint4(pair(raw.x, key.x, key.y), pair(raw.y, key.z, key.w), pair(raw.z, k1.x, k1.y), pair(raw.w, k1.z, k1.w));
-                if (ks == 0) {
-                    key = float4_at(&W.cf[key_of(2)]);
-                    raw = L.Gs[2][1][lane];
-                }
-                Y[1] = mfma_bf16(xb, g, Y[1]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            // ---------------- y over the wave's own columns of x: elements 8 hf .. 8 hf + 7 are channels 16 hf + 8 q .. + 7 of
-            // token 32 ih + i
-#pragma unroll
-            for (int ih = 0; ih < 2; ++ih)
-                if (32 * ih + i >= lo && 32 * ih + i < hi) {
-#pragma unroll
-                    for (int hf = 0; hf < 2; ++hf)
-                        *reinterpret_cast<uint4 *>(&T.XY[32 * ih + i][32 * w + 16 * hf + 8 * q]) = make_uint4(
-                            pack2_bf16(Y[ih][8 * hf + 0], Y[ih][8 * hf + 1]), pack2_bf16(Y[ih][8 * hf + 2], Y[ih][8 * hf + 3]),
-                            pack2_bf16(Y[ih][8 * hf + 4], Y[ih][8 * hf + 5]), pack2_bf16(Y[ih][8 * hf + 6], Y[ih][8 * hf + 7]));
-                }
-            __builtin_amdgcn_wave_barrier();  // another pass reads these columns
-            return hi;
+                S[nb][e] *= dl;
         };
-        int lo = pass(0, std::true_type());
-        while (__builtin_expect(lo < t.len, 0))
-            lo = pass(lo, std::false_type());
+        uint4 bt[2];
+        auto load_b = [&](int st) {
+            const int n2 = st >> 2 << 1, ks = st & 3;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                bt[u] = lds_frag_tr(&T.Bs[16 * ks + tr_row][32 * (n2 + u) + tr_col],
+                                    &T.Bs[16 * ks + tr_row + 4][32 * (n2 + u) + tr_col]);
+        };
+        auto update = [&](int st) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                S[(st >> 2 << 1) + u] = mfma_f16(bt[u], xw[st & 3], S[(st >> 2 << 1) + u]);
+        };
+        const auto key_of = [&](int a) { return 16 * (a >> 1) + 8 * q + 4 * (a & 1); };
+        const float ri[2] = {W.ri[i], W.ri[32 + i]}, ei[2] = {W.ei[i], W.ei[32 + i]};
+        float4 key = float4_at(&W.cf[key_of(0)]);
+        uint4 raw = diag[0], g = make_uint4(0, 0, 0, 0);
+        load_b(0);
+        ld.start(t_after, k + 2 < p.tile_end);
+        decay_state(0);
+        decay_state(1);
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            Y[0][e] *= ei[0];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int st = 0; st < 8; ++st) {
+            const int blk = st >> 2, a = st & 3, nx = st + 1;
+            update(st);
+            if (nx < 8)
+                load_b(nx);
+            if (a & 1)
+                xb = x_operand(2 * blk + (a >> 1));
+            const float f[4] = {ri[blk] * key.x, ri[blk] * key.y, ri[blk] * key.z, ri[blk] * key.w};
+            key = nx < 8 ? float4_at(&W.cf[32 * (nx >> 2) + key_of(nx & 3)]) : float4_at(&W.cf[key_of(0)]);
+            const uint2 two = (a & 1) ? mask_quarter(raw.z, raw.w, f, a, mask, Dh) : mask_quarter(raw.x, raw.y, f, a, mask, Dh);
+            if (a & 1) {
+                g.z = two.x, g.w = two.y;
+                raw = nx < 8 ? diag[nx / 2 * 64] : L.Gs[2][0][lane];
+                Y[blk] = mfma_bf16(xb, g, Y[blk]);  // Gm.x is added onto e^{l_i} (S C_i)
+            } else {
+                g.x = two.x, g.y = two.y;
+            }
+            if (st == 0)
+                decay_state(2);
+            if (st == 1)
+                decay_state(3);
+            if (st == 2 || st == 3)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    Y[1][8 * (st & 1) + e] *= ei[1];
+            stage(O, st);  // the next tile into the other buffer, the rows of the one after requested
+            request(st);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // keys 0..31, queries 32..63: unmasked
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            auto pair = [&](uint32_t r, float u, float v) {
+                return pack2_bf16(f16_lo(r) * (ri[1] * u), f16_hi(r) * (ri[1] * v));
+            };
+            const float4 k1 = float4_at(&W.cf[key_of(2 * ks + 1)]);
+            xb = x_operand(ks);
+            g = make_uint4(pair(raw.x, key.x, key.y), pair(raw.y, key.z, key.w), pair(raw.z, k1.x, k1.y), pair(raw.w, k1.z, k1.w));
+            if (ks == 0) {
+                key = float4_at(&W.cf[key_of(2)]);
+                raw = L.Gs[2][1][lane];
+            }
+            Y[1] = mfma_bf16(xb, g, Y[1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // ---------------- the diagonal blocks of a tile that decays by too much for the factors: one exponential per score.
+        // x is still in place here, so the tile takes one walk whatever its decay (walks over windows of tokens that
+        // together decay by less, each leaving its y over x for the next, took 16 x 8192 tokens of 128 heads with A = -16 and
+        // dt = 0.1 5.9 ms instead of 1.28, and made a y that is not finite 0 x inf in the state).
+        if (__builtin_expect(!fast, 0)) {
+            const float step = step_of(T.dt, lane, hd, t.len), l = to_log2(wave_inclusive_sum(step * Ah));
+            W.ei[lane] = l;  // both tables have been read
+            W.wt[lane] = l - __builtin_amdgcn_logf(step);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int blk = 0; blk < 2; ++blk) {
+                const float li = W.ei[32 * blk + i];
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) {
+                    const uint4 r = L.Gs[blk][hf][lane];
+                    const float4 c0 = float4_at(&W.wt[32 * blk + key_of(2 * hf)]), c1 = float4_at(&W.wt[32 * blk + key_of(2 * hf + 1)]);
+                    const float f0[4] = {exp2_fast(li - c0.x), exp2_fast(li - c0.y), exp2_fast(li - c0.z), exp2_fast(li - c0.w)};
+                    const float f1[4] = {exp2_fast(li - c1.x), exp2_fast(li - c1.y), exp2_fast(li - c1.z), exp2_fast(li - c1.w)};
+                    const uint2 g0 = mask_quarter(r.x, r.y, f0, 2 * hf, mask, 0.f), g1 = mask_quarter(r.z, r.w, f1, 2 * hf + 1, mask, 0.f);
+                    Y[blk] = mfma_bf16(x_operand(2 * blk + hf), make_uint4(g0.x, g0.y, g1.x, g1.y), Y[blk]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // ---------------- y over the wave's own columns of x: elements 8 hf .. 8 hf + 7 are channels 16 hf + 8 q .. + 7 of
+        // token 32 ih + i
+#pragma unroll
+        for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+                *reinterpret_cast<uint4 *>(&T.XY[32 * ih + i][32 * w + 16 * hf + 8 * q]) = make_uint4(
+                    pack2_bf16(Y[ih][8 * hf + 0], Y[ih][8 * hf + 1]), pack2_bf16(Y[ih][8 * hf + 2], Y[ih][8 * hf + 3]),
+                    pack2_bf16(Y[ih][8 * hf + 4], Y[ih][8 * hf + 5]), pack2_bf16(Y[ih][8 * hf + 6], Y[ih][8 * hf + 7]));
         if (t.ckpt_slot >= 0) {
             const size_t slot_row = (size_t)t.ckpt_slot * a.H * a.P * kN + state_row;
 #pragma unroll

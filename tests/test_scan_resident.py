@@ -8,7 +8,8 @@ import pytest
 import torch
 
 from helpers import TOL, rel_err
-from test_kernel_emulation import CLANG, CSRC, EMU, ROOT, _convert, _emulate, _oracle, _with_empty_sequence
+from test_kernel_emulation import (CLANG, CSRC, EMU, ROOT, _convert, _emulate, _oracle, _with_empty_sequence,
+                                   emu_binary)  # noqa: F401  (the fixture that builds the other scans)
 from workloads import LayerShape, make_workload
 
 # name: (H, P, N, G, chunk), configuration of the generator, its overrides; every group is a multiple of 256 channels
@@ -73,6 +74,68 @@ def test_emulated_scan_matches_oracle(emu_resident, tmp_path, monkeypatch, case,
         assert max(rel_err(st.astype(np.float64), st_ref)) <= TOL["bf16"]
         first = raw if first is None else first
         assert np.array_equal(first, raw), f"wave order {order} changes the result: LDS race"
+
+
+# What is not finite in an input, or becomes so in fp16, must reach what it reaches in the other matrix-core scan and nothing
+# more.  One sequence of 150 tokens; heads of the usual decay, of one whose tiles leave the range of the masks' factors and of
+# ones in between (16 with steps of 0.1 is the end of the usual ranges).
+SPOILED = ["state_above_fp16", "C_infinite", "C_infinite_steps_of_0.1"]
+
+
+def _spoiled(what, device, copies=1):
+    """The workload with `copies` equal sequences and their initial states."""
+    wl = make_workload(2, "cpu", seed=19, shape=LayerShape(4, 64, 128, 1, 64, "bf16"), batch=1, len_range=(150, 150))
+    wl.A = wl.A * torch.tensor([1.0, 40.0, 400.0, 3.0])
+    init = torch.randn((4, 64, 128), generator=torch.Generator().manual_seed(5))
+    if what == "state_above_fp16":
+        init[:, :, 9] = 7e4
+    if what.startswith("C_infinite"):
+        wl.inputs.C[20, 0, 7] = float("inf")
+    if what.endswith("steps_of_0.1"):
+        wl.A = torch.full_like(wl.A, -16.0)
+        wl.inputs.dt.fill_(0.1)
+    wl.inputs = type(wl.inputs)(*[torch.cat([t] * copies).to(device) for t in (wl.inputs.x, wl.inputs.dt, wl.inputs.B, wl.inputs.C)])
+    wl.A, wl.D = wl.A.to(device), wl.D.to(device)
+    wl.seqlens, wl.ckpt_pos = [150] * copies, [[70, 150]] * copies
+    wl.cu_seqlens = np.arange(copies + 1, dtype=np.int32) * 150
+    return wl, [init.to(device)] * copies
+
+
+def _same_reach(got, want, tol):
+    """Infinite and NaN at the same places; elsewhere the same within `tol` of the value or the rms."""
+    assert np.array_equal(np.isnan(got), np.isnan(want)), (np.isnan(got).sum(), np.isnan(want).sum())
+    assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+    ok = np.isfinite(want)
+    assert max(rel_err(got[ok], want[ok])) <= tol
+
+
+@pytest.mark.parametrize("what", SPOILED)
+def test_emulated_values_that_are_not_finite(emu_resident, emu_binary, tmp_path, what):  # noqa: F811
+    wl, init = _spoiled(what, "cpu")
+    y_ref, st_ref, _ = _emulate(emu_binary, wl, init, tmp_path, 0, "end")
+    y, st, _ = _emulate(emu_resident, wl, init, tmp_path, 0, "end")
+    assert not np.isfinite(y_ref).all() and np.isfinite(st_ref).all()
+    _same_reach(st.astype(np.float64), st_ref.astype(np.float64), 1e-3)  # both round the weighted x to fp16 alike
+    _same_reach(y, y_ref, TOL["bf16"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", SPOILED)
+def test_gpu_values_that_are_not_finite(what):
+    """300 equal sequences, a batch for this scan, against one alone, which the other scan takes."""
+    from helpers import gpu_run
+
+    print(what, flush=True)
+    wl, init = _spoiled(what, "cuda:0", copies=300)
+    one, first = _spoiled(what, "cuda:0")
+    y_ref, st_ref, _ = gpu_run(one, first)
+    y, st, _ = gpu_run(wl, init)
+    y_ref, st_ref = y_ref.float().cpu().numpy(), st_ref.cpu().numpy()
+    assert not np.isfinite(y_ref).all() and np.isfinite(st_ref).all()
+    y, st = y.float().cpu().numpy().reshape(300, *y_ref.shape), st.cpu().numpy().reshape(300, *st_ref.shape)
+    for k in (0, 1, 137, 299):
+        _same_reach(st[k], st_ref, 1e-3)
+        _same_reach(y[k], y_ref, TOL["bf16"])
 
 
 # on the GPU: batches that the plan gives to this scan, H, P, G, lengths, decay, type of the cached states
