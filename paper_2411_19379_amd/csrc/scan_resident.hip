@@ -105,7 +105,7 @@ __device__ __forceinline__ int operand_index(int i)
 
 // The operands of one tile on their way from device memory to LDS, 16 bytes of a token row at a time, and the steps of the
 // workgroup's heads, every wave those of eight tokens.  Rows past the end of a partial tile re-read its last row: their
-// step counts as zero, so any finite value will do.  A tile that is not there is read through descriptors of size zero,
+// step counts as zero, so any finite x and C will do; B is cleared there.  A tile that is not there is read through descriptors of size zero,
 // which return zeros without touching memory.
 struct TileRegs {
     uint4 b[kPassesBC], c[kPassesBC], x[kPassesX];
@@ -178,6 +178,18 @@ struct TileLoader {
         load_dt(r);
     }
 };
+// Zeros in the rows of B behind a partial tile, which the loader fills with its last row: that row may hold infinities (or
+// values above the fp16 range), and 0 x inf is NaN.  Behind the thread's own stores to the same rows.
+__device__ __forceinline__ void clear_rows_behind(_Float16 (*Bs)[LDB], const TileLoader &ld, int len)
+{
+    if (__builtin_expect(len < kQ, 0)) {
+        const uint32_t zero = (uint32_t)len >> 16;  // a constant would occupy four registers throughout
+#pragma unroll
+        for (int m = 0; m < kPassesBC; ++m)
+            if (ld.row + kRowsBC * m >= len)
+                *reinterpret_cast<uint4 *>(&Bs[ld.row + kRowsBC * m][ld.col]) = make_uint4(zero, zero, zero, zero);
+    }
+}
 __device__ __forceinline__ TileLoader make_loader(const ResidentArgs &a, int c0, int g)
 {
     TileLoader l;
@@ -388,6 +400,7 @@ __global__ __launch_bounds__(kThreads, 4) void ssm_segment_state_kernel(Resident
             *reinterpret_cast<uint4 *>(&L.XY[ld.xr + kRowsX * m][ld.xc]) = regs.x[m];
         if (lane < 8)
             *reinterpret_cast<uint2 *>(L.dt[ld.dt_tok]) = make_uint2(regs.dt[0], regs.dt[1]);
+        clear_rows_behind(L.Bs, ld, t.len);
         lds_barrier();
         if (k + 1 < p.tile_end)
             ld.load<false>(regs, t_next);
@@ -568,6 +581,7 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
 #pragma unroll
     for (int m = 0; m < 8; ++m)
         stage(L.tile[0], m);
+    clear_rows_behind(L.tile[0].Bs, ld, t.len);
     const bool two = p.tile_begin + 1 < p.tile_end;
     if (two)
         t_next = scalar_load(a.tiles + p.tile_begin + 1);
@@ -795,6 +809,7 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
                     store_state4(a.state_out, slot_row + 32 * nb + 16 * (e >> 1) + 4 * (e & 1),
                                  make_float4(S[nb][4 * e], S[nb][4 * e + 1], S[nb][4 * e + 2], S[nb][4 * e + 3]), ST);
         }
+        clear_rows_behind(O.Bs, ld, t_next.len);
         y_tok0 = t.tok0;
         y_len = t.len;
         t = t_next;
