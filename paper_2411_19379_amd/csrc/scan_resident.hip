@@ -71,7 +71,7 @@ struct ResidentTile {
 struct ResidentLds {
     ResidentTile tile[2];
     uint4 Gs[3][2][64];             // raw score blocks as accumulator images, fp16
-    uint4 none[2][2][64];           // zeros in the place of the first two
+    uint4 none[2][2][64];           // zeros in the place of the first two, and of factors
     ResidentTables tb[kWaves];
 };
 constexpr int kWindows = 2 * kWaves;  // of 64 tokens, looked back over at a time
@@ -640,10 +640,11 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
         const float dtj = step_of(T.dt, lane, hd, t.len);
         const float ell2 = to_log2(wave_inclusive_sum(dtj * Ah)), mid = read_lane(ell2, 31), last = read_lane(ell2, 63);
         // The factors e^{l_i - l_31} and e^{l_31 - l_j} of the diagonal blocks must stay inside the fp32 exponent range
-        // (2^+-100 is far inside).  If they do not, the blocks' scores and their factors are zeros here, and what the
-        // blocks contribute is added behind the others; the factors of the third block are at most 1 whatever the decay.
+        // (2^+-100 is far inside).  If they do not, or a step is NaN, the blocks' scores and factors are zeros here, and what
+        // the blocks contribute is added behind the others; the factors of the third block are at most 1 whatever the decay.
         const bool fast = mid > -100.f && last - mid > -100.f;
         const uint4 *diag = fast ? &L.Gs[0][0][lane] : &L.none[0][0][lane];
+        const float *factors = fast ? &W.cf[8 * q] : reinterpret_cast<const float *>(&L.none[0][0][2 * q]);
         float dl = 0.f;
         f32x16 Y[2] = {zero16(), zero16()};  // [token half]
         uint4 xw[4], xb;
@@ -682,10 +683,8 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
             __builtin_amdgcn_sched_barrier(0);
             if (ks == 0 && y_len)
                 store_y(y_tok0, y_len);
-            if (ks == 2 && __builtin_expect(!fast, 0)) {
+            if (ks == 2 && __builtin_expect(!fast, 0))
                 W.ri[lane & 31] = 0.f;
-                W.cf[lane | 32] = 0.f;
-            }
         }
         lds_barrier();  // the raw scores are in place
         // ---------------- the decayed state accumulates the update, two blocks of 32 state indices x 16 tokens at a time;
@@ -711,7 +710,7 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
         };
         const auto key_of = [&](int a) { return 16 * (a >> 1) + 8 * q + 4 * (a & 1); };
         const float ri[2] = {W.ri[i], W.ri[32 + i]}, ei[2] = {W.ei[i], W.ei[32 + i]};
-        float4 key = float4_at(&W.cf[key_of(0)]);
+        float4 key = float4_at(&factors[key_of(0) - 8 * q]);
         uint4 raw = diag[0], g = make_uint4(0, 0, 0, 0);
         load_b(0);
         ld.start(t_after, k + 2 < p.tile_end);
@@ -730,7 +729,7 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
             if (a & 1)
                 xb = x_operand(2 * blk + (a >> 1));
             const float f[4] = {ri[blk] * key.x, ri[blk] * key.y, ri[blk] * key.z, ri[blk] * key.w};
-            key = nx < 8 ? float4_at(&W.cf[32 * (nx >> 2) + key_of(nx & 3)]) : float4_at(&W.cf[key_of(0)]);
+            key = nx < 8 ? float4_at(&factors[32 * (nx >> 2) + key_of(nx & 3) - 8 * q]) : float4_at(&W.cf[key_of(0)]);
             const uint2 two = (a & 1) ? mask_quarter(raw.z, raw.w, f, a, mask, Dh) : mask_quarter(raw.x, raw.y, f, a, mask, Dh);
             if (a & 1) {
                 g.z = two.x, g.w = two.y;

@@ -80,7 +80,8 @@ def test_emulated_scan_matches_oracle(emu_resident, tmp_path, monkeypatch, case,
 # more.  One sequence of 150 tokens; heads of the usual decay, of one whose tiles leave the range of the masks' factors and of
 # ones in between (16 with steps of 0.1 is the end of the usual ranges).
 # The tiles are those of tokens 0, 64, 70 and 134 on, the second and the fourth partial.
-SPOILED = ["state_above_fp16", "C_infinite", "C_infinite_steps_of_0.1", "B_infinite_in_a_partial_tile", "B_above_fp16_in_a_partial_tile"]
+SPOILED = ["state_above_fp16", "C_infinite", "C_infinite_steps_of_0.1", "B_infinite_in_a_partial_tile", "B_above_fp16_in_a_partial_tile",
+           "step_NaN", "step_infinite", "late_step_NaN"]
 
 
 def _spoiled(what, device, copies=1):
@@ -95,6 +96,8 @@ def _spoiled(what, device, copies=1):
     if what.startswith("B_"):
         wl.inputs.B[[69, 149], 0, 7] = float("inf") if "infinite" in what else 1e5
         wl.A = wl.A[:1].repeat(4) * torch.tensor([1.0, 2.0, 0.5, 1.0])
+    if "step_" in what:
+        wl.inputs.dt[110 if "late" in what else 9, 1:] = float(what.split("_")[-1].replace("infinite", "inf"))
     if what.endswith("steps_of_0.1"):
         wl.A = torch.full_like(wl.A, -16.0)
         wl.inputs.dt.fill_(0.1)
@@ -118,7 +121,7 @@ def test_emulated_values_that_are_not_finite(emu_resident, emu_binary, tmp_path,
     wl, init = _spoiled(what, "cpu")
     y_ref, st_ref, _ = _emulate(emu_binary, wl, init, tmp_path, 0, "end")
     y, st, _ = _emulate(emu_resident, wl, init, tmp_path, 0, "end")
-    assert not np.isfinite(y_ref).all() and np.isfinite(st_ref).all() == (what[0] != "B")
+    assert not np.isfinite(y_ref).all() and np.isfinite(st_ref).all() == (what[0] in "Cs" and "step_" not in what)
     _same_reach(st.astype(np.float64), st_ref.astype(np.float64), 1e-3)  # both round the weighted x to fp16 alike
     _same_reach(y, y_ref, TOL["bf16"])
     if what[0] == "B":  # through the segments too
@@ -140,7 +143,7 @@ def test_gpu_values_that_are_not_finite(what):
     y_ref, st_ref, _ = gpu_run(one, first)
     y, st, _ = gpu_run(wl, init)
     y_ref, st_ref = y_ref.float().cpu().numpy(), st_ref.cpu().numpy()
-    assert not np.isfinite(y_ref).all() and np.isfinite(st_ref).all() == (what[0] != "B")
+    assert not np.isfinite(y_ref).all() and np.isfinite(st_ref).all() == (what[0] in "Cs" and "step_" not in what)
     y, st = y.float().cpu().numpy().reshape(300, *y_ref.shape), st.cpu().numpy().reshape(300, *st_ref.shape)
     for k in (0, 1, 137, 299):
         _same_reach(st[k], st_ref, 1e-3)
