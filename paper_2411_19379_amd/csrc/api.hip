@@ -259,8 +259,9 @@ constexpr size_t kNoAllocMaxStretches = kNoAllocMaxBatch + 256;  // cutting adds
 constexpr size_t kScratchSeqsOff = kNoAllocMaxTiles * sizeof(SsmTile);
 constexpr size_t kScratchPtrsOff = kScratchSeqsOff + kNoAllocMaxBatch * sizeof(SsmSeq);
 constexpr size_t kScratchScanSeqsOff = kScratchPtrsOff + kNoAllocMaxBatch * sizeof(void *);
-// a plan with resident states has fewer pieces than that, and at most one segment per kSegmentTiles tiles and per piece more
-constexpr size_t kNoAllocMaxPieces = 2 * kNoAllocMaxStretches + kNoAllocMaxTiles / kSegmentTiles;
+// a plan with resident states adds at most kMostAddedPieces pieces to its sequences, each of which makes one continued, and
+// the continued ones have at most one segment per kSegmentTiles tiles and one more each
+constexpr size_t kNoAllocMaxPieces = kNoAllocMaxBatch + 2 * kMostAddedPieces + kNoAllocMaxTiles / kSegmentTiles;
 constexpr size_t kScratchScanBytes = kNoAllocMaxStretches * sizeof(SsmScanSeq) > kNoAllocMaxPieces * sizeof(SsmPiece)
                                          ? kNoAllocMaxStretches * sizeof(SsmScanSeq)
                                          : kNoAllocMaxPieces * sizeof(SsmPiece);

@@ -295,6 +295,7 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
 {
     std::vector<SsmPiece> segments;
     plan->pieces.clear();
+    plan->n_continued = 0;
     for (int32_t i = 0; i < plan->batch; ++i) {
         const int64_t begin = plan->seqs[i].tile_begin, n = plan->seqs[i].tile_end - begin;
         const int64_t parts = (n + most - 1) / most;
@@ -306,10 +307,13 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
             p.seq = i;
             p.slot = (int32_t)segments.size() - 1;
             p.back = back;
-            p.stop = p.tile_end;
+            p.stop = (int32_t)(begin + n);
+            p.part = (int32_t)k;
+            p.first = plan->n_continued;
             plan->pieces.push_back(p);
             if (k + 1 == parts)
                 break;
+            p.stop = p.tile_end;  // of its segments
             const int64_t m = p.tile_end - p.tile_begin, cuts = (m + segment - 1) / segment;
             for (int64_t c = 0; c < cuts; ++c) {
                 SsmPiece g = p;
@@ -320,6 +324,7 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
                 segments.push_back(g);
             }
         }
+        plan->n_continued += parts > 0 ? (int32_t)parts - 1 : 0;
     }
     std::stable_sort(plan->pieces.begin(), plan->pieces.end(), [](const SsmPiece &a, const SsmPiece &b) {
         return a.tile_end - a.tile_begin > b.tile_end - b.tile_begin;
@@ -332,14 +337,15 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
     plan->pieces.insert(plan->pieces.end(), segments.begin(), segments.end());
 }
 
-size_t ssm_piece_decay_offset(const ssm_plan *plan)
+SsmPieceWorkspace ssm_piece_workspace(const ssm_plan *plan)
 {
-    const ssm_shape_t &s = plan->shape;
-    return (size_t)plan->n_segments * s.nheads * s.headdim * s.d_state * sizeof(float);
-}
-size_t ssm_piece_workspace(const ssm_plan *plan)
-{
-    return ssm_piece_decay_offset(plan) + (size_t)plan->n_segments * plan->shape.nheads * sizeof(float);
+    const size_t H = (size_t)plan->shape.nheads, state = H * plan->shape.headdim * plan->shape.d_state * sizeof(float);
+    SsmPieceWorkspace w;
+    w.spoil = plan->n_segments * state;
+    w.decay = w.spoil + plan->n_continued * state;
+    w.spoiled = (w.decay + plan->n_segments * H * sizeof(float) + 15) / 16 * 16;
+    w.total = w.spoiled + plan->n_continued * (H * plan->shape.headdim / 32) * sizeof(int32_t);
+    return w;
 }
 
 // Tiles that the busiest of `places` workgroups-at-a-time works through, for pieces (or stretches) of `lengths` tiles,
@@ -566,10 +572,11 @@ extern "C" int ssm_plan_workspace_bytes(const ssm_plan_t *plan, size_t *bytes)
     // The running state never leaves the chip between tiles; the matrix-core scan needs room for the operands
     // that the heads of a group share (written by its first kernel, read by its second) and, when it cuts long
     // sequences into stretches, for the states carried from one stretch to the next and each tile's total decay.  The scan
-    // with resident states needs some only if it cuts a sequence: a state and a decay per segment.  A plan's requirement
+    // with resident states needs some only if it cuts a sequence: a state and a decay per segment, a state per continued
+    // piece.  A plan's requirement
     // is the larger of the two, whichever scan it takes.
     *bytes = ssm_mfma_workspace(plan).total;
     if (plan->resident)
-        *bytes = std::max(*bytes, ssm_piece_workspace(plan));
+        *bytes = std::max(*bytes, ssm_piece_workspace(plan).total);
     return SSM_OK;
 }

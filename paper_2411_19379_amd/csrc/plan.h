@@ -50,7 +50,9 @@ struct SsmPiece {
     int32_t seq;
     int32_t slot;  // of a segment: its own; of a piece: that of the segment in front of it.  The ones before have those below
     int32_t back;  // segments of the sequence in front of it
-    int32_t stop;  // of a segment: the tile where its piece ends
+    int32_t stop;  // of a segment: the tile where its piece ends; of a piece: the one where its sequence ends
+    int32_t part;  // pieces of the sequence in front of it
+    int32_t first; // of a piece: number of pieces, of sequences in front of its own, that others continue
 };
 
 // Launch order of the matrix-core scan.  Its work items, one per (rank of a non-empty sequence, head, channel slice),
@@ -109,7 +111,7 @@ struct ssm_plan {
     std::vector<SsmScanSeq> scan_seqs;  // matrix-core scan only
     // Scan with resident states only: the pieces in launch order (longest first) and, behind them, the segments.
     bool resident = false;
-    int32_t n_pieces = 0, n_segments = 0;
+    int32_t n_pieces = 0, n_segments = 0, n_continued = 0;  // n_continued: pieces that others continue
     std::vector<SsmPiece> pieces;
     // Device copies of the two tables and a buffer for the per-call state
     // pointers, one set per GPU the plan has been used on.  A cache behind a
@@ -136,9 +138,12 @@ void ssm_plan_build_stretches(ssm_plan *plan, int64_t per_round, int32_t min_til
 
 // Scan with resident states: (re)builds the pieces, of at most `most` tiles each, and the segments, of at most `segment`.
 void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment);
-// Where its workspace holds the total decay of every (slot, head), behind the slots, and how much it needs in all.
-size_t ssm_piece_decay_offset(const ssm_plan *plan);
-size_t ssm_piece_workspace(const ssm_plan *plan);
+// Its workspace, in byte offsets: from 0 on an fp32 state per segment, then one per continued piece, the segments' total
+// decay per head, a flag per continued piece and 32 channels.  Empty unless a sequence is cut.
+struct SsmPieceWorkspace {
+    size_t spoil = 0, decay = 0, spoiled = 0, total = 0;
+};
+SsmPieceWorkspace ssm_piece_workspace(const ssm_plan *plan);
 
 // Tokens of sequence i.
 inline int32_t ssm_plan_tokens(const ssm_plan *plan, int32_t i)

@@ -14,7 +14,8 @@
 //   ssm_segment_state_kernel, computes what the segments of every piece that is continued add to the state, as far as it
 //   has not decayed below 2^-150 by the end of the piece; a piece of the second kernel,
 //   ssm_scan_resident_kernel, starts from the sum of the segments in front of it.  So y is written once, from the true
-//   state.
+//   state.  An infinity or NaN does not decay: a third kernel, ssm_not_finite_kernel, which leaves at once if there is
+//   none, takes those in the state at the end of a piece to the rest of the sequence.
 //
 // Time per call, this scan and the other: 128 heads, 131072 tokens 1430 us and 1850, 16 x 8192 1282 and 1689, 32 x 1024
 // 353 and 485; 80 heads, 16 requests of 500 to 7700 tokens 522 and 564; 16 heads, 32768 tokens 85 and 118.  At 128 heads
@@ -52,7 +53,7 @@ constexpr int kThreads = 64 * kWaves;
 // Row strides in LDS: four rows of a transpose read meet on no bank; the pieces of a row of C, which go to the same lane of
 // 16 operands, spread over the banks.
 constexpr int LDB = kN + 24, LDX = kResidentChannels + 24, LDC = 64 + 1;
-constexpr float kCutoffLog2 = -150.f;         // below this nothing is added in fp32
+constexpr float kCutoffLog2 = -150.f;         // a finite state that has decayed below this adds nothing to others of its size
 constexpr int kRowsBC = kThreads / 16, kPassesBC = kQ / kRowsBC;  // rows of B and C per pass of the workgroup
 constexpr int kLanesX = kResidentChannels / 8, kRowsX = kThreads / kLanesX, kPassesX = kQ / kRowsX;  // and of x
 
@@ -71,7 +72,7 @@ struct ResidentTile {
 struct ResidentLds {
     ResidentTile tile[2];
     uint4 Gs[3][2][64];             // raw score blocks as accumulator images, fp16
-    uint4 none[2][2][64];           // zeros in the place of the first two, and of factors
+    uint4 none[2][2][64];           // zeros in the place of the first two
     ResidentTables tb[kWaves];
 };
 constexpr int kWindows = 2 * kWaves;  // of 64 tokens, looked back over at a time
@@ -92,8 +93,12 @@ struct ResidentArgs {
     StatePtrs init;
     const SsmTile *tiles;
     const SsmPiece *pieces;  // of this launch, in launch order
-    float4 *carry;           // per slot: what the piece adds to the state, as accumulator images
-    float *decay;            // per (slot, head): the piece's total log2 decay
+    float4 *carry;           // per slot: what the segment adds to the state, as accumulator images
+    float *decay;            // per (slot, head): the segment's total log2 decay
+    // per piece that another one continues and 32 channels: whether the state at its end holds a value that is not finite;
+    // if it does, that state, as accumulator images
+    int *spoiled;
+    float4 *spoil;
     int H, P, G, blocks, n_items;
 };
 
@@ -222,7 +227,8 @@ __device__ __forceinline__ float to_log2(float l)
     return l * kLog2e;
 }
 
-// The accumulator images of a slot, from channel cw on, in float4 units: + 16 * 64 per 32 channels, + (4 nb + a) 64 + lane.
+// The accumulator images of a slot or of a continued piece, from channel cw on, in float4 units: + 16 * 64 per 32 channels,
+// + (4 nb + a) 64 + lane.
 __device__ __forceinline__ size_t carry_at(const ResidentArgs &a, int slot, int cw)
 {
     return ((size_t)slot * ((size_t)a.H * a.P / 32) + cw / 32) * (16 * 64);
@@ -644,7 +650,6 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
         // the blocks contribute is added behind the others; the factors of the third block are at most 1 whatever the decay.
         const bool fast = mid > -100.f && last - mid > -100.f;
         const uint4 *diag = fast ? &L.Gs[0][0][lane] : &L.none[0][0][lane];
-        const float *factors = fast ? &W.cf[8 * q] : reinterpret_cast<const float *>(&L.none[0][0][2 * q]);
         float dl = 0.f;
         f32x16 Y[2] = {zero16(), zero16()};  // [token half]
         uint4 xw[4], xb;
@@ -683,8 +688,13 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
             __builtin_amdgcn_sched_barrier(0);
             if (ks == 0 && y_len)
                 store_y(y_tok0, y_len);
-            if (ks == 2 && __builtin_expect(!fast, 0))
+            if (ks == 2 && __builtin_expect(!fast, 0)) {
+                const float key = W.cf[lane];
                 W.ri[lane & 31] = 0.f;
+                // NaN where a step of the first half is; the queries' factor of the third block is then NaN too
+                if (lane >= 32 || key != key)
+                    W.cf[lane] = 0.f;
+            }
         }
         lds_barrier();  // the raw scores are in place
         // ---------------- the decayed state accumulates the update, two blocks of 32 state indices x 16 tokens at a time;
@@ -710,7 +720,7 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
         };
         const auto key_of = [&](int a) { return 16 * (a >> 1) + 8 * q + 4 * (a & 1); };
         const float ri[2] = {W.ri[i], W.ri[32 + i]}, ei[2] = {W.ei[i], W.ei[32 + i]};
-        float4 key = float4_at(&factors[key_of(0) - 8 * q]);
+        float4 key = float4_at(&W.cf[key_of(0)]);
         uint4 raw = diag[0], g = make_uint4(0, 0, 0, 0);
         load_b(0);
         ld.start(t_after, k + 2 < p.tile_end);
@@ -729,7 +739,7 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
             if (a & 1)
                 xb = x_operand(2 * blk + (a >> 1));
             const float f[4] = {ri[blk] * key.x, ri[blk] * key.y, ri[blk] * key.z, ri[blk] * key.w};
-            key = nx < 8 ? float4_at(&factors[32 * (nx >> 2) + key_of(nx & 3) - 8 * q]) : float4_at(&W.cf[key_of(0)]);
+            key = nx < 8 ? float4_at(&W.cf[32 * (nx >> 2) + key_of(nx & 3)]) : float4_at(&W.cf[key_of(0)]);
             const uint2 two = (a & 1) ? mask_quarter(raw.z, raw.w, f, a, mask, Dh) : mask_quarter(raw.x, raw.y, f, a, mask, Dh);
             if (a & 1) {
                 g.z = two.x, g.w = two.y;
@@ -817,6 +827,116 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
     lds_barrier();
     read_y(L.tile[(p.tile_end - p.tile_begin - 1) & 1]);
     store_y(y_tok0, y_len);
+    // read and made again here: what the loop does not need would fill registers there that the rows in flight need
+    const int me = ssm_launch_item(blockIdx.x, a.n_items), me_cw = me % a.blocks * kResidentChannels + 32 * w;
+    const int ln = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+    const SsmPiece done = a.pieces[me / a.blocks];
+    if (done.tile_end < done.stop) {
+        float sum = 0.f;  // NaN if one of them is not finite
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                sum = __builtin_fmaf(S[nb][e], 0.f, sum);
+        const bool spoiled = __any(sum != 0.f);
+        const int own = done.first + done.part;
+        if (ln == 0)
+            a.spoiled[(size_t)own * (a.H * a.P / 32) + me_cw / 32] = spoiled;
+        if (spoiled) {
+            float4 *out = a.spoil + carry_at(a, own, me_cw) + ln;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    out[(4 * nb + e) * 64] = make_float4(S[nb][4 * e], S[nb][4 * e + 1], S[nb][4 * e + 2], S[nb][4 * e + 3]);
+        }
+    }
+}
+
+// ================================================================ values that are not finite
+// One workgroup per (piece, 256 channels).  A state element that is infinite or NaN stays so, but a piece starts without what
+// has decayed.  Where an earlier piece of the sequence ended with such elements, they are added to the piece's checkpoints
+// and, through C, to its outputs; where the piece started with them, that changes nothing.  Without any, which is all that
+// ever happens with sound inputs, the workgroup reads a flag per earlier piece and 32 channels and leaves: 3 us with the launch
+// (32768 tokens of 16 heads 81 -> 84 us).  To look for such elements in the segments instead would mean to read all of x and B
+// a second time.
+constexpr int kRestThreads = 256;
+struct RestLds {
+    float P[32][kN];  // the elements that are not finite, else 0
+    int any[kResidentChannels / 32];
+};
+template <int ST>
+__global__ __launch_bounds__(kRestThreads) void ssm_not_finite_kernel(ResidentArgs a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    RestLds &L = *reinterpret_cast<RestLds *>(lds_raw);
+    const int item = ssm_launch_item(blockIdx.x, a.n_items), tid = threadIdx.x;
+    if (item < 0)
+        return;
+    const SsmPiece p = scalar_load(a.pieces + item / a.blocks);
+    if (p.part == 0)
+        return;
+    const int c0 = item % a.blocks * kResidentChannels, groups = a.H * a.P / 32;
+    constexpr int kGroups = kResidentChannels / 32;
+    auto spoiled = [&](int m, int u) { return a.spoiled[(size_t)(p.first + m) * groups + c0 / 32 + u]; };
+    static_assert(kGroups == 8, "two words of four flags");
+    int seen[kGroups] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int m = tid; m < p.part; m += kRestThreads) {
+        const int4 *f = reinterpret_cast<const int4 *>(a.spoiled + (size_t)(p.first + m) * groups + c0 / 32);
+        const int4 lo = f[0], hi = f[1];
+        seen[0] |= lo.x, seen[1] |= lo.y, seen[2] |= lo.z, seen[3] |= lo.w;
+        seen[4] |= hi.x, seen[5] |= hi.y, seen[6] |= hi.z, seen[7] |= hi.w;
+    }
+    if (tid < kGroups)
+        L.any[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kGroups; ++u)
+        if (seen[u])
+            L.any[u] = 1;
+    __syncthreads();
+    const bf16_t *C = a.C + (size_t)(c0 / (a.H / a.G * a.P)) * kN;
+    const SsmTile begin = scalar_load(a.tiles + p.tile_begin), end = scalar_load(a.tiles + p.tile_end - 1);
+    for (int u = 0; u < kGroups; ++u) {
+        if (!L.any[u])
+            continue;  // the whole workgroup
+        const int cw = c0 + 32 * u;
+        for (int m = tid; m < 16 * 64; m += kRestThreads) {
+            const int lane = m & 63, nb = m >> 8, e = (m >> 6) & 3;
+            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < p.part; ++k)
+                if (spoiled(k, u)) {
+                    const float4 v = a.spoil[carry_at(a, p.first + k, cw) + m];
+                    const float vs[4] = {v.x, v.y, v.z, v.w};
+                    for (int r = 0; r < 4; ++r)
+                        sum[r] += vs[r] * 0.f != 0.f ? vs[r] : 0.f;
+                }
+            for (int r = 0; r < 4; ++r)
+                L.P[operand_index(lane & 31)][32 * nb + 16 * (e >> 1) + 4 * (e & 1) + 8 * (lane >> 5) + r] = sum[r];
+        }
+        __syncthreads();
+        const int ch = tid & 31;
+        for (int tok = begin.tok0 + (tid >> 5); tok < end.tok0 + end.len; tok += kRestThreads / 32) {
+            float sum = 0.f;
+            for (int n = 0; n < kN; ++n)
+                if (L.P[ch][n] != 0.f)
+                    sum += L.P[ch][n] * bf16_to_f32(C[(size_t)tok * a.G * kN + n]);
+            bf16_t *y = a.y + (size_t)tok * a.H * a.P + cw + ch;
+            if (sum != 0.f)
+                *y = f32_to_bf16(bf16_to_f32(*y) + sum);
+        }
+        for (int k = p.tile_begin; k < p.tile_end; ++k) {
+            const int slot = a.tiles[k].ckpt_slot;
+            if (slot < 0)
+                continue;
+            for (int m = tid; m < 32 * kN; m += kRestThreads) {
+                const size_t at = ((size_t)slot * a.H * a.P + cw) * kN + m;
+                if ((&L.P[0][0])[m] != 0.f)
+                    state_store(a.state_out, at, state_load(a.state_out, at, ST) + (&L.P[0][0])[m], ST);
+            }
+        }
+        __syncthreads();
+    }
 }
 
 template <int ST>
@@ -854,7 +974,13 @@ hipError_t launch_resident_st(const ssm_plan *plan, ResidentArgs a, const SsmPie
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     if (hipEvent_t mark = ssm_profile_event(1))
-        e = hipEventRecord(mark, stream);
+        if ((e = hipEventRecord(mark, stream)) != hipSuccess)
+            return e;
+    if (plan->n_continued > 0) {
+        hipLaunchKernelGGL(ssm_not_finite_kernel<ST>, dim3((unsigned)ssm_launch_blocks(a.n_items)), dim3(kRestThreads),
+                           sizeof(RestLds), stream, a);
+        e = hipGetLastError();
+    }
     return e;
 }
 
@@ -876,8 +1002,12 @@ hipError_t launch_scan_resident(const ssm_plan *plan, const ScanArgs &args, cons
     a.state_out = args.state_out;
     a.init = state_ptrs_of(args.init_ptrs, args.host_ptrs, args.n_host_ptrs);
     a.tiles = args.tiles;
-    a.carry = static_cast<float4 *>(workspace);
-    a.decay = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + ssm_piece_decay_offset(plan));
+    const SsmPieceWorkspace w = ssm_piece_workspace(plan);
+    unsigned char *base = static_cast<unsigned char *>(workspace);
+    a.carry = reinterpret_cast<float4 *>(base);
+    a.spoil = reinterpret_cast<float4 *>(base + w.spoil);
+    a.decay = reinterpret_cast<float *>(base + w.decay);
+    a.spoiled = reinterpret_cast<int *>(base + w.spoiled);
     a.H = args.H;
     a.P = args.P;
     a.G = args.G;

@@ -145,6 +145,9 @@ static inline uint32_t emu_perm(uint32_t hi, uint32_t lo, uint32_t sel)
 }
 #define __builtin_amdgcn_perm(hi, lo, sel) emu_perm((hi), (lo), (sel))
 #define __any(v) emu::any_lane((v), __LINE__)
+// the lane's number, as the count of lanes in front of it
+#define __builtin_amdgcn_mbcnt_lo(mask, n) (n)
+#define __builtin_amdgcn_mbcnt_hi(mask, n) ((n) + (int)(threadIdx.x & 63))
 #define __amdgpu_buffer_rsrc_t emu::BufRsrc
 #define __builtin_amdgcn_make_buffer_rsrc(p, stride, n, flags) emu::make_buffer_rsrc((p), (stride), (n), (flags))
 #define __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, aux) emu::buffer_load<emu::u32x4>((r), (voff), (soff), __LINE__)

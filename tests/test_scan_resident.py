@@ -131,6 +131,67 @@ def test_emulated_values_that_are_not_finite(emu_resident, emu_binary, tmp_path,
         _same_reach(y, y_ref, TOL["bf16"])
 
 
+# An infinity or NaN in a state stays there to the end of the sequence, also in pieces that start without what has decayed: as
+# in a sequence that is walked in one go.  (Infinite or NaN is not compared: what is infinite becomes NaN in a tile whose decay
+# is zero in fp32.)
+STICKY = {"x": ("x", 5, (1, 17)), "B": ("B", 130, (0, 5)), "dt": ("dt", 3, (2,)), "state": ("init", None, (1, 9, 11))}
+
+
+def _sticky(spot, value, device, tokens, decay):
+    wl = make_workload(2, "cpu", seed=29, shape=LayerShape(4, 64, 128, 1, 64, "bf16"), batch=1, len_range=(tokens, tokens))
+    wl.A = wl.A * torch.tensor(decay)
+    wl.ckpt_pos = [[tokens // 8, tokens // 2, tokens - 1]]
+    init = torch.randn((4, 64, 128), generator=torch.Generator().manual_seed(7))
+    name, tok, idx = STICKY[spot]
+    (init if name == "init" else getattr(wl.inputs, name))[idx if tok is None else (tok, *idx)] = value
+    wl.inputs = type(wl.inputs)(*[t.to(device) for t in (wl.inputs.x, wl.inputs.dt, wl.inputs.B, wl.inputs.C)])
+    wl.A, wl.D = wl.A.to(device), wl.D.to(device)
+    return wl, [init.to(device)]
+
+
+def _same_finite(got, want, tol):
+    ok = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), ok), ((~np.isfinite(got)).sum(), (~ok).sum())
+    assert not ok.all() and max(rel_err(got[ok], want[ok])) <= tol
+
+
+@pytest.mark.parametrize("most,segment", [(1, 1), (3, 2)])
+@pytest.mark.parametrize("spot,value,state_type", [("x", float("inf"), None), ("x", float("nan"), "f16"), ("B", float("-inf"), None),
+                                                   ("dt", float("nan"), None), ("state", float("inf"), "bf16")])
+def test_emulated_values_that_are_not_finite_stay(emu_resident, emu_binary, tmp_path, monkeypatch, spot, value, state_type,  # noqa: F811
+                                                  most, segment):
+    wl, init = _sticky(spot, value, "cpu", 500, [1.0, 60.0, 20.0, 400.0])
+    y_ref, st_ref, _ = _emulate(emu_binary, wl, init, tmp_path, 0, "end", state_type=state_type)
+    monkeypatch.setenv("EMU_PIECES", str(most))
+    monkeypatch.setenv("EMU_SEGMENTS", str(segment))
+    for order, align in ((0, "end"), (1, "start")):
+        y, st, _ = _emulate(emu_resident, wl, init, tmp_path, order, align, state_type=state_type)
+        _same_finite(st.astype(np.float64), st_ref, 1e-2)
+        _same_finite(y, y_ref, TOL["bf16"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("spot", sorted(STICKY))
+def test_gpu_values_that_are_not_finite_stay(spot):
+    """9000 tokens, which this scan cuts, against three sequences of a third each that resume from the one before."""
+    from helpers import gpu_run
+
+    print(spot, flush=True)
+    wl, init = _sticky(spot, float("inf"), "cuda:0", 9000, [1.0, 1.0, 30.0, 4.0])
+    y, st, _ = gpu_run(wl, init)
+    state, ys, states = init[0], [], []
+    for lo in (0, 3000, 6000):
+        part = [t[lo:lo + 3000].contiguous() for t in (wl.inputs.x, wl.inputs.dt, wl.inputs.B, wl.inputs.C)]
+        at = [p - lo for p in wl.ckpt_pos[0] if lo < p <= lo + 3000]
+        y1, st1, _ = gpu_run(wl, [state], inputs=type(wl.inputs)(*part), cu=np.asarray([0, 3000], np.int32),
+                             ckpt_pos=[sorted({*at, 3000})])
+        ys.append(y1)
+        states += [st1[k] for k in range(len(at))]
+        state = st1[-1].contiguous()
+    _same_finite(st.cpu().numpy(), torch.stack(states).cpu().numpy(), 1e-2)
+    _same_finite(y.float().cpu().numpy(), torch.cat(ys).float().cpu().numpy(), TOL["bf16"])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("what", SPOILED)
 def test_gpu_values_that_are_not_finite(what):
