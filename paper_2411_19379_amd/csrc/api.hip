@@ -427,10 +427,12 @@ extern "C" int ssm_conv1d_prefill(const ssm_plan_t *plan, int32_t channels, int3
         if (e != hipSuccess)
             return hip_fail("upload of the initial-state pointers", e);
     }
+    const size_t state_bytes = (size_t)channels * kernel_width * (plan->shape.io_dtype == SSM_DT_F32 ? 4 : 2);
     const hipError_t e = launch_conv1d_prefill(
         plan, static_cast<const SsmTile *>(t.tiles), static_cast<const SsmSeq *>(t.seqs), channels, kernel_width, in,
         weight, bias, in_table ? static_cast<const void *const *>(t.ptrs) : nullptr, out, state_out, activation,
-        stream, in_args ? init_state_ptrs : nullptr, in_args ? plan->batch : 0);
+        stream, in_args ? init_state_ptrs : nullptr, in_args ? plan->batch : 0,
+        ssm_states_overlap(init_state_ptrs, plan->batch, state_bytes, state_out, plan->n_ckpt * state_bytes));
     if (e != hipSuccess)
         return hip_fail("kernel launch", e);
     return SSM_OK;

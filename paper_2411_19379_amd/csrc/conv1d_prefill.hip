@@ -214,11 +214,11 @@ bool conv1d_supports(int channels, int K, int io_dtype)
 
 // Launch over the tiles of `plan` (any shape: only its tile table, sequence table and storage type are used).
 // `d_init_ptrs` is null or a device array of plan->batch device pointers; `state_out` may be null if the plan has no
-// checkpoints.
+// checkpoints.  `states_overlap`: an initial state shares memory with `state_out`.
 hipError_t launch_conv1d_prefill(const ssm_plan *plan, const SsmTile *d_tiles, const SsmSeq *d_seqs, int channels,
                                  int K, const void *in, const float *w, const float *bias,
                                  const void *const *d_init_ptrs, void *out, void *state_out, int act,
-                                 hipStream_t stream, const void *const *host_ptrs, int n_host_ptrs)
+                                 hipStream_t stream, const void *const *host_ptrs, int n_host_ptrs, bool states_overlap)
 {
     if (!conv1d_supports(channels, K, plan->shape.io_dtype))
         return hipErrorInvalidValue;
@@ -242,9 +242,10 @@ hipError_t launch_conv1d_prefill(const ssm_plan *plan, const SsmTile *d_tiles, c
     // Few tiles leave most of the chip idle, and each is a serial walk: they are cut into parts, of no less than a group of
     // rows for tiles of average length, up to kConvWorkgroups workgroups in all.  Whole tiles and in parts, bf16: 500 tokens
     // of 5376 channels 23 and 8 us, 2048 25 and 17 (1024 workgroups: 21), 4096 26 and 24 (32); 32768 tokens of 10240
-    // channels, 2560 workgroups, 270 and, cut in two, 274.
+    // channels, 2560 workgroups, 270 and, cut in two, 274.  Not where a state is updated in place: a whole tile's walk has
+    // read the state in front of it before it writes the one behind, but the last part may write it before the first reads.
     a.parts = 1;
-    while (a.parts < kConvMostParts && (int64_t)n_tiles * a.blocks_per_tile * a.parts * 2 <= kConvWorkgroups &&
+    while (!states_overlap && a.parts < kConvMostParts && (int64_t)n_tiles * a.blocks_per_tile * a.parts * 2 <= kConvWorkgroups &&
            plan->total_tokens > (int64_t)n_tiles * a.parts * kAhead)
         a.parts *= 2;
     const dim3 grid((unsigned)n_tiles * (unsigned)a.parts * (unsigned)a.blocks_per_tile);

@@ -150,4 +150,4 @@ bool conv1d_supports(int channels, int K, int io_dtype);
 hipError_t launch_conv1d_prefill(const ssm_plan *plan, const SsmTile *d_tiles, const SsmSeq *d_seqs, int channels,
                                  int K, const void *in, const float *w, const float *bias,
                                  const void *const *d_init_ptrs, void *out, void *state_out, int act,
-                                 hipStream_t stream, const void *const *host_ptrs = nullptr, int n_host_ptrs = 0);
+                                 hipStream_t stream, const void *const *host_ptrs = nullptr, int n_host_ptrs = 0, bool states_overlap = false);

@@ -212,6 +212,17 @@ extern "C" int ssm_f32_slices(int split, int d_state, int headdim, int64_t strea
     return nc;
 }
 
+bool ssm_states_overlap(const void *const *states, int32_t n, size_t bytes, const void *out, size_t out_bytes)
+{
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(out), hi = lo + out_bytes;
+    for (int32_t i = 0; states && i < n; ++i) {
+        const uintptr_t s = reinterpret_cast<uintptr_t>(states[i]);
+        if (s && s < hi && s + bytes > lo)
+            return true;
+    }
+    return false;
+}
+
 static void ssm_plan_order_sequences(ssm_plan *plan);
 
 void ssm_plan_build_stretches(ssm_plan *plan, int64_t per_round, int32_t min_tiles)

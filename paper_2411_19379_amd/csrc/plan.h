@@ -145,6 +145,9 @@ struct SsmPieceWorkspace {
 };
 SsmPieceWorkspace ssm_piece_workspace(const ssm_plan *plan);
 
+// Whether any of the (host array of) `n` states of `bytes` bytes, null entries aside, shares memory with `out`.
+bool ssm_states_overlap(const void *const *states, int32_t n, size_t bytes, const void *out, size_t out_bytes);
+
 // Tokens of sequence i.
 inline int32_t ssm_plan_tokens(const ssm_plan *plan, int32_t i)
 {

@@ -2,6 +2,7 @@
 // the scan's plan for the layer shape (the convolution walks the same tile table), runs the CPU-compiled kernel on
 // fibers and writes the outputs and the checkpointed states.  Buffers are guarded as in emu_main.cpp.
 //   emu_conv_main <in.bin> <out.bin> [order] [end|start]
+// With EMU_IN_PLACE set a sequence with an initial state has it in the slot of its only checkpoint.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -84,8 +85,16 @@ int main(int argc, char **argv)
     void *st = guarded((size_t)(n_ckpt ? n_ckpt : 1) * nst * esz, end_aligned);
     memset(out, 0xFF, nin * esz);  // NaN patterns: every output must be overwritten
     memset(st, 0xFF, (size_t)n_ckpt * nst * esz);
-    if (launch_conv1d_prefill(plan, tiles, seqs, Cch, K, in, w, bias, any_init ? init : nullptr, out, st, act, nullptr) !=
-        hipSuccess) {
+    if (getenv("EMU_IN_PLACE"))
+        for (int b = 0; b < batch; ++b)
+            if (init[b] && cu_ck[b + 1] == cu_ck[b] + 1) {
+                unsigned char *slot = static_cast<unsigned char *>(st) + (size_t)cu_ck[b] * nst * esz;
+                memcpy(slot, init[b], nst * esz);
+                init[b] = slot;
+            }
+    const bool overlap = ssm_states_overlap(init, batch, nst * esz, st, (size_t)n_ckpt * nst * esz);
+    if (launch_conv1d_prefill(plan, tiles, seqs, Cch, K, in, w, bias, any_init ? init : nullptr, out, st, act, nullptr,
+                              nullptr, 0, overlap) != hipSuccess) {
         fprintf(stderr, "launch_conv1d_prefill failed\n");
         return 2;
     }

@@ -535,6 +535,8 @@ void launch_impl(dim3 grid, dim3 block, size_t lds_bytes, void (*fn)(void *), vo
             ids.push_back(b);
     if (ids.empty())
         return;
+    if (getenv("EMU_LAST_BLOCK_FIRST"))
+        std::reverse(ids.begin(), ids.end());
     if (g_cooperative) {
         run_blocks(ids, grid, block, lds_bytes);  // all workgroups resident at once
         return;
