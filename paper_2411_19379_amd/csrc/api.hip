@@ -187,14 +187,23 @@ static void fill_args(const ssm_plan *plan, ScanArgs &args, const void *tiles, c
     args.state_dtype = plan->shape.state_dtype;
 }
 
+// Whether a state that a piece of a cut sequence reads may be one that another piece of the call writes.
+static bool cut_in_place(const ssm_plan *plan, const void *const *init_state_ptrs, const void *state_out)
+{
+    const ssm_shape_t &s = plan->shape;
+    const size_t bytes = (size_t)s.nheads * s.headdim * s.d_state * (s.state_dtype == SSM_ST_F32 ? 4 : 2);
+    return plan->n_continued > 0 && ssm_states_overlap(init_state_ptrs, plan->batch, bytes, state_out, plan->n_ckpt * bytes);
+}
+
 // Launch the scan with the plan's tables at the given device addresses.  The initial states' pointers come as a device
 // array or, for a batch small enough, as the host array itself; both are null when no sequence starts from one.
 static int launch_scan(const ssm_plan *plan, const void *x, const void *dt, const float *A, const void *B,
                        const void *C, const float *D, void *y_out, void *state_out, void *workspace,
                        const void *d_tiles, const void *d_seqs, const void *d_scan_seqs, const void *d_init_ptrs,
-                       const void *const *host_ptrs, hipStream_t stream)
+                       const void *const *host_ptrs, bool states_overlap, hipStream_t stream)
 {
     ScanArgs args;
+    args.states_overlap = states_overlap;
     args.x = x;
     args.dt = dt;
     args.A = A;
@@ -245,7 +254,8 @@ extern "C" int ssm_prefill(const ssm_plan_t *plan,
             return hip_fail("upload of the initial-state pointers", e);
     }
     return launch_scan(plan, x, dt, A, B, C, D, y_out, state_out, workspace, t.tiles, t.seqs, t.scan_seqs,
-                       in_table ? t.ptrs : nullptr, in_args ? init_state_ptrs : nullptr, stream);
+                       in_table ? t.ptrs : nullptr, in_args ? init_state_ptrs : nullptr, cut_in_place(plan, init_state_ptrs, state_out),
+                       stream);
 }
 
 // ---------------------------------------------------------------- the scan for callers that cannot allocate
@@ -332,7 +342,8 @@ extern "C" int ssm_prefill_noalloc(const ssm_plan_t *plan,
         return hip_fail("upload of the plan's tables into the fixed device array", e);
     return launch_scan(plan, x, dt, A, B, C, D, y_out, state_out, workspace, base, base + kScratchSeqsOff,
                        base + kScratchScanSeqsOff, in_table ? base + kScratchPtrsOff : nullptr,
-                       in_args ? init_state_ptrs : nullptr, stream);
+                       in_args ? init_state_ptrs : nullptr, cut_in_place(plan, init_state_ptrs, state_out),
+                       stream);
 }
 
 // ---------------------------------------------------------------- roll-forward / decode step

@@ -116,6 +116,7 @@ struct ScanArgs {
     const void *const *host_ptrs = nullptr;  // the same pointers as a host array
     int32_t n_host_ptrs = 0;                 // its entries, if at most kStatePtrsInArgs: then the device array is not needed
     const int32_t *order = nullptr;          // [batch] the plan's sequences by decreasing number of tokens
+    bool states_overlap = false;             // an initial state shares memory with state_out; asked only for cut sequences
 };
 
 inline StatePtrs state_ptrs_of(const void *const *device_table, const void *const *host, int n)

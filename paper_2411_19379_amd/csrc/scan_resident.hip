@@ -100,6 +100,7 @@ struct ResidentArgs {
     int *spoiled;
     float4 *spoil;
     int H, P, G, blocks, n_items;
+    int kept;                // the cached states of cut sequences have been copied to `spoil`, 32 channels in each one's place
 };
 
 // pi: which of 32 columns or rows an operand lane stands for.
@@ -509,11 +510,16 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
             f = uniform(f + a.decay[(size_t)(slot - m) * a.H + h]);
         }
     } else if (const void *init = a.init.of(p.seq)) {
+        size_t row = state_row;
+        if (a.kept && p.tile_end < p.stop) {
+            init = a.spoil + carry_at(a, p.first, cw);
+            row -= (size_t)cw * kN;
+        }
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float4 v = load_state4(init, state_row + 32 * nb + 16 * (e >> 1) + 4 * (e & 1), ST);
+                const float4 v = load_state4(init, row + 32 * nb + 16 * (e >> 1) + 4 * (e & 1), ST);
                 S[nb][4 * e + 0] = v.x + 0.f;
                 S[nb][4 * e + 1] = v.y + 0.f;
                 S[nb][4 * e + 2] = v.z + 0.f;
@@ -853,6 +859,30 @@ __global__ __launch_bounds__(kThreads, 2) void ssm_scan_resident_kernel(Resident
     }
 }
 
+// ================================================================ states that are updated in place
+// One workgroup per (piece, 256 channels), in front of the scan and only for calls whose cached states share memory with the
+// checkpoints.  The first piece of a cut sequence reads the cached state while the last one may already write its successor to
+// the same place: the first piece takes a copy, in the memory that holds its last state only behind the scan.
+template <int ST>
+__global__ __launch_bounds__(256) void ssm_keep_states_kernel(ResidentArgs a)
+{
+    const int item = ssm_launch_item(blockIdx.x, a.n_items);
+    if (item < 0)
+        return;
+    const SsmPiece p = scalar_load(a.pieces + item / a.blocks);
+    const void *init = a.init.of(p.seq);
+    if (p.part > 0 || p.tile_end == p.stop || !init)
+        return;
+    constexpr int kBytes = 32 * kN * (ST == SSM_ST_F32 ? 4 : 2);
+    const int c0 = item % a.blocks * kResidentChannels;
+    for (int u = 0; u < kResidentChannels / 32; ++u) {
+        const uint4 *from = reinterpret_cast<const uint4 *>(static_cast<const unsigned char *>(init) + (size_t)(c0 / 32 + u) * kBytes);
+        uint4 *to = reinterpret_cast<uint4 *>(a.spoil + carry_at(a, p.first, c0 + 32 * u));
+        for (int m = threadIdx.x; m < kBytes / 16; m += 256)
+            to[m] = from[m];
+    }
+}
+
 // ================================================================ values that are not finite
 // One workgroup per (piece, 256 channels).  A state element that is infinite or NaN stays so, but a piece starts without what
 // has decayed.  Where an earlier piece of the sequence ended with such elements, they are added to the piece's checkpoints
@@ -956,6 +986,13 @@ hipError_t launch_resident_st(const ssm_plan *plan, ResidentArgs a, const SsmPie
     });
     if (attr_err[dev] != hipSuccess)
         return attr_err[dev];
+    if (a.kept) {
+        a.pieces = d_pieces;
+        a.n_items = plan->n_pieces * a.blocks;
+        hipLaunchKernelGGL(ssm_keep_states_kernel<ST>, dim3((unsigned)ssm_launch_blocks(a.n_items)), dim3(256), 0, stream, a);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+    }
     if (plan->n_segments > 0) {
         a.pieces = d_pieces + plan->n_pieces;
         a.n_items = plan->n_segments * a.blocks;
@@ -1013,6 +1050,7 @@ hipError_t launch_scan_resident(const ssm_plan *plan, const ScanArgs &args, cons
     a.G = args.G;
     a.blocks = args.H * args.P / kResidentChannels;
     a.n_items = 0;
+    a.kept = args.states_overlap && plan->n_continued > 0 && (args.init_ptrs || args.host_ptrs);
     a.pieces = nullptr;
     switch (args.state_dtype) {
     case SSM_ST_F16: return launch_resident_st<SSM_ST_F16>(plan, a, d_pieces, stream);

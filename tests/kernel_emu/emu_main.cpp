@@ -197,6 +197,15 @@ int main(int argc, char **argv)
         const size_t np = plan->pieces.size();
         SsmPiece *pieces = static_cast<SsmPiece *>(guarded(sizeof(SsmPiece) * (np ? np : 1), end_aligned));
         memcpy(pieces, plan->pieces.data(), sizeof(SsmPiece) * np);
+        if (getenv("EMU_IN_PLACE"))  // a sequence with an initial state has it in the slot of its only checkpoint
+            for (int b = 0; b < batch; ++b)
+                if (init[b] && cu_ck[b + 1] == cu_ck[b] + 1) {
+                    unsigned char *slot = static_cast<unsigned char *>(args.state_out) + (size_t)cu_ck[b] * nst * st_esz;
+                    memcpy(slot, init[b], nst * st_esz);
+                    init[b] = reinterpret_cast<const float *>(slot);
+                }
+        args.states_overlap = ssm_states_overlap(reinterpret_cast<const void *const *>(init), batch, nst * st_esz, args.state_out,
+                                                 (size_t)n_ckpt * nst * st_esz);
         const hipError_t e = launch_scan_resident(plan, args, pieces, ws, nullptr);
 #else
         const hipError_t e = plan->path == SSM_PATH_MFMA_BF16 ? launch_scan_mfma(plan, args, ws, nullptr)

@@ -211,6 +211,52 @@ def test_gpu_values_that_are_not_finite(what):
         _same_reach(y[k], y_ref, TOL["bf16"])
 
 
+# A cached state that is updated in place: the initial state of a cut sequence is the slot of its only checkpoint.
+def _in_place(shape, lens, device):
+    total = sum(lens)
+    wl = make_workload(2, device, seed=37, batch=1, len_range=(total, total), shape=shape)
+    wl.seqlens, wl.cu_seqlens = list(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    wl.ckpt_pos = [[n] for n in lens]
+    g = torch.Generator(device=device).manual_seed(41)
+    return wl, [torch.randn((shape.nheads, shape.headdim, 128), generator=g, device=device) for _ in lens]
+
+
+@pytest.mark.parametrize("state_type", [None, "f16", "bf16"])
+def test_emulated_states_updated_in_place(emu_resident, tmp_path, monkeypatch, state_type):
+    """The workgroups run from the last to the first."""
+    wl, init = _in_place(LayerShape(8, 64, 128, 2, 64, "bf16"), [200, 40, 131], "cpu")
+    monkeypatch.setenv("EMU_PIECES", "1")
+    monkeypatch.setenv("EMU_SEGMENTS", "1")
+    want = _emulate(emu_resident, wl, init, tmp_path, 0, "end", state_type=state_type)[2]
+    monkeypatch.setenv("EMU_LAST_BLOCK_FIRST", "1")
+    monkeypatch.setenv("EMU_IN_PLACE", "1")
+    assert np.array_equal(_emulate(emu_resident, wl, init, tmp_path, 0, "end", state_type=state_type)[2], want)
+
+
+@pytest.mark.gpu
+def test_gpu_states_updated_in_place():
+    import paper_2411_19379_amd as ssm
+
+    wl, init = _in_place(LayerShape(8, 64, 128, 2, 64, "bf16"), [5000, 90, 9000], "cuda:0")
+    plan = ssm.Plan(8, 64, 128, 2, 64, "bf16", wl.cu_seqlens, wl.ckpt_pos)
+    i = wl.inputs
+
+    def run(states, out):
+        y = torch.empty_like(i.x)
+        ssm.prefill(plan, i.x, i.dt, wl.A, i.B, i.C, wl.D, states, y_out=y, state_out=out)
+        torch.cuda.synchronize()
+        return y
+
+    apart = torch.empty((3, 8, 64, 128), device="cuda:0")
+    want = run(init, apart)
+    for rep in range(20):
+        print(f"in place, pass {rep}", flush=True)
+        states = torch.stack(init)
+        assert torch.equal(run(list(states), states).view(torch.int16), want.view(torch.int16))
+        assert torch.equal(states, apart)
+    plan.close()
+
+
 # on the GPU: batches that the plan gives to this scan, H, P, G, lengths, decay, type of the cached states
 GPU_CASES = {
     "many_short": (32, 64, 2, [130, 65, 1, 64, 63, 0] * 48, 1.0, "f32"),   # several rounds of uncut pieces
