@@ -307,6 +307,7 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
     std::vector<SsmPiece> segments;
     plan->pieces.clear();
     plan->n_continued = 0;
+    int32_t most_slots = 0;
     for (int32_t i = 0; i < plan->batch; ++i) {
         const int64_t begin = plan->seqs[i].tile_begin, n = plan->seqs[i].tile_end - begin;
         const int64_t parts = (n + most - 1) / most;
@@ -318,6 +319,7 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
             p.seq = i;
             p.slot = (int32_t)segments.size() - 1;
             p.back = back;
+            most_slots = std::max(most_slots, back);
             p.stop = (int32_t)(begin + n);
             p.part = (int32_t)k;
             p.first = plan->n_continued;
@@ -345,6 +347,7 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
                      [](const SsmPiece &a, const SsmPiece &b) { return a.stop - a.tile_end < b.stop - b.tile_end; });
     plan->n_pieces = (int32_t)plan->pieces.size();
     plan->n_segments = (int32_t)segments.size();
+    plan->n_groups = most_slots > kMostSlots ? plan->n_segments / kGroupSlots : 0;
     plan->pieces.insert(plan->pieces.end(), segments.begin(), segments.end());
 }
 
@@ -352,9 +355,10 @@ SsmPieceWorkspace ssm_piece_workspace(const ssm_plan *plan)
 {
     const size_t H = (size_t)plan->shape.nheads, state = H * plan->shape.headdim * plan->shape.d_state * sizeof(float);
     SsmPieceWorkspace w;
-    w.spoil = plan->n_segments * state;
+    const size_t slots = (size_t)plan->n_segments + plan->n_groups;
+    w.spoil = slots * state;
     w.decay = w.spoil + plan->n_continued * state;
-    w.spoiled = (w.decay + plan->n_segments * H * sizeof(float) + 15) / 16 * 16;
+    w.spoiled = (w.decay + slots * H * sizeof(float) + 15) / 16 * 16;
     w.total = w.spoiled + plan->n_continued * (H * plan->shape.headdim / 32) * sizeof(int32_t);
     return w;
 }

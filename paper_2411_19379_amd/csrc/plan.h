@@ -112,6 +112,7 @@ struct ssm_plan {
     // Scan with resident states only: the pieces in launch order (longest first) and, behind them, the segments.
     bool resident = false;
     int32_t n_pieces = 0, n_segments = 0, n_continued = 0;  // n_continued: pieces that others continue
+    int32_t n_groups = 0;  // of kGroupSlots slots, whose sums are made for the pieces far behind them
     std::vector<SsmPiece> pieces;
     // Device copies of the two tables and a buffer for the per-call state
     // pointers, one set per GPU the plan has been used on.  A cache behind a
@@ -138,8 +139,8 @@ void ssm_plan_build_stretches(ssm_plan *plan, int64_t per_round, int32_t min_til
 
 // Scan with resident states: (re)builds the pieces, of at most `most` tiles each, and the segments, of at most `segment`.
 void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment);
-// Its workspace, in byte offsets: from 0 on an fp32 state per segment, then one per continued piece, the segments' total
-// decay per head, a flag per continued piece and 32 channels.  Empty unless a sequence is cut.
+// Its workspace, in byte offsets: from 0 on an fp32 state per segment and group, then one per continued piece, the segments'
+// and groups' total decay per head, a flag per continued piece and 32 channels.  Empty unless a sequence is cut.
 struct SsmPieceWorkspace {
     size_t spoil = 0, decay = 0, spoiled = 0, total = 0;
 };
@@ -199,6 +200,10 @@ constexpr int kResidentPerRound = 256;
 constexpr int kMostAddedPieces = 255;
 constexpr int kMinPieceTiles = 4;
 constexpr int kSegmentTiles = 32;
+// With slow decay a piece sums up all slots in front of it, 0.85 us each.  Where a piece may have more than kMostSlots in front
+// of it, another kernel adds up every kGroupSlots of them; below that it does not repay its launch (3 us).
+constexpr int kGroupSlots = 8;
+constexpr int kMostSlots = 32;
 
 // A sequence is cut into stretches only if each gets at least this many tiles (the second kernel's work per stretch
 // does not shrink with the stretch), and only if it has at least kMfmaMinCutTiles tiles: at 128 tiles two stretches

@@ -76,6 +76,25 @@ def test_emulated_scan_matches_oracle(emu_resident, tmp_path, monkeypatch, case,
         assert np.array_equal(first, raw), f"wave order {order} changes the result: LDS race"
 
 
+@pytest.mark.parametrize("a_scale", [(0.01, 0.01, 0.01, 0.01), (0.01, 400.0, 3.0, 30.0)])
+def test_emulated_sums_of_segments(emu_resident, tmp_path, monkeypatch, a_scale):
+    """Pieces with up to 40 segments of 16 tokens in front of them, of which groups of eight are summed up for the pieces far
+    behind: groups that are needed, that hold two sequences, and that strong decay leaves out."""
+    total = sum(lens := [200, 650, 300])
+    wl = make_workload(2, "cpu", seed=43, batch=1, len_range=(total, total), shape=LayerShape(4, 64, 128, 1, 16, "bf16"))
+    wl.seqlens, wl.cu_seqlens = lens, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    wl.ckpt_pos = [[100, 200], [648], []]
+    wl.A = wl.A * torch.tensor(a_scale)
+    init = [torch.randn((4, 64, 128), generator=torch.Generator().manual_seed(k)) for k in range(3)]
+    y_ref, st_ref = _oracle(wl, init)
+    monkeypatch.setenv("EMU_PIECES", "1")
+    monkeypatch.setenv("EMU_SEGMENTS", "1")
+    for order, align in ((0, "end"), (7, "start")):
+        y, st, _ = _emulate(emu_resident, wl, init, tmp_path, order, align)
+        assert max(rel_err(y, y_ref)) <= TOL["bf16"]
+        assert max(rel_err(st.astype(np.float64), st_ref)) <= TOL["bf16"]
+
+
 # What is not finite in an input, or becomes so in fp16, must reach what it reaches in the other matrix-core scan and nothing
 # more.  One sequence of 150 tokens; heads of the usual decay, of one whose tiles leave the range of the masks' factors and of
 # ones in between (16 with steps of 0.1 is the end of the usual ranges).
@@ -262,6 +281,7 @@ GPU_CASES = {
     "many_short": (32, 64, 2, [130, 65, 1, 64, 63, 0] * 48, 1.0, "f32"),   # several rounds of uncut pieces
     "cut": (16, 64, 1, [33000], 1.0, "f32"),                               # pieces that start from segments
     "cut_slow_decay": (16, 64, 1, [17001, 9000], 0.01, "f32"),             # whose segments all count
+    "sums_of_segments": (8, 64, 2, [33000], 0.01, "f32"),                  # 128 pieces
     "p128_f16": (8, 128, 2, [20011, 15000], 1.0, "f16"),
     "p256_bf16": (4, 256, 1, [24000], 1.0, "bf16"),
 }
