@@ -5,7 +5,6 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
-#include <functional>
 #include <map>
 #include <new>
 #include <numeric>
@@ -306,6 +305,7 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
 {
     std::vector<SsmPiece> segments;
     plan->pieces.clear();
+    plan->pieces.reserve(plan->batch + kMostAddedPieces);
     plan->n_continued = 0;
     int32_t most_slots = 0;
     for (int32_t i = 0; i < plan->batch; ++i) {
@@ -339,9 +339,9 @@ void ssm_plan_build_pieces(ssm_plan *plan, int32_t most, int32_t segment)
         }
         plan->n_continued += parts > 0 ? (int32_t)parts - 1 : 0;
     }
-    std::stable_sort(plan->pieces.begin(), plan->pieces.end(), [](const SsmPiece &a, const SsmPiece &b) {
-        return a.tile_end - a.tile_begin > b.tile_end - b.tile_begin;
-    });
+    auto longer = [](const SsmPiece &a, const SsmPiece &b) { return a.tile_end - a.tile_begin > b.tile_end - b.tile_begin; };
+    if (!std::is_sorted(plan->pieces.begin(), plan->pieces.end(), longer))
+        std::stable_sort(plan->pieces.begin(), plan->pieces.end(), longer);
     // those at the end of their piece first: the others may turn out to have decayed to nothing by then
     std::stable_sort(segments.begin(), segments.end(),
                      [](const SsmPiece &a, const SsmPiece &b) { return a.stop - a.tile_end < b.stop - b.tile_end; });
@@ -363,26 +363,43 @@ SsmPieceWorkspace ssm_piece_workspace(const ssm_plan *plan)
     return w;
 }
 
-// Tiles that the busiest of `places` workgroups-at-a-time works through, for pieces (or stretches) of `lengths` tiles,
-// longest first, `copies` workgroups each, dealt out in order as places become free.  `fill` is the busy share of it all.
-static double ssm_busiest(const std::vector<int64_t> &lengths, int64_t copies, int64_t places, double *fill)
+// Pieces (or stretches) of equal length.
+struct LengthRun {
+    int64_t tiles, count;
+};
+static void add_run(std::vector<LengthRun> &runs, int64_t tiles, int64_t count)
 {
-    int64_t all = 0;
-    for (int64_t v : lengths)
-        all += v;
+    if (!runs.empty() && runs.back().tiles == tiles)
+        runs.back().count += count;
+    else if (count > 0)
+        runs.push_back({tiles, count});
+}
+
+// Tiles that the busiest of `places` workgroups-at-a-time works through, for pieces (or stretches) of the lengths of `runs`,
+// longest first, `copies` workgroups each, dealt out in order as places become free.  `fill` is the busy share of it all.
+// (Every plan passes through here, those of one decode step among them: runs instead of single sequences, and rounds of equal
+// ones in one step, take the plan of 256 one-token sequences from 34 to 14 us, of 64 from 11 to 4.)
+static double ssm_busiest(const std::vector<LengthRun> &runs, int64_t copies, int64_t places, double *fill)
+{
+    int64_t all = 0, n = 0;
+    for (const LengthRun &r : runs) {
+        all += r.tiles * r.count;
+        n += r.count * copies;
+    }
     const double share = (double)all * copies / places;
-    const int64_t n = (int64_t)lengths.size() * copies, longest = lengths.empty() ? 0 : lengths[0];
+    const int64_t longest = runs.empty() ? 0 : runs[0].tiles;
     double busiest = (double)longest;
     if (n > 64 * places) {
         busiest = std::max(busiest, share + 0.25 * longest);
     } else if (n > places) {
         std::map<int64_t, int64_t> ends;  // when places become free: how many
         ends[0] = places;
-        for (int64_t v : lengths)
-            for (int64_t left = copies; v > 0 && left > 0;) {
+        for (const LengthRun &r : runs)
+            for (int64_t left = r.tiles > 0 ? copies * r.count : 0; left > 0;) {
                 const auto first = ends.begin();
-                const int64_t end = first->first + v, taken = std::min(left, first->second);
-                left -= taken;
+                const int64_t rounds = first->second == places ? std::max<int64_t>(1, left / places) : 1;
+                const int64_t end = first->first + r.tiles * rounds, taken = std::min(left, first->second);
+                left -= taken * rounds;
                 if (taken == first->second)
                     ends.erase(first);
                 else
@@ -413,10 +430,11 @@ static void ssm_plan_choose_pieces(ssm_plan *plan)
     if (s.headdim < 64 || kResidentChannels % s.headdim != 0 || group % kResidentChannels != 0 || plan->tiles.empty())
         return;
     const int64_t blocks = channels / kResidentChannels;
-    std::vector<int64_t> lengths;
-    for (const SsmScanSeq &q : plan->scan_seqs)
-        lengths.push_back(q.tile_end - q.tile_begin);
-    std::sort(lengths.begin(), lengths.end(), std::greater<int64_t>());
+    std::vector<LengthRun> lengths;  // of the stretches, then of the sequences
+    for (const SsmScanSeq &r : plan->scan_seqs) {
+        const SsmScanSeq &q = plan->scan_seqs[r.by_length];
+        add_run(lengths, q.tile_end - q.tile_begin, 1);
+    }
     double fill = 0;
     const bool wide = s.headdim / plan->p_split == kMfmaWideChannels;
     double other = ssm_busiest(lengths, (int64_t)s.nheads * plan->p_split, kMfmaWorkgroupsPerRound, &fill);
@@ -425,35 +443,39 @@ static void ssm_plan_choose_pieces(ssm_plan *plan)
     if (plan->n_carry > 0)
         other += 20.0 + 0.25 * plan->n_carry * (double)channels / kMfmaWideChannels;
 
-    int64_t longest = 0;
-    lengths.clear();
-    for (const SsmSeq &q : plan->seqs) {
-        lengths.push_back(q.tile_end - q.tile_begin);
-        longest = std::max(longest, lengths.back());
+    auto longer = [](const LengthRun &a, const LengthRun &b) { return a.tiles > b.tiles; };
+    if (plan->n_carry > 0) {  // else the stretches are the sequences
+        lengths.clear();
+        for (const SsmSeq &q : plan->seqs)
+            add_run(lengths, q.tile_end - q.tile_begin, 1);
+        std::sort(lengths.begin(), lengths.end(), longer);
     }
+    const int64_t longest = lengths[0].tiles;
     auto pieces_of = [&](int64_t most) {
         int64_t n = 0;
-        for (int64_t v : lengths)
-            n += (v + most - 1) / most;
+        for (const LengthRun &r : lengths)
+            n += (r.tiles + most - 1) / most * r.count;
         return n;
     };
     double best = other;
     int64_t best_most = 0;
     auto consider = [&](int64_t most) {
-        std::vector<int64_t> pieces;
+        std::vector<LengthRun> pieces;
         int64_t counted = 0, added = 0;
-        for (int64_t v : lengths) {
-            const int64_t parts = (v + most - 1) / most;
-            for (int64_t k = 0; k < parts; ++k)
-                pieces.push_back(v * (k + 1) / parts - v * k / parts);
+        for (const LengthRun &r : lengths) {
+            if (r.tiles == 0)
+                continue;
+            const int64_t parts = (r.tiles + most - 1) / most, more = r.tiles % parts;  // `more` of them have a tile more
+            add_run(pieces, r.tiles / parts + 1, more * r.count);
+            add_run(pieces, r.tiles / parts, (parts - more) * r.count);
             if (parts > 1) {
-                added += parts - 1;
-                counted += (parts - 1) * std::min<int64_t>(v / parts, 48);
+                added += (parts - 1) * r.count;
+                counted += (parts - 1) * std::min<int64_t>(r.tiles / parts, 48) * r.count;
             }
         }
         if (added > kMostAddedPieces)
             return;
-        std::sort(pieces.begin(), pieces.end(), std::greater<int64_t>());
+        std::sort(pieces.begin(), pieces.end(), longer);
         const double tiles = ssm_busiest(pieces, blocks, kResidentPerRound, &fill);
         double t = 15.0 + tiles * (3.9 + 1.1 * fill * fill * fill * fill);
         if (added > 0)
