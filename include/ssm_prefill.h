@@ -78,9 +78,10 @@ typedef struct {
     int32_t n_tiles;       /* token tiles the kernels walk (sequence-local, split at checkpoints) */
     int32_t tile_tokens;   /* upper bound of a tile's length */
     int32_t path;          /* SSM_PATH_* */
-    int32_t n_workgroups;  /* grid size of the matrix-core scan; (sequence, head) pairs on the fp32 path */
-    int32_t n_stretches;   /* stretches the scan walks: one per sequence, more when long sequences are cut
-                              (ssm_plan_stretch) */
+    int32_t n_workgroups;  /* workgroups of the matrix-core scan that walks stretches; (sequence, head) pairs on the
+                              fp32 path */
+    int32_t n_stretches;   /* stretches of that scan: one per sequence, more when long sequences are cut
+                              (ssm_plan_stretch, which also says when another scan runs instead) */
 } ssm_plan_info_t;
 
 /*
@@ -117,7 +118,7 @@ int ssm_plan_info(const ssm_plan_t *plan, ssm_plan_info_t *info);
 int ssm_plan_tile(const ssm_plan_t *plan, int32_t i, int32_t *tok0, int32_t *len,
                   int32_t *seq, int32_t *ckpt_slot);
 
-/* Launch order of the matrix-core scan, for inspection: how the planner spreads the chunked prefill of Section 4.1
+/* Launch order of the matrix-core scan that walks stretches (ssm_plan_stretch), for inspection: how the planner spreads the chunked prefill of Section 4.1
  * over the GPU when the batch mixes long and short requests (the request mix of Section 5.1's traces).  Work items
  * are (rank of a non-empty sequence by decreasing tile count, head, channel slice), numbered by rank, then head, then
  * slice; the launch has n_blocks workgroups, dealt round-robin to the GPU's 8 dies, and ssm_plan_launch_item tells
@@ -142,7 +143,8 @@ int ssm_plan_launch_item(const ssm_plan_t *plan, int64_t block, int32_t *item);
  * adds to their outputs and checkpoints (the recurrence of Section 2.1's state update is linear in the state) is added
  * by a second kernel of the same call.  Results are those of the plain scan up to rounding.  Plans with enough work
  * to fill the GPU with workgroups of 256 channels take a scan that cuts sequences by a rule of its own; the stretches
- * listed here are those of the other one.  Any output pointer may be NULL; SSM_ERR_INVALID_ARG if the plan is NULL or i is out of range. */
+ * listed here, their launch order and their workgroups are those of the other one.  Any output pointer may be NULL;
+ * SSM_ERR_INVALID_ARG if the plan is NULL or i is out of range. */
 int ssm_plan_stretch(const ssm_plan_t *plan, int32_t i, int32_t *tile_begin, int32_t *tile_end,
                      int32_t *starts_from_zero);
 
@@ -158,7 +160,7 @@ int ssm_plan_workspace_bytes(const ssm_plan_t *plan, size_t *bytes);
  * the default stream): the chunked prefill of Section 4.1 with cached-state
  * resume (Section 2.2) and exact-position checkpoints.
  *
- * Synchronisation: the first call with a plan on a GPU makes three small
+ * Synchronisation: the first call with a plan on a GPU makes four small
  * device allocations owned by the plan and waits once for the upload of the
  * plan's tables on `hip_stream`; every later call with that plan only
  * enqueues and never synchronises.  The plan itself is not modified (the

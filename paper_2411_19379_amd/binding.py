@@ -7,7 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import List, Optional, Sequence
+from typing import NamedTuple, List, Optional, Sequence
 
 import numpy as np
 
@@ -79,6 +79,8 @@ def load_library():
     lib.ssm_plan_launch_item.argtypes = [vp, ctypes.c_int64, i32p]
     lib.ssm_plan_stretch.restype = ctypes.c_int
     lib.ssm_plan_stretch.argtypes = [vp, ctypes.c_int32, i32p, i32p, i32p]
+    lib.ssm_plan_scan.restype = ctypes.c_int
+    lib.ssm_plan_scan.argtypes = [vp, i32p, i32p, i32p, i32p, i32p]
     lib.ssm_plan_tile.restype = ctypes.c_int
     lib.ssm_plan_tile.argtypes = [vp, ctypes.c_int32, i32p, i32p, i32p, i32p]
     lib.ssm_plan_workspace_bytes.restype = ctypes.c_int
@@ -226,6 +228,14 @@ def ssm_conv1d_prefill(plan: int, channels: int, kernel_width: int, xin: int, we
                                              hip_stream))
 
 
+class PlanScan(NamedTuple):
+    kind: str         # "resident", "stretches" or "fp32"
+    n_pieces: int     # of the scan with resident states: what its workgroups walk,
+    n_segments: int   # what those of the kernel in front walk,
+    n_continued: int  # the pieces that others continue,
+    n_groups: int     # and the sums of segments
+
+
 class Plan:
     """Owns an ssm_plan_t for one packed batch."""
 
@@ -255,6 +265,13 @@ class Plan:
 
     def stretches(self):
         return [ssm_plan_stretch(self.handle, i) for i in range(self.info.n_stretches)]
+
+    def scan(self):
+        """Which scan the plan takes and, of the one with resident states, the table it walks."""
+        v = [ctypes.c_int32() for _ in range(5)]
+        _check(load_library().ssm_plan_scan(self.handle, *[ctypes.byref(c) for c in v]))
+        path = "fp32" if self.info.path == SSM_PATH_VALU_F32 else "resident" if v[0].value else "stretches"
+        return PlanScan(path, *[c.value for c in v[1:]])
 
     def workspace(self, device):
         """The plan's device workspace as a torch tensor (allocated once per device, reused by every call)."""

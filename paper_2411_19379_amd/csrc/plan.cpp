@@ -538,6 +538,19 @@ extern "C" int ssm_plan_info(const ssm_plan_t *plan, ssm_plan_info_t *info)
     return SSM_OK;
 }
 
+extern "C" int ssm_plan_scan(const ssm_plan_t *plan, int32_t *resident, int32_t *n_pieces, int32_t *n_segments,
+                             int32_t *n_continued, int32_t *n_groups)
+{
+    if (!plan)
+        return fail(SSM_ERR_INVALID_ARG, "plan is NULL");
+    if (resident) *resident = plan->resident;
+    if (n_pieces) *n_pieces = plan->n_pieces;
+    if (n_segments) *n_segments = plan->n_segments;
+    if (n_continued) *n_continued = plan->n_continued;
+    if (n_groups) *n_groups = plan->n_groups;
+    return SSM_OK;
+}
+
 extern "C" int ssm_plan_tile(const ssm_plan_t *plan, int32_t i, int32_t *tok0, int32_t *len,
                              int32_t *seq, int32_t *ckpt_slot)
 {

@@ -149,6 +149,11 @@ SsmPieceWorkspace ssm_piece_workspace(const ssm_plan *plan);
 // Whether any of the (host array of) `n` states of `bytes` bytes, null entries aside, shares memory with `out`.
 bool ssm_states_overlap(const void *const *states, int32_t n, size_t bytes, const void *out, size_t out_bytes);
 
+// For tests and the benchmark, beside the interface: which matrix-core scan the plan takes and, if that is the one with resident
+// states, what it walks.  Any output pointer may be null.
+extern "C" int ssm_plan_scan(const ssm_plan_t *plan, int32_t *resident, int32_t *n_pieces, int32_t *n_segments,
+                             int32_t *n_continued, int32_t *n_groups);
+
 // Tokens of sequence i.
 inline int32_t ssm_plan_tokens(const ssm_plan *plan, int32_t i)
 {

@@ -275,3 +275,25 @@ def test_stretch_queries_reject_bad_indices_and_cover_the_fp32_path():
     with pytest.raises(ssm.SsmError):
         ssm.ssm_plan_stretch(q.handle, 2)
     q.close()
+
+
+@pytest.mark.parametrize("H,G,P,lens,want", [
+    (128, 8, 64, [131072], ("resident", 8, 56, 7, 7)),   # eight pieces, each of the first seven in eight segments
+    (128, 8, 64, [8192] * 16, ("resident", 16, 0, 0, 0)),  # nothing to cut
+    (128, 8, 64, [32768], ("stretches", 0, 0, 0, 0)),
+    (80, 1, 64, [2048], ("stretches", 0, 0, 0, 0)),
+    (128, 8, 64, [137], ("stretches", 0, 0, 0, 0)),
+    (16, 1, 64, [33000], ("resident", 58, 57, 57, 7)),
+    (16, 8, 64, [33000], ("stretches", 0, 0, 0, 0)),     # groups of 128 channels
+    (16, 1, 32, [33000], ("stretches", 0, 0, 0, 0)),     # 32 channels per head
+])
+def test_scan_that_a_plan_takes(H, G, P, lens, want):
+    p = ssm.Plan(H, P, 128, G, 64, "bf16", np.concatenate([[0], np.cumsum(lens)]).tolist(), None)
+    assert p.scan() == want
+    p.close()
+
+
+def test_scan_of_an_fp32_plan():
+    p = ssm.Plan(4, 16, 16, 1, 64, "f32", [0, 100], None)
+    assert p.scan() == ("fp32", 0, 0, 0, 0)
+    p.close()

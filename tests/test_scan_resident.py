@@ -23,6 +23,7 @@ CASES = {
     # decay up to 400 times the usual: the masks' exact branch, and pieces that nothing in front of them reaches
     "strong_decay": ((4, 64, 128, 1, 64), 2, dict(batch=2, len_range=(60, 200), a_scale=[1.0, 40.0, 400.0, 0.01])),
     # a hundredth of it: everything in front of a piece reaches all of it
+    "p256": ((2, 256, 128, 1, 64), 2, dict(batch=2, len_range=(60, 200))),
     "slow_decay": ((4, 64, 128, 1, 64), 2, dict(batch=2, len_range=(300, 400), a_scale=[0.01, 0.01, 0.02, 0.03])),
 }
 
@@ -93,6 +94,19 @@ def test_emulated_sums_of_segments(emu_resident, tmp_path, monkeypatch, a_scale)
         y, st, _ = _emulate(emu_resident, wl, init, tmp_path, order, align)
         assert max(rel_err(y, y_ref)) <= TOL["bf16"]
         assert max(rel_err(st.astype(np.float64), st_ref)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("a_scale", [0.002, 1.0])
+def test_emulated_segments_longer_than_the_windows_looked_back_over(emu_resident, tmp_path, monkeypatch, a_scale):
+    """A piece of 18 tiles that another continues: its segment looks back over more than 1024 tokens, or stops before."""
+    wl = make_workload(4, "cpu", seed=47, shape=LayerShape(4, 64, 128, 1, 64, "bf16"), seqlen=2300, ckpt_every=1150)
+    wl.A = wl.A * a_scale
+    init = [torch.randn((4, 64, 128), generator=torch.Generator().manual_seed(3))]
+    y_ref, st_ref = _oracle(wl, init)
+    monkeypatch.setenv("EMU_PIECES", "19")
+    y, st, _ = _emulate(emu_resident, wl, init, tmp_path, 0, "end")
+    assert max(rel_err(y, y_ref)) <= TOL["bf16"]
+    assert max(rel_err(st.astype(np.float64), st_ref)) <= TOL["bf16"]
 
 
 # What is not finite in an input, or becomes so in fp16, must reach what it reaches in the other matrix-core scan and nothing
@@ -276,14 +290,25 @@ def test_gpu_states_updated_in_place():
     plan.close()
 
 
-# on the GPU: batches that the plan gives to this scan, H, P, G, lengths, decay, type of the cached states
+# on the GPU: batches that the plan gives to this scan, H, P, G, lengths, decay, type of the cached states; then pieces, segments,
+# continued pieces and sums of segments
 GPU_CASES = {
-    "many_short": (32, 64, 2, [130, 65, 1, 64, 63, 0] * 48, 1.0, "f32"),   # several rounds of uncut pieces
-    "cut": (16, 64, 1, [33000], 1.0, "f32"),                               # pieces that start from segments
-    "cut_slow_decay": (16, 64, 1, [17001, 9000], 0.01, "f32"),             # whose segments all count
-    "sums_of_segments": (8, 64, 2, [33000], 0.01, "f32"),                  # 128 pieces
-    "p128_f16": (8, 128, 2, [20011, 15000], 1.0, "f16"),
-    "p256_bf16": (4, 256, 1, [24000], 1.0, "bf16"),
+    # several rounds of uncut pieces
+    "many_short": (32, 64, 2, [130, 65, 1, 64, 63, 0] * 48, 1.0, "f32", (240, 0, 0, 0)),
+    # the same with tiles that leave the range of the masks' factors
+    "many_short_strong_decay": (32, 64, 2, [130, 65, 1, 64, 63, 0] * 48, 60.0, "f32", (240, 0, 0, 0)),
+    # pieces that start from segments
+    "cut": (16, 64, 1, [33000], 1.0, "f32", (58, 57, 57, 7)),
+    # whose segments all count
+    "cut_slow_decay": (16, 64, 1, [17001, 9000], 0.01, "f32", (60, 58, 58, 7)),
+    # and of which hardly any does
+    "cut_strong_decay": (16, 64, 1, [33000], 60.0, "f32", (58, 57, 57, 7)),
+    # 103 segments in front of the last piece, summed up in eights
+    "sums_of_segments": (8, 64, 2, [33000], 0.01, "f32", (104, 103, 103, 12)),
+    # pieces of more than 2000 tokens, in two segments, all of which count
+    "long_pieces_slow_decay": (32, 64, 2, [67700], 0.002, "f32", (32, 62, 31, 7)),
+    "p128_f16": (8, 128, 2, [20011, 15000], 1.0, "f16", (62, 60, 60, 7)),
+    "p256_bf16": (4, 256, 1, [24000], 1.0, "bf16", (63, 62, 62, 7)),
 }
 
 
@@ -295,7 +320,7 @@ def test_gpu_matches_oracle(case):
     from helpers import gpu_run
     from test_gpu_configs import compare_all_heads
 
-    H, P, G, lens, a_scale, state = GPU_CASES[case]
+    H, P, G, lens, a_scale, state, walked = GPU_CASES[case]
     total = sum(lens)
     wl = make_workload(2, "cuda", seed=61, batch=1, len_range=(total, total), shape=LayerShape(H, P, 128, G, 64, "bf16"))
     wl.seqlens, wl.cu_seqlens = list(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -304,6 +329,9 @@ def test_gpu_matches_oracle(case):
     kind = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[state]
     init = [None if i % 2 else (0.5 * torch.randn(H, P, 128, device="cuda")).to(kind) for i in range(len(lens))]
     ref = [None if v is None else v.float().cpu().numpy() for v in init]
+    import paper_2411_19379_amd as ssm
+    plan = ssm.Plan(H, P, 128, G, 64, "bf16", wl.cu_seqlens, wl.ckpt_pos, state_dtype=state)
+    assert plan.scan() == ("resident", *walked)
+    plan.close()
     y, states, info = gpu_run(wl, init, state_dtype=state)
-    assert info.path == 1
     compare_all_heads(wl, y, states.float(), ref, tol={"f32": TOL["bf16"], "f16": 2e-2, "bf16": 2.5e-2}[state], block=H)

@@ -40,18 +40,20 @@ def test_noalloc_entry_matches_ssm_prefill(io):
         assert not torch.isnan(y.float()).any() and not torch.isnan(st[: wl.n_ckpt]).any()
 
 
-def test_noalloc_entry_with_sequences_cut_into_stretches():
-    """A batch small enough for the plan to cut its long sequence into stretches: the stretch table travels through
-    the fixed device array too, and the kernels behind the scan run in the same call."""
+@pytest.mark.parametrize("kind,G", [("resident", 2), ("stretches", 4)])
+def test_noalloc_entry_with_sequences_cut_into_stretches(kind, G):
+    """A batch small enough for the plan to cut its long sequence, into stretches or into the pieces of the scan with resident
+    states: their table travels through the fixed device array too, and the kernels beside the scan run in the same call."""
     import paper_2411_19379_amd as ssm
-    shape = LayerShape(8, 64, 128, 2, 256, "bf16")
+    shape = LayerShape(8, 64, 128, G, 256, "bf16")
     big = make_workload(2, DEV, seed=311, batch=2, len_range=(10300, 13000), shape=shape)
     small = make_workload(2, DEV, seed=312, batch=1, len_range=(10300, 10300), shape=shape)
     for wl in (big, small):
         s = wl.shape
         plan = ssm.Plan(s.nheads, s.headdim, s.d_state, s.ngroups, s.chunk, s.io_dtype, wl.cu_seqlens, wl.ckpt_pos)
-        n_stretches = plan.info.n_stretches
+        n_stretches, scan = plan.info.n_stretches, plan.scan()
         plan.close()
+        assert scan.kind == kind and (kind == "stretches" or scan.n_continued > 0)
         print(f"noalloc, cut: {wl.seqlens} tokens in {n_stretches} stretches", flush=True)
         assert n_stretches > wl.batch
         init = list(wl.init_state)
@@ -73,19 +75,23 @@ def test_noalloc_rejects_oversized_plans():
     plan.close()
 
 
-@pytest.mark.parametrize("lens", [(100, 700), (10300, 11000)])
-def test_noalloc_entry_under_graph_capture(lens):
+@pytest.mark.parametrize("lens,kind,G", [((100, 700), "stretches", 2), ((10300, 11000), "resident", 2),
+                                         ((10300, 11000), "stretches", 4)])
+def test_noalloc_entry_under_graph_capture(lens, kind, G):
     """What the entry point is for: a caller that records its work into a HIP graph and may not allocate while it
     does.  The call is captured once (after one eager call, which sets the per-device tables' address up) and
     replayed several times with eager work and synchronisations in between; every replay, on inputs refreshed in
-    place, equals the eager result.  With the longer requests the plan cuts sequences into stretches, and the kernels
-    that carry the states over are part of the recorded call."""
+    place, equals the eager result.  With the longer requests the plan cuts sequences, into stretches or into pieces, and the
+    kernels that carry the states over or make those the pieces start from are part of the recorded call."""
     import paper_2411_19379_amd as ssm
-    shape = LayerShape(8, 64, 128, 2, 256, "bf16")
+    shape = LayerShape(8, 64, 128, G, 256, "bf16")
     wl = make_workload(2, DEV, seed=303, batch=3, len_range=lens, shape=shape)
     init = list(wl.init_state)
     s = wl.shape
     plan = ssm.Plan(s.nheads, s.headdim, s.d_state, s.ngroups, s.chunk, s.io_dtype, wl.cu_seqlens, wl.ckpt_pos)
+    scan = plan.scan()
+    assert scan.kind == kind and (kind == "stretches" or scan.n_groups > 0)
+    assert plan.info.n_stretches > wl.batch or lens[0] < 10300
     plan.workspace(torch.device(DEV))  # allocated before the capture
     x = wl.inputs.x.clone()
     y = torch.empty_like(x)
