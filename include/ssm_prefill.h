@@ -150,7 +150,7 @@ int ssm_plan_stretch(const ssm_plan_t *plan, int32_t i, int32_t *tile_begin, int
 
 /* Bytes of device workspace ssm_prefill needs for this plan (may be 0): the
  * per-(tile, group) operands that the heads of a group share in the chunked
- * scan of Section 4.1.  The caller allocates it, 256-byte aligned, owns it,
+ * scan of Section 4.1, or the states that the parts of cut sequences start from.  The caller allocates it, 256-byte aligned, owns it,
  * and may reuse it between calls that do not overlap; its contents mean
  * nothing between calls. */
 int ssm_plan_workspace_bytes(const ssm_plan_t *plan, size_t *bytes);

@@ -619,14 +619,10 @@ extern "C" int ssm_plan_workspace_bytes(const ssm_plan_t *plan, size_t *bytes)
 {
     if (!plan || !bytes)
         return fail(SSM_ERR_INVALID_ARG, "plan or bytes is NULL");
-    // The running state never leaves the chip between tiles; the matrix-core scan needs room for the operands
-    // that the heads of a group share (written by its first kernel, read by its second) and, when it cuts long
-    // sequences into stretches, for the states carried from one stretch to the next and each tile's total decay.  The scan
-    // with resident states needs some only if it cuts a sequence: a state and a decay per segment, a state per continued
-    // piece.  A plan's requirement
-    // is the larger of the two, whichever scan it takes.
-    *bytes = ssm_mfma_workspace(plan).total;
-    if (plan->resident)
-        *bytes = std::max(*bytes, ssm_piece_workspace(plan).total);
+    // The running state never leaves the chip between tiles.  The scan with stretches needs room for the operands that the heads
+    // of a group share (written by its first kernel, read by its second) and, when it cuts long sequences, for the states
+    // carried from one stretch to the next and each tile's total decay.  The scan with resident states needs some only if it
+    // cuts a sequence: a state and a decay per segment and sum of segments, a state per continued piece.
+    *bytes = plan->resident ? ssm_piece_workspace(plan).total : ssm_mfma_workspace(plan).total;
     return SSM_OK;
 }

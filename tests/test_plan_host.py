@@ -293,6 +293,19 @@ def test_scan_that_a_plan_takes(H, G, P, lens, want):
     p.close()
 
 
+def test_workspace_of_the_scan_with_resident_states():
+    """Only what it reads: nothing for uncut sequences; else an fp32 state and a decay per head for every segment and sum of
+    segments, a state and a flag per 32 channels for every continued piece."""
+    p = ssm.Plan(128, 64, 128, 8, 64, "bf16", [8192 * i for i in range(17)], None)
+    assert p.scan().kind == "resident" and ssm.ssm_plan_workspace_bytes(p.handle) == 0
+    p.close()
+    p = ssm.Plan(128, 64, 128, 8, 64, "bf16", [0, 131072], None)
+    s = p.scan()
+    state, slots = 128 * 64 * 128 * 4, s.n_segments + s.n_groups
+    assert ssm.ssm_plan_workspace_bytes(p.handle) == (slots + s.n_continued) * state + slots * 128 * 4 + s.n_continued * 256 * 4
+    p.close()
+
+
 def test_scan_of_an_fp32_plan():
     p = ssm.Plan(4, 16, 16, 1, 64, "f32", [0, 100], None)
     assert p.scan() == ("fp32", 0, 0, 0, 0)
