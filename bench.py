@@ -39,9 +39,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # (profiles/ssm_scan_mfma_kernel_cfg3_cfg4_hbm_bytes.txt gives the commands and the raw
 # readings): FETCH_SIZE and WRITE_SIZE in KiB per dispatch, each divided by
 # what the same counter reads per KiB actually moved by the 1 GiB copy of
-# --calibrate-copy, and the kernel they were read of.  Keyed by the hash of the kernel
-# sources the counters were taken on: once those change the figure is reported as null.
-SCAN_SOURCES = ("scan_mfma.hip", "mfma_utils.h", "scan_resident.hip")
+# --calibrate-copy.  Keyed by the hash of the sources the counters were taken on: once
+# those change the figure is reported as null.  The hash covers the kernels' sources
+# and of the plan's, which decide what those walk.
+SCAN_SOURCES = ("scan_mfma.hip", "mfma_utils.h", "scan_resident.hip", "device_utils.h", "plan.h", "plan.cpp")
 MEASURED_TRAFFIC = {
     "bfd83cbd3ddb42245a1968c8e90b6589b66cba77": {
         "cfg2_varlen16_bf16": {"fetch_bytes": 755449856, "write_bytes": 691262464, "kernel": "ssm_scan_mfma_kernel"},
@@ -270,9 +271,11 @@ def main() -> int:
     ev = [(new_event(), new_event(), new_event(), new_event()) for _ in range(args.steps)]
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    # kernels behind the scan exist only when long sequences were cut into stretches (the carried states'
-    # contribution); only then is the second event recorded
-    cut = mfma and plan.info.n_stretches > wl.batch
+    # kernels behind the scan exist only when long sequences were cut (the carried states' contribution, or values that are
+    # not finite); only then is the second event recorded
+    scan = plan.scan()
+    resident = scan.kind == "resident"
+    cut = scan.n_continued > 0 if resident else mfma and plan.info.n_stretches > wl.batch
     for a, m, m2, b in ev:
         a.record()
         if mfma:
@@ -299,12 +302,12 @@ def main() -> int:
     achieved = abytes / (kern_ms * 1e-3) / 1e9
     flops = algorithmic_flops(wl, plan.info.tile_tokens)
     traffic = None
-    # which of the two the plan took is not part of its interface; the counters say it
-    kernel = "ssm_scan_mfma_kernel or ssm_scan_resident_kernel" if mfma else "ssm_scan_f32_kernel"
+    kernel, prep_kernel = {"fp32": ("ssm_scan_f32_kernel", None), "stretches": ("ssm_scan_mfma_kernel", "ssm_prep_kernel"),
+                           "resident": ("ssm_scan_resident_kernel", "ssm_segment_state_kernel" if cut else None)}[scan.kind]
     if mfma:
         m = MEASURED_TRAFFIC.get(kernel_source_hash(), {}).get(wl.name + ("_nockpt" if args.no_checkpoints else ""))
         if m:
-            traffic, kernel = m["fetch_bytes"] + m["write_bytes"], m["kernel"]
+            traffic = m["fetch_bytes"] + m["write_bytes"]
     out = {
         "metric": "SSM-layer prefill tokens/s (1 GPU) with state checkpoints",
         "value": T / (ms_per_step * 1e-3),
@@ -323,7 +326,9 @@ def main() -> int:
                    "checkpoints": n_ckpt,
                    "initial_states": 0 if init is None else sum(1 for v in init if v is not None),
                    "kernel_path": "mfma_bf16" if mfma else "valu_f32",
-                   "workgroups": plan.info.n_workgroups, "stretches": plan.info.n_stretches, "plan_ms": plan_ms,
+                   "scan": scan.kind,
+                   "workgroups": scan.n_pieces * (s.nheads * s.headdim // 256) if resident else plan.info.n_workgroups,
+                   "stretches": scan.n_pieces if resident else plan.info.n_stretches, "plan_ms": plan_ms,
                    "call_ms_mean": float(call_ms.mean()), "call_ms_median": float(np.median(call_ms)),
                    "call_ms_min": float(call_ms.min()), "ms_per_step_with_events": events_ms_per_step},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -331,7 +336,7 @@ def main() -> int:
                      "kernel": kernel,
                      "kernel_ms": kern_ms, "kernel_ms_median": float(np.median(scan_ms)),
                      "kernel_ms_min": float(scan_ms.min()),
-                     "prep_kernel": None if not mfma else "ssm_segment_state_kernel" if "resident" in kernel else "ssm_prep_kernel", "prep_kernel_ms": float(prep_ms.mean()),
+                     "prep_kernel": prep_kernel, "prep_kernel_ms": float(prep_ms.mean()),
                      "carry_kernels_ms": float(tail_ms.mean()),
                      "algorithmic_bytes": abytes,
                      "whole_call_frac": abytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,

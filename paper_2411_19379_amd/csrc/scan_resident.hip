@@ -14,8 +14,9 @@
 //   ssm_segment_state_kernel, computes what the segments of every piece that is continued add to the state, as far as it
 //   has not decayed below 2^-150 by the end of the piece; a piece of the second kernel,
 //   ssm_scan_resident_kernel, starts from the sum of the segments in front of it.  So y is written once, from the true
-//   state.  An infinity or NaN does not decay: a third kernel, ssm_not_finite_kernel, which leaves at once if there is
-//   none, takes those in the state at the end of a piece to the rest of the sequence.
+//   state.  For pieces with many segments in front of them ssm_group_states_kernel sums these up in eights.  An infinity or
+//   NaN does not decay: a last kernel, ssm_not_finite_kernel, which leaves at once if there is none, takes those in the state
+//   at the end of a piece to the rest of the sequence.
 //
 // Time per call, this scan and the other: 128 heads, 131072 tokens 1430 us and 1850, 16 x 8192 1282 and 1689, 32 x 1024
 // 353 and 485; 80 heads, 16 requests of 500 to 7700 tokens 522 and 564; 16 heads, 32768 tokens 85 and 118.  At 128 heads
@@ -34,12 +35,6 @@
 #include "mfma_utils.h"
 
 namespace {
-
-// Wait for this wave's own LDS traffic (LDS executes a wave's accesses in order).
-__device__ __forceinline__ void lds_wait()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-}
 
 // Workgroup barrier that orders LDS traffic only: device memory accesses stay in flight.  Device memory written by these
 // kernels is never read back by the same launch.
