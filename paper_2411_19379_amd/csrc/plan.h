@@ -206,7 +206,7 @@ constexpr int kMostAddedPieces = 255;
 constexpr int kMinPieceTiles = 4;
 constexpr int kSegmentTiles = 32;
 // With slow decay a piece sums up all slots in front of it, 0.85 us each.  Where a piece may have more than kMostSlots in front
-// of it, another kernel adds up every kGroupSlots of them; below that it does not repay its launch (3 us).
+// of it, another kernel adds up every kGroupSlots of them; below that it does not repay its launch (3 to 5 us).
 constexpr int kGroupSlots = 8;
 constexpr int kMostSlots = 32;
 

@@ -20,10 +20,11 @@
 //
 // Time per call, this scan and the other: 128 heads, 131072 tokens 1430 us and 1850, 16 x 8192 1282 and 1689, 32 x 1024
 // 353 and 485; 80 heads, 16 requests of 500 to 7700 tokens 522 and 564; 16 heads, 32768 tokens 85 and 118.  At 128 heads
-// the scan kernel of 131072 tokens and 32 checkpoints takes 1270 us and moves 5.06 GB, 4.0 TB/s, the segments' 174 us and
-// 0.65 GB.  What bounds it is the serial work of a tile on a compute unit, 3.9 us with a few units busy and 5.0 us with all:
-// 41 matrix instructions per wave are 1.1 us of it (two waves per matrix core), the rest is the packing of their operands on
-// the vector units, LDS traffic and two barriers.
+// the scan kernel of 131072 tokens and 32 checkpoints takes 1280 us and moves 5.06 GB, 4.0 TB/s, the segments' 171 us and
+// 0.65 GB.  What bounds it is the serial work of a tile on a compute unit, 3.9 us with a few units busy and 5.0 us with all.
+// Counters of that call, per tile and wave: 547 vector, 41 matrix, 124 LDS, 13 memory instructions; vector units busy 45 % of
+// the time, matrix cores 27 %, LDS 45 % (22 % of it bank conflicts), waves waiting 41 %, to issue 20 %: no unit is full, two
+// waves per SIMD and two barriers per tile do not cover what each waits for.
 //
 // Lane layouts.  Everything a lane holds in runs is in natural order, eight neighbours at a time: the transpose reads that
 // fetch a B^T or x^T operand pick the four 4-column groups of a 16-column block in the order 0, 2, 1, 3, so that
@@ -465,9 +466,12 @@ __global__ __launch_bounds__(kGroupThreads) void ssm_group_states_kernel(Residen
     const int units = a.H * a.P / 32, group = blockIdx.x / units, cw = 32 * (blockIdx.x % units);
     const int h = cw / a.P, first = group * kGroupSlots;
     auto decay_of = [&](int slot) { return scalar_load(a.decay + (size_t)slot * a.H + h); };
-    float behind = first + 2 * kGroupSlots <= a.n_segments ? 0.f : -__builtin_inff();
-    for (int s = first + kGroupSlots; s < first + 2 * kGroupSlots && s < a.n_segments; ++s)
-        behind += decay_of(s);
+    float behind = 0.f;
+#pragma unroll
+    for (int s = first + kGroupSlots; s < first + 2 * kGroupSlots; ++s)
+        behind += decay_of(s < a.n_segments ? s : a.n_segments - 1);  // all loads at once
+    if (first + 2 * kGroupSlots > a.n_segments)
+        behind = -__builtin_inff();
     // f[s]: from the end of slot `first` + s to the end of the group
     float f[kGroupSlots], all = 0.f;
 #pragma unroll
