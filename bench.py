@@ -44,11 +44,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # and of the plan's, which decide what those walk.
 SCAN_SOURCES = ("scan_mfma.hip", "mfma_utils.h", "scan_resident.hip", "device_utils.h", "plan.h", "plan.cpp")
 MEASURED_TRAFFIC = {
-    "bfd83cbd3ddb42245a1968c8e90b6589b66cba77": {
-        "cfg2_varlen16_bf16": {"fetch_bytes": 755449856, "write_bytes": 691262464, "kernel": "ssm_scan_mfma_kernel"},
-        "cfg3_7b_32k_bf16": {"fetch_bytes": 843251712, "write_bytes": 546151424, "kernel": "ssm_scan_mfma_kernel"},
-        "cfg4_7b_128k_ckpt4096_bf16": {"fetch_bytes": 2772152320, "write_bytes": 2283274240,
-                                       "kernel": "ssm_scan_resident_kernel"},
+    "c1bd292776aa6d2a115bcd1bf9274439cbba74c1": {
+        "cfg2_varlen16_bf16": {"fetch_bytes": 754595084, "write_bytes": 691262464},
+        "cfg3_7b_32k_bf16": {"fetch_bytes": 843896338, "write_bytes": 546152448},
+        "cfg4_7b_128k_ckpt4096_bf16": {"fetch_bytes": 2780430023, "write_bytes": 2283281408},
     },
 }
 
