@@ -44,7 +44,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # and of the plan's, which decide what those walk.
 SCAN_SOURCES = ("scan_mfma.hip", "mfma_utils.h", "scan_resident.hip", "device_utils.h", "plan.h", "plan.cpp")
 MEASURED_TRAFFIC = {
-    "c1bd292776aa6d2a115bcd1bf9274439cbba74c1": {
+    "539b8f3b4f04ca74485ce09c07775fd7ac0d8803": {
         "cfg2_varlen16_bf16": {"fetch_bytes": 754595084, "write_bytes": 691262464},
         "cfg3_7b_32k_bf16": {"fetch_bytes": 843896338, "write_bytes": 546152448},
         "cfg4_7b_128k_ckpt4096_bf16": {"fetch_bytes": 2780430023, "write_bytes": 2283281408},
